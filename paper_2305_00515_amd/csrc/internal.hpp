@@ -42,6 +42,10 @@ struct U8Shape {
     int tallx = 0;      // batched kernel: tall chunks of tallx tile heights (0: batched_split())
 };
 
+// Magnitudes of the four-directional operator on the banded matrix-core
+// kernels (u8_band.hpp); `waves`: waves to launch (0: by size).
+hipError_t launch_band_mag(const U8Job &j, int border, int waves, hipStream_t stream);
+
 // True when the fast (vector-load) kernel may read this image: 16-byte
 // aligned base and pitch.
 bool u8_rows_aligned(const U8Job &j);
@@ -49,17 +53,13 @@ bool u8_rows_aligned(const U8Job &j);
 // Fills the tiling fields of `j` for shape `s`.
 void u8_tile(U8Job &j, const U8Shape &s);
 
-// Single image: one launch; every resident wave takes an equal row range of
-// one strip of four tiles.  `border` is the public SOBEL4X5_BORDER_* code
+// Single image: one launch.  Magnitudes alone run on the banded matrix-core
+// kernels; with planes every resident wave takes an equal row range of one
+// strip of four tiles.  `border` is the public SOBEL4X5_BORDER_* code
 // (replicate 0, valid 1, zero 2, reflect-101 3); the zero and reflect-101
 // kernels live in their own translation unit (launch_u8_single_zr).
 hipError_t launch_u8_single(const U8Job &j, int border, const U8Shape &s, hipStream_t stream);
 hipError_t launch_u8_single_zr(const U8Job &j, int border, const U8Shape &s, hipStream_t stream);
-
-// Magnitudes alone of the four-directional operator on the matrix cores
-// (u8_mfma.hpp): 32 x 128 output tiles, `waves` waves in all (0 = four
-// rounds of resident waves).  `border`: the public code.
-hipError_t launch_u8_mfma(const U8Job &j, int border, int waves, hipStream_t stream);
 
 // Magnitudes of four run-time kernels (HOST array of 4*25 int32, the layout
 // of sobel4x5_u8_weighted, already validated) on the matrix cores, when

@@ -890,11 +890,12 @@ int sobel4x5_u8(const uint8_t *src, int32_t width, int32_t height, int64_t src_p
     if (int rc = validate_u8(src, width, height, src_pitch, border, out, &Wo, &Ho)) return rc;
     U8Job j = make_job(src, width, height, src_pitch, Wo, Ho, out->mag, out->mag_pitch,
                        out->dir_type ? out->dir : nullptr, out->dir_pitch, out->dir_type);
-    const U8Shape s = default_shape(Wo, Ho, out->dir_type);
-    u8_tile(j, s);
-    if (out->dir_type == SOBEL4X5_DIR_NONE && out->mag && env_int("SOBEL4X5_U8_MFMA", 0) == 1) {
-        hipError_t e = guard(launch_u8_mfma(j, border, env_int("SOBEL4X5_U8_WAVES", 0), static_cast<hipStream_t>(stream)));
-        return e == hipSuccess ? ok() : hip_fail(e, "sobel4x5_u8 launch");
+    U8Shape s{};
+    if (out->dir_type) {
+        s = default_shape(Wo, Ho, out->dir_type);
+        u8_tile(j, s);
+    } else {
+        s.waves = env_int("SOBEL4X5_U8_WAVES", 0);
     }
     hipError_t e = guard(launch_u8_single(j, border, s, static_cast<hipStream_t>(stream)));
     return e == hipSuccess ? ok() : hip_fail(e, "sobel4x5_u8 launch");
@@ -1438,9 +1439,7 @@ int sobel4x5_pipe_run(sobel4x5_pipe p, const sobel4x5_image *imgs, int32_t count
             hipMemcpy2DAsync(sl.d_src, sl.pitch, hs, hp, m.width, m.height, hipMemcpyHostToDevice, sl.st));
         if (e != hipSuccess) return abandon(hip_fail(e, "pipeline host-to-device copy"));
         U8Job j = make_job(sl.d_src, m.width, m.height, sl.pitch, Wo, Ho, sl.d_mag, sl.pitch, nullptr, 0, 0);
-        const U8Shape shape = default_shape(Wo, Ho, SOBEL4X5_DIR_NONE);
-        u8_tile(j, shape);
-        if ((e = guard(launch_u8_single(j, border, shape, sl.st))) != hipSuccess)
+        if ((e = guard(launch_u8_single(j, border, U8Shape{}, sl.st))) != hipSuccess)
             return abandon(hip_fail(e, "pipeline launch"));
         sl.staged_out = !is_pinned(m.mag);
         e = guard(hipMemcpy2DAsync(sl.staged_out ? sl.h_mag : m.mag, sl.staged_out ? sl.pitch : m.mag_pitch,

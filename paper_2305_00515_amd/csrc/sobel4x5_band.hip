@@ -1,0 +1,74 @@
+// Launches of the banded matrix-core kernels (u8_band.hpp).
+
+#include "u8_band.hpp"
+
+#include <algorithm>
+#include <atomic>
+
+namespace s4x5 {
+namespace {
+
+// Waves the current device holds at once (256 CUs if unknown).
+int64_t band_slots()
+{
+    static std::atomic<int> cus[64];
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256 * kBandResident;
+    n = cus[dev].load(std::memory_order_relaxed);
+    if (n <= 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return (int64_t)n * kBandResident;
+}
+
+// The tile grid of one image.
+// - Rows of tiles start at multiples of 8 tiles (128 bytes of magnitudes)
+//   where that adds at most a sixteenth of the tiles, so that a wave's 256
+//   bytes of a row are whole lines.
+// - Bands: the fewest steps with which all waves are resident at once, as a
+//   wave that waits for a slot starts with a trip to memory (4096^2 at 4
+//   steps 10.7 us, at 2 12.1; 3840x2160 at 2 steps 6.9 us, at 1 8.5).  Above
+//   one step an even number (the steps come in pairs: 4001x2999 9.1 us at 4
+//   steps, 10.0 at 3).  At most 8 steps: larger images run several rounds,
+//   which hide each other's first loads and end more evenly (16384^2: 103.6
+//   us at 8 steps, 114.8 at 64; 8192^2: 25.8 at 8 and 25.7 at 16).
+template <int NB>
+BandGrid band_grid(const U8Job &j, int off, int border, int64_t slots)
+{
+    int64_t nt = (j.Wo + 4 * NB - 1) / (4 * NB);
+    const int64_t nq = (j.Ho + 3) / 4, whole = (nt + 7) / 8 * 8;
+    if ((whole - nt) * 16 <= nt) nt = whole;
+    const int64_t bands = std::max<int64_t>(1, slots * 16 / nt);
+    int64_t bq = (nq + bands - 1) / bands;
+    if (bq > 1) bq = std::min<int64_t>((bq + 1) / 2 * 2, 8);
+    while (nt * ((nq + bq - 1) / bq) > INT32_MAX) bq *= 2;   // tiles are numbered in 32 bits
+    BandGrid g;
+    g.nt = (u32)nt;
+    g.inv_nt = (u32)std::min<uint64_t>((1ull << 32) / (uint64_t)nt, 0xffffffffull);
+    g.tiles = (u32)(nt * ((nq + bq - 1) / bq));
+    g.bq = (int)bq;
+    g.off = off;
+    g.bm = border == 2 ? kBandZero : border == 3 ? kBandRefl : kBandRep;
+    return g;
+}
+
+template <int NB, int NR, bool CLAMP>
+hipError_t launch_band(const U8Job &j, const BandTaps &taps, int off, int border, int waves, hipStream_t st)
+{
+    if (j.Wo <= 0 || j.Ho <= 0) return hipSuccess;
+    const BandGrid g = band_grid<NB>(j, off, border, waves > 0 ? waves : band_slots());
+    const u32 groups = (g.tiles + 16 * kBandWaves - 1) / (16 * kBandWaves);
+    void *args[] = {const_cast<U8Job *>(&j), const_cast<BandTaps *>(&taps), const_cast<BandGrid *>(&g)};
+    return hipLaunchKernel(reinterpret_cast<const void *>(&k_band_single<NB, NR, CLAMP>), dim3(groups),
+                           dim3(64 * kBandWaves), args, 0, st);
+}
+
+}  // namespace
+
+hipError_t launch_band_mag(const U8Job &j, int border, int waves, hipStream_t st)
+{
+    return launch_band<4, 4, false>(j, kTaps4x5, border == 1 ? 2 : 0, border, waves, st);
+}
+
+}  // namespace s4x5

@@ -10,30 +10,12 @@
 namespace s4x5 {
 namespace {
 
-// Workgroup of kMWaves waves: one copy of the T table, then each wave sweeps
-// its own tiles through its own LDS tile.  Wave w takes column strip
-// w % ntx and the w / ntx-th of nchunk equal runs of 32-row tiles, so the
-// waves of a workgroup hold neighbouring strips of the same rows and the
-// workgroups that share an XCD (every eighth) hold vertically neighbouring
-// runs: the rows a run re-reads above and below come from the same L2.
-template <int OFF, int BM>
-__global__ __launch_bounds__(64 * kMWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_u8_mfma(U8Job J, int nchunk)
-{
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kLutTSize + kMWaves * kMTileBytes];
-    lut_fill_t<64 * kMWaves>(lds);
-    __syncthreads();
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int ntx = (J.Wo + kMCols - 1) / kMCols, nty = (J.Ho + kMRows - 1) / kMRows;
-    const int w = (int)blockIdx.x * kMWaves + wv;
-    if (w >= ntx * nchunk) return;
-    const int sx = w % ntx, ch = w / ntx;
-    const int b0 = (int)((int64_t)ch * nty / nchunk), b1 = (int)((int64_t)(ch + 1) * nty / nchunk);
-    const u32 tile = (u32)(size_t)(LDS uint8_t *)lds + (u32)(kLutTSize + (wv & (kMWaves - 1)) * kMTileBytes);
-    v4i A[3];
-    mfma_a_default(A);
-    mfma_strip<OFF, BM, MagT, kStageInPlace>(J, sx, b0, b1, tile, A, MagT{(const LDS uint8_t *)lds}, tile);
-}
-
+// Workgroup of kMWaves waves; each sweeps its own tiles through its own LDS
+// tile.  Wave w takes column strip w % ntx and the w / ntx-th of nchunk equal
+// runs of 32-row tiles, so the waves of a workgroup hold neighbouring strips
+// of the same rows and the workgroups that share an XCD (every eighth) hold
+// vertically neighbouring runs: the rows a run re-reads above and below come
+// from the same L2.
 // Run-time kernels (weights fitting int8): the same sweep, weight operands
 // from the launch's arguments, no table (square-root rounding), so each
 // wave also stages its output tile in LDS for full-line stores.
@@ -52,16 +34,6 @@ __global__ __launch_bounds__(64 * kMWaves) __attribute__((amdgpu_waves_per_eu(4,
     v4i A[3];
     mfma_a_runtime(W, A);
     mfma_strip<OFF, BM, MagS<CLAMP>, kStageOwn>(J, sx, b0, b1, base, A, MagS<CLAMP>{}, base + kMTileBytes);
-}
-
-const void *mfma_fn(int border)
-{
-    switch (border) {
-    case 1: return reinterpret_cast<const void *>(&k_u8_mfma<2, kBmRep>);
-    case 2: return reinterpret_cast<const void *>(&k_u8_mfma<0, kBmZero>);
-    case 3: return reinterpret_cast<const void *>(&k_u8_mfma<0, kBmRefl>);
-    default: return reinterpret_cast<const void *>(&k_u8_mfma<0, kBmRep>);
-    }
 }
 
 template <bool CLAMP>
@@ -110,12 +82,6 @@ hipError_t mfma_launch(const void *fn, const U8Job &j, int waves, void *extra, h
 }
 
 }  // namespace
-
-hipError_t launch_u8_mfma(const U8Job &j, int border, int waves, hipStream_t st)
-{
-    if (j.Wo <= 0 || j.Ho <= 0) return hipSuccess;
-    return mfma_launch(mfma_fn(border), j, waves, nullptr, st);
-}
 
 bool mfma_weights_fit(const int32_t *weights)
 {

@@ -119,6 +119,7 @@ void u8_tile(U8Job &j, const U8Shape &s)
 
 hipError_t launch_u8_single(const U8Job &j, int border, const U8Shape &s, hipStream_t st)
 {
+    if (!j.dir_type) return launch_band_mag(j, border, s.waves, st);
     if (border == 2 || border == 3) return launch_u8_single_zr(j, border, s, st);
     return launch_single_border<kOp4x5, 2, kBmRep>(j, border == 1, s, st);
 }

@@ -1,0 +1,475 @@
+// The uint8 operators as banded matrix products on the int8 matrix cores,
+// streamed from memory: no LDS, no barrier, any alignment of rows and bases.
+//
+// One v_mfma_i32_16x16x64_i8 multiplies a 16 x 64 weight block A by a 64 x 16
+// image block B.  The kernels lay it out so that the lane that loads a piece
+// of the image is the lane that stores the piece of the result at the same
+// place (n = lane % 16, g = lane / 16):
+//   B[k][n]: n = one of 16 tiles; k = (g, byte) is held by lane (g, n): four
+//            rows of a "quad" of input rows, one per lane group g, as two
+//            8-byte windows: one of quad q, one of quad q + 1 (the five rows
+//            of any of four consecutive output rows lie in two quads);
+//   A[m][k]: m = (output row j of four, response f of four): response f's
+//            weight at row offset (g or g + 4) - j, column offset byte - s,
+//            for the output column whose taps start at byte s of the window;
+//            zero off the band;
+//   D[m][n]: lane (g, n) receives m = 4 g .. 4 g + 3: the four responses of
+//            output row g, column c of tile n.
+// So a step of a wave covers 4 rows x (4 NB) columns of 16 tiles: each lane
+// loads one window of 4 NB + 8 bytes of a row (NB words and one on each
+// side), and after 4 NB products holds all responses of 4 NB consecutive
+// pixels of one row.  The first two columns of a word take the windows of
+// that word and the one before, the last two of that word and the next.  An image quad enters
+// once and serves two steps (its operand registers keep their place, and the
+// weight operands come in two orders instead).
+//
+// The tiles of a wave are 16 consecutive ones of the image's tile grid, row
+// band by row band; each lane addresses its own, so narrow images and the
+// last columns waste nothing but the last wave.  A tile whose columns would
+// pass the right edge is moved left until it ends at it: the columns it
+// shares with its neighbour get the same bytes twice.
+//
+// uint8 pixels enter as int8 through x ^ 0x80 = x - 128: every filter here
+// is antisymmetric under a half turn, so its weights sum to zero and the
+// shift leaves the response unchanged.  Responses are exact in int32.
+//
+// What bounds it: memory.  A four-directional magnitude takes 8.7 vector
+// instructions and one product a pixel (8192^2: 10.1 M wave instructions,
+// 1.05 M of them products; 18 us of issue), and HBM moves 1.07 times the
+// input and 1.00 times the output.  8192^2 takes 25.8 us, 5.2 TB/s, where a
+// plain copy of the same bytes takes 27.0 us; the packed int16 sweep that
+// ran here before took 20.4 instructions a pixel and 45.1 us.  What counted:
+//   - 16-byte stores past the L2 (nontemporal): 31.7 -> 25.8 us, and rows
+//     of the output that are not aligned to lines cost 2 us instead of 5;
+//   - windows loaded at multiples of 4 bytes: at odd addresses (kShift) a
+//     launch took 38 us before, 33 us with it (26.8 us with the stores above);
+//   - neighbouring workgroups on one XCD: 35.7 -> 31.7 us;
+//   - taking the words beside a tile from the neighbour lane's registers
+//     instead of loading them gained nothing.
+#pragma once
+
+#include "band_cols.hpp"
+#include "internal.hpp"
+
+#include <type_traits>
+
+namespace s4x5 {
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned int u32;
+typedef unsigned long long u64;
+typedef u32 bv4 __attribute__((ext_vector_type(4)));
+typedef u32 bv2 __attribute__((ext_vector_type(2)));
+// global memory at any byte address (the runtime runs the GPU in unaligned
+// access mode)
+#define BAND_G __attribute__((address_space(1)))
+typedef bv4 bv4_u __attribute__((aligned(1)));
+typedef bv2 bv2_u __attribute__((aligned(1)));
+typedef bv4 bv4_a __attribute__((aligned(4)));
+typedef bv2 bv2_a __attribute__((aligned(4)));
+typedef u32 u32_u1 __attribute__((aligned(1)));
+typedef const BAND_G uint8_t *gsrc;
+typedef BAND_G uint8_t *gdst;
+
+constexpr int kBandWaves = 4;     // waves per workgroup
+constexpr int kBandResident = 16; // waves a CU holds: 4 on each SIMD, at up to 128 VGPRs
+
+// Weights of an operator: bytes 0..4 of row[5 f + dy] are the int8 weights of
+// row dy of response f.
+struct BandTaps {
+    uint64_t row[20];
+};
+template <class K>
+constexpr BandTaps band_taps(const K &k, int responses)
+{
+    BandTaps t{};
+    for (int f = 0; f < responses; ++f)
+        for (int dy = 0; dy < 5; ++dy)
+            for (int dx = 0; dx < 5; ++dx) t.row[5 * f + dy] |= (uint64_t)(uint8_t)(int8_t)k[f][dy][dx] << (8 * dx);
+    return t;
+}
+
+// Eq. (sobel5_1) in plane order: 0, 45, 90, 135 degrees.
+constexpr int kSobel5[4][5][5] = {
+    {{-1, -2, 0, 2, 1}, {-4, -8, 0, 8, 4}, {-6, -12, 0, 12, 6}, {-4, -8, 0, 8, 4}, {-1, -2, 0, 2, 1}},
+    {{-6, -4, -1, -2, 0}, {-4, -12, -8, 0, 2}, {-1, -8, 0, 8, 1}, {-2, 0, 8, 12, 4}, {0, 2, 1, 4, 6}},
+    {{-1, -4, -6, -4, -1}, {-2, -8, -12, -8, -2}, {0, 0, 0, 0, 0}, {2, 8, 12, 8, 2}, {1, 4, 6, 4, 1}},
+    {{0, -2, -1, -4, -6}, {2, 0, -8, -12, -4}, {1, 8, 0, -8, -1}, {4, 12, 8, 0, -2}, {6, 4, 1, 2, 0}},
+};
+constexpr BandTaps kTaps4x5 = band_taps(kSobel5, 4);
+
+// Operand word of the lane's weights: bytes 0..4 of the result are the five
+// weights of row dy of response f (zero outside the filter).  The twenty
+// rows come as kernel arguments; lane i takes row i, and each lane then
+// fetches its row from there, which costs no memory access.
+__device__ __forceinline__ u64 band_tap(u32 lo, u32 hi, int f, int dy)
+{
+    const int at = 4 * (5 * f + band_clamp(dy, 0, 4));
+    const u32 a = (u32)__builtin_amdgcn_ds_bpermute(at, (int)lo);
+    const u32 b = (u32)__builtin_amdgcn_ds_bpermute(at, (int)hi);
+    return (dy >= 0 && dy <= 4) ? ((u64)b << 32 | a) : 0ull;
+}
+
+// Weight operands: NR responses a pixel (4, or 2 for the two-directional
+// operators, whose products serve two columns each), in both quad orders.
+template <int NR>
+struct BandA {
+    v4i w[2][NR];
+};
+
+template <int NR>
+__device__ __forceinline__ void band_weights(const BandTaps &T, BandA<NR> &A)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, j = (lane >> 2) & 3, r = lane & 3;
+    const int f = r % NR, cc = r / NR;
+    u32 lo = 0, hi = 0;
+#pragma unroll
+    for (int i = 0; i < 5 * NR; ++i) {
+        asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((u32)T.row[i]), "n"(i));
+        asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((u32)(T.row[i] >> 32)), "n"(i));
+    }
+    const u64 near = band_tap(lo, hi, f, g - j), far = band_tap(lo, hi, f, g + 4 - j);
+#pragma unroll
+    for (int p = 0; p < NR; ++p) {
+        const int sh = 8 * ((p * (4 / NR) + cc) ^ 2);   // columns 0..3 of a word start at bytes 2, 3, 0, 1
+        const u64 a = near << sh, b = far << sh;
+        A.w[0][p] = v4i{(int)(u32)a, (int)(u32)(a >> 32), (int)(u32)b, (int)(u32)(b >> 32)};
+        A.w[1][p] = v4i{(int)(u32)b, (int)(u32)(b >> 32), (int)(u32)a, (int)(u32)(a >> 32)};
+    }
+}
+
+// a * a + acc on the 24-bit multiplier (|a| < 2^23), one instruction.
+__device__ __forceinline__ int sq24(int a, int acc)
+{
+    int r;
+    asm("v_mad_i32_i24 %0, %1, %1, %2" : "=v"(r) : "v"(a), "v"(acc));
+    return r;
+}
+
+// One lane's tile: its first output column and row, and the number of steps
+// of four rows (the same in all lanes of a wave).
+struct BandTile {
+    int xo, yo, steps;
+};
+
+// How a wave reads its windows.
+//   kInside:  every byte and row of every lane lies in the image, and windows
+//             start at multiples of 4 bytes;
+//   kShift:   the same at other addresses: the aligned words around a window
+//             are loaded and shifted (a load of several words at an address
+//             that is no multiple of 4 takes about twice as long);
+//   kEdge:    the words beside the lane's own columns are loaded inside the
+//             row and permuted, rows are mapped;
+//   kNarrow:  rows narrower than a tile: every word is loaded inside the row
+//             and permuted.
+constexpr int kInside = 0, kShift = 1, kEdge = 2, kNarrow = 3;
+
+// Windows of the quads of one lane's tile.  load() issues the loads of the
+// next quad into `d`, words(d) puts the oldest loaded quad's words in place.
+template <int NB, int MODE>
+struct BandSource {
+    static_assert(NB == 2 || NB == 4, "words per lane");
+    static constexpr int kWords = NB + 2;
+    static constexpr int kRaw = MODE == kShift ? NB + 3 : NB + 2;
+    static constexpr int kCols = MODE == kNarrow ? kWords : 2;
+
+    gsrc p;              // kInside: the lane's window, kEdge: its own columns, kNarrow: the row's start;
+                         // in its row of the next quad (without `whole`: in row 0)
+    int64_t pitch;
+    int quads;           // quads not loaded yet; the last one is loaded again when none is left
+    int y, yf;           // the lane's row of the next quad to load / to put in place
+    int H, W, bm;
+    bool whole;          // every row of every lane lies in the image
+    int col[kCols];      // kEdge: offsets of the words beside, kNarrow: columns of all words
+    u32 sel[kCols];
+    u32 shift;           // kShift: bytes before the window in its first word
+    int last;            // kShift: offset of the word that holds the window's last byte
+
+    __device__ __forceinline__ void init(const U8Job &J, const BandTile &t, int off, int border_mode, bool rows_in)
+    {
+        const int g = (threadIdx.x >> 4) & 3;
+        const int x = t.xo + off - 4;
+        y = yf = t.yo + off - 2 + g;
+        H = J.H;
+        W = J.W;
+        bm = border_mode;
+        whole = MODE == kInside || MODE == kShift || rows_in;
+        pitch = J.src_pitch;
+        quads = t.steps + 1;
+        p = (gsrc)J.src + (MODE == kNarrow ? 0 : MODE == kEdge ? x + 4 : x);
+        if (whole) p += (int64_t)y * pitch;
+        if constexpr (MODE == kShift) {
+            // four rows below, the shift is the same
+            shift = (u32)(uintptr_t)p & 3;
+            p -= shift;
+            last = shift ? 4 * kWords : 4 * kWords - 4;
+        } else if constexpr (MODE == kEdge) {
+            col[0] = window_load(x, W) - (x + 4);
+            sel[0] = window_sel(x, W, bm);
+            col[1] = window_load(x + 4 + 4 * NB, W) - (x + 4);
+            sel[1] = window_sel(x + 4 + 4 * NB, W, bm);
+        } else if constexpr (MODE == kNarrow) {
+#pragma unroll
+            for (int b = 0; b < kWords; ++b) {
+                col[b] = window_load(x + 4 * b, W);
+                sel[b] = window_sel(x + 4 * b, W, bm);
+            }
+        }
+    }
+
+    __device__ __forceinline__ void load(u32 (&d)[kRaw])
+    {
+        gsrc r = p;
+        if (!whole) r += (int64_t)band_index(y, H, bm) * pitch;
+        if constexpr (MODE == kEdge) {
+            if constexpr (NB == 4) {
+                const bv4 v = *reinterpret_cast<const BAND_G bv4_u *>(r);
+                d[1] = v.x, d[2] = v.y, d[3] = v.z, d[4] = v.w;
+            } else {
+                const bv2 v = *reinterpret_cast<const BAND_G bv2_u *>(r);
+                d[1] = v.x, d[2] = v.y;
+            }
+            d[0] = *reinterpret_cast<const BAND_G u32_u1 *>(r + col[0]);
+            d[NB + 1] = *reinterpret_cast<const BAND_G u32_u1 *>(r + col[1]);
+        } else if constexpr (MODE == kInside || MODE == kShift) {
+            const bv4 v = *reinterpret_cast<const BAND_G bv4_a *>(r);
+            d[0] = v.x, d[1] = v.y, d[2] = v.z, d[3] = v.w;
+            if constexpr (NB == 4) {
+                const bv2 w = *reinterpret_cast<const BAND_G bv2_a *>(r + 16);
+                d[4] = w.x, d[5] = w.y;
+            }
+            if constexpr (MODE == kShift) d[kRaw - 1] = *reinterpret_cast<const BAND_G u32 *>(r + last);
+        } else if (W >= 4) {
+#pragma unroll
+            for (int b = 0; b < kWords; ++b) d[b] = *reinterpret_cast<const BAND_G u32_u1 *>(r + col[b]);
+        } else {
+            u32 v = 0;
+#pragma unroll
+            for (int t = 0; t < 3; ++t) v |= (u32)r[band_clamp(t, 0, W - 1)] << (8 * t);
+#pragma unroll
+            for (int b = 0; b < kWords; ++b) d[b] = v;
+        }
+        const bool more = --quads > 0;
+        if (whole)
+            p += more ? 4 * pitch : 0;
+        else
+            y += more ? 4 : 0;
+    }
+
+    // the window as int8
+    __device__ __forceinline__ void words(const u32 (&d)[kRaw], u32 (&e)[kWords])
+    {
+#pragma unroll
+        for (int b = 0; b < kWords; ++b)
+            {
+            if constexpr (MODE == kShift)
+                e[b] = __builtin_amdgcn_alignbyte(d[b + 1], d[b], shift);
+            else
+                e[b] = d[b];
+        }
+        if constexpr (MODE == kEdge || MODE == kNarrow) {
+            if constexpr (MODE == kEdge) {
+                e[0] = __builtin_amdgcn_perm(0u, d[0], sel[0]);
+                e[NB + 1] = __builtin_amdgcn_perm(0u, d[NB + 1], sel[1]);
+            } else {
+#pragma unroll
+                for (int b = 0; b < kWords; ++b) e[b] = __builtin_amdgcn_perm(0u, d[b], sel[b]);
+            }
+            if (!whole) {
+                const u32 keep = bm == kBandZero && (yf < 0 || yf >= H) ? 0u : ~0u;
+#pragma unroll
+                for (int b = 0; b < kWords; ++b) e[b] &= keep;
+                yf += 4;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < kWords; ++b) e[b] ^= 0x80808080u;
+    }
+};
+
+// The magnitude byte of the sum of squares S: the float conversion is exact
+// below 2^24 and anything above saturates, the root is within 1 ulp, and no
+// integer S comes nearer than 4.9e-4 to a half-way point.  Inserted as byte
+// `at` of `w` by the same instruction that rounds and saturates.
+__device__ __forceinline__ u32 mag_byte(int S, int at, u32 w)
+{
+    return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_sqrtf((float)S), at, w);
+}
+
+template <int NR, bool CLAMP>
+__device__ __forceinline__ int sum_squares(const int (&G)[NR])
+{
+    int S = 0;
+#pragma unroll
+    for (int f = 0; f < NR; ++f) {
+        const int v = CLAMP ? band_clamp(G[f], -256, 256) : G[f];
+        S = f == 0 ? __mul24(v, v) : sq24(v, S);
+    }
+    return S;
+}
+
+// One lane's share of a wave: all steps of its tile.
+template <int NB, int NR, int MODE, bool CLAMP>
+__device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T,
+                                           bool rows_in)
+{
+    constexpr int NC = 4 * NB;
+    constexpr bool IN = MODE == kInside || MODE == kShift;   // every lane's outputs lie in the image
+    constexpr bool AHEAD = MODE != kNarrow;                    // two quads in flight; narrow images are small
+    using Source = BandSource<NB, MODE>;
+    Source src;
+    src.init(J, t, off, bm, rows_in);
+    u32 raw[2][Source::kRaw];
+    v4i B[NB + 1];   // windows (word b, word b + 1), of the quad in even and the one in odd place
+    auto place = [&](const u32 (&d)[Source::kRaw], auto half) __attribute__((always_inline)) {
+        constexpr int h = decltype(half)::value;
+        u32 e[Source::kWords];
+        src.words(d, e);
+#pragma unroll
+        for (int b = 0; b <= NB; ++b) B[b][2 * h] = (int)e[b], B[b][2 * h + 1] = (int)e[b + 1];
+    };
+    BandA<NR> A;
+    if constexpr (AHEAD) {
+        src.load(raw[0]);
+        src.load(raw[1]);
+        band_weights<NR>(T, A);   // while the first rows travel
+        place(raw[0], std::integral_constant<int, 0>{});
+        src.load(raw[0]);
+    } else {
+        band_weights<NR>(T, A);
+        src.load(raw[0]);
+        place(raw[0], std::integral_constant<int, 0>{});
+    }
+
+    const int g = (threadIdx.x >> 4) & 3;
+    int yo = t.yo + g;
+    gdst mag = (gdst)J.mag + (int64_t)yo * J.mag_pitch + t.xo;
+    const int left = J.Wo - t.xo;
+    auto step = [&](auto par) __attribute__((always_inline)) {
+        constexpr int P = decltype(par)::value;
+        u32(&d)[Source::kRaw] = raw[AHEAD ? P ^ 1 : 0];
+        if constexpr (!AHEAD) src.load(d);
+        place(d, std::integral_constant<int, P ^ 1>{});
+        if constexpr (AHEAD) src.load(d);
+        // the products of a block are issued ahead of the squares of the one before
+        v4i D[2][NR];
+        auto products = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int p = 0; p < NR; ++p)
+                D[b & 1][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A.w[P][p], B[b + (p >= NR / 2)], v4i{0, 0, 0, 0}, 0, 0, 0);
+        };
+        u32 m[NB];
+        products(0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (b + 1 < NB) products(b + 1);
+            m[b] = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                int G[NR];
+#pragma unroll
+                for (int f = 0; f < NR; ++f) G[f] = D[b & 1][c * NR / 4][(c * NR + f) & 3];
+                m[b] = mag_byte(sum_squares<NR, CLAMP>(G), c, m[b]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (IN || yo < J.Ho) {
+            if (IN || left >= NC) {
+                if constexpr (NB == 4)
+                    __builtin_nontemporal_store(bv4{m[0], m[1], m[2], m[3]}, reinterpret_cast<BAND_G bv4_u *>(mag));
+                else
+                    __builtin_nontemporal_store(bv2{m[0], m[1]}, reinterpret_cast<BAND_G bv2_u *>(mag));
+            } else {
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    if (c < left) mag[c] = (uint8_t)(m[c / 4] >> (8 * (c % 4)));
+            }
+        }
+        yo += 4;
+        mag += 4 * J.mag_pitch;
+    };
+    // the first two steps stand before the loop: the loop then starts with the
+    // loads and stores in flight that it also ends with, and its waits leave
+    // them all out
+    int k = t.steps;
+    if (AHEAD && k >= 2) {
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+        for (k -= 2; k >= 2; k -= 2) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+    }
+    if constexpr (!AHEAD) {
+        for (; k >= 2; k -= 2) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+    }
+    if (k > 0) step(std::integral_constant<int, 0>{});
+}
+
+// Tile `id` of an image's tile grid: nt tile columns of 4 NB pixels, bands
+// of bq steps.
+template <int NB>
+__device__ __forceinline__ BandTile band_tile(const U8Job &J, u32 id, u32 nt, u32 inv_nt, int bq)
+{
+    BandTile t;
+    u32 band = __umulhi(id, inv_nt), tx = id - band * nt;   // at most one short
+    if (tx >= nt) ++band, tx -= nt;
+    // a tile beyond the last one that fits ends at the edge (nt may be rounded up)
+    t.xo = min((int)(tx * 4 * NB), max(J.Wo - 4 * NB, 0));
+    t.yo = 4 * bq * (int)band;
+    // tiles of the last band are shorter; a wave that starts above it runs
+    // whole bands and its rows past the image are not stored
+    t.steps = __builtin_amdgcn_readfirstlane(min(bq, (J.Ho + 3 - t.yo) / 4));
+    return t;
+}
+
+template <int NB, int NR, bool CLAMP>
+__device__ __forceinline__ void band_run(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T)
+{
+    const int x = t.xo + off - 4, y = t.yo + off - 2;
+    auto all = [](bool v) { return __builtin_amdgcn_ballot_w64(v) == ~0ull; };
+    const bool rows_in = all(y >= 0 && y + 4 * (t.steps + 1) <= J.H && t.yo + 4 * t.steps <= J.Ho);
+    const bool cols_in = all(x >= 0 && x + 4 * NB + 8 <= J.W && J.Wo >= 4 * NB);
+    const bool word = all((((u32)(uintptr_t)J.src + (u32)x) & 3) == 0) && (J.src_pitch & 3) == 0;
+    if (rows_in && cols_in && word)
+        band_sweep<NB, NR, kInside, CLAMP>(J, t, off, bm, T, true);
+    else if (rows_in && cols_in)
+        band_sweep<NB, NR, kShift, CLAMP>(J, t, off, bm, T, true);
+    else if (J.Wo >= 4 * NB)
+        band_sweep<NB, NR, kEdge, CLAMP>(J, t, off, bm, T, rows_in);
+    else
+        band_sweep<NB, NR, kNarrow, CLAMP>(J, t, off, bm, T, rows_in);
+}
+
+struct BandGrid {
+    u32 nt, inv_nt;  // tile columns; floor(2^32 / nt), at most 2^32 - 1
+    u32 tiles;       // tiles of the image
+    int bq;          // steps of a band
+    int off, bm;     // output (0, 0) is centred at input (off, off); border rule
+};
+
+// Workgroup b runs on XCD b mod 8: each XCD takes one of eight contiguous
+// stretches of the grid, so the lines that neighbours share meet in one L2.
+__device__ __forceinline__ u32 band_workgroup(u32 b, u32 groups)
+{
+    const u32 per = groups / 8;
+    return b < 8 * per ? (b & 7) * per + b / 8 : b;
+}
+
+template <int NB, int NR, bool CLAMP>
+__global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_band_single(
+    const U8Job J, const BandTaps T, const BandGrid gr)
+{
+    const u32 wave = band_workgroup(blockIdx.x, gridDim.x) * kBandWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32 id = min(16 * wave + (threadIdx.x & 15), gr.tiles - 1);
+    const BandTile t = band_tile<NB>(J, id, gr.nt, gr.inv_nt, gr.bq);
+    if (16 * wave >= gr.tiles) return;
+    band_run<NB, NR, CLAMP>(J, t, gr.off, gr.bm, T);
+}
+
+}  // namespace
+}  // namespace s4x5

@@ -1,0 +1,51 @@
+"""GPU parity of the banded matrix-core kernels (u8_band.hpp) against the CPU
+oracle, bit-exact, where their loads and tiles can go wrong."""
+import numpy as np
+import pytest
+
+from paper_2305_00515_amd import synth
+from test_gpu_u8 import run
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def check_mag(oracle_mod, api, img, dev, border, **kw):
+    mag, _, flat = run(api, img, dev, border, 0, **kw)
+    om, _ = oracle_mod.sobel_u8(np.ascontiguousarray(img), border, want_dir=False)
+    bad = int((mag != om).sum())
+    assert bad == 0, "border %d, %s, %s: %d pixels differ" % (border, img.shape, kw, bad)
+
+
+# 16-column tiles, quads of 4 rows, waves of 16 tiles (256 columns), rows of
+# fewer than 4 bytes: widths and heights on both sides of each
+WIDTHS = [1, 2, 3, 4, 5, 7, 15, 16, 17, 19, 20, 23, 24, 31, 33, 40, 127, 240, 255, 257, 272, 529]
+
+
+@pytest.mark.parametrize("border", [0, 1, 2, 3])
+@pytest.mark.parametrize("w", WIDTHS)
+def test_widths_heights_and_borders(oracle_mod, sobel_lib, gpu, border, w):
+    for h in (1, 2, 3, 4, 5, 8, 9, 13, 34):
+        if border == 1 and (h < 5 or w < 5):
+            continue
+        # small values: the magnitudes do not saturate
+        check_mag(oracle_mod, sobel_lib, synth.rect_image(h, w, 97 * h + w) % 5, gpu, border)
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 3, 4, 9])
+def test_any_alignment(oracle_mod, sobel_lib, gpu, offset):
+    """Rows at every byte alignment, in and out, wide enough for waves whose
+    windows all lie inside the image."""
+    img = synth.rect_image(53, 1100, 40 + offset) % 7
+    for pitch in (1100, 1101, 1102, 1103, 1280):
+        for border in (0, 1):
+            check_mag(oracle_mod, sobel_lib, img, gpu, border, pitch=pitch, offset=offset, mag_pitch=1100 + offset)
+
+
+@pytest.mark.parametrize("h,w", [(520, 2050), (1031, 4001), (4099, 2057), (70000, 33)])
+def test_bands_of_several_steps(oracle_mod, sobel_lib, gpu, h, w):
+    """Bands of 2 to 8 steps, even and odd last bands, tile rows that end
+    inside a wave, more waves than one round."""
+    img = synth.rect_image(h, w, h + w)
+    for border in (0, 3):
+        check_mag(oracle_mod, sobel_lib, img, gpu, border)
