@@ -36,15 +36,9 @@ struct U8Shape {
     int ppl;        // pixels per lane: 8 or 16
     int th;         // rows per tile (batched kernel)
     int wpg;        // waves per workgroup (4)
-    int waves = 0;  // single-image kernel: waves to launch (0 = all resident waves)
-    int min_rows = 2;   // single-image kernel: fewest output rows per wave (small images are latency-bound)
-    bool sep = false;   // four-directional magnitudes in the separable form (the kernel that also serves planes)
+    int waves = 0;  // single image: waves to launch (0 = by size); batched: kStaticGrid or a persistent grid
     int tallx = 0;      // batched kernel: tall chunks of tallx tile heights (0: batched_split())
 };
-
-// Magnitudes of the four-directional operator on the banded matrix-core
-// kernels (u8_band.hpp); `waves`: waves to launch (0: by size).
-hipError_t launch_band_mag(const U8Job &j, int border, int waves, hipStream_t stream);
 
 // True when the fast (vector-load) kernel may read this image: 16-byte
 // aligned base and pitch.
@@ -53,13 +47,10 @@ bool u8_rows_aligned(const U8Job &j);
 // Fills the tiling fields of `j` for shape `s`.
 void u8_tile(U8Job &j, const U8Shape &s);
 
-// Single image: one launch.  Magnitudes alone run on the banded matrix-core
-// kernels; with planes every resident wave takes an equal row range of one
-// strip of four tiles.  `border` is the public SOBEL4X5_BORDER_* code
-// (replicate 0, valid 1, zero 2, reflect-101 3); the zero and reflect-101
-// kernels live in their own translation unit (launch_u8_single_zr).
+// Single image: one launch of the banded matrix-core kernels (u8_band.hpp),
+// magnitude and/or planes.  `border` is the public SOBEL4X5_BORDER_* code
+// (replicate 0, valid 1, zero 2, reflect-101 3).
 hipError_t launch_u8_single(const U8Job &j, int border, const U8Shape &s, hipStream_t stream);
-hipError_t launch_u8_single_zr(const U8Job &j, int border, const U8Shape &s, hipStream_t stream);
 
 // Magnitudes of four run-time kernels (HOST array of 4*25 int32, the layout
 // of sobel4x5_u8_weighted, already validated) on the matrix cores, when
@@ -67,11 +58,10 @@ hipError_t launch_u8_single_zr(const U8Job &j, int border, const U8Shape &s, hip
 bool mfma_weights_fit(const int32_t *weights);
 hipError_t launch_u8_mfma_weighted(const U8Job &j, int border, const int32_t *weights, int waves, hipStream_t stream);
 
-// Two-directional operators on the single-image sweep: op 1 = the 0 / 90 deg
-// filters of the 5x5 operator, op 2 = the 3x3 pair (VALID: off = 1).  The
-// job's Wo, Ho and tiling are those of the operator's own border rule.
+// The same for the two-directional operators: op 1 = the 0 / 90 deg filters of
+// the 5x5 operator, op 2 = the 3x3 pair (VALID: output (0, 0) is centred at
+// input (1, 1)).  The job's Wo, Ho are those of the operator's own border rule.
 hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, hipStream_t stream);
-hipError_t launch_u8_2dir_zr(const U8Job &j, int op, int border, const U8Shape &s, hipStream_t stream);
 
 // Batched persistent launch (`aligned`: every image may take the vector
 // path: 16-byte aligned src rows, and at least 3 columns under reflect-101).

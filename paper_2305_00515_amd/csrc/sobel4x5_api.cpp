@@ -181,79 +181,16 @@ int env_int(const char *name, int dflt)
     return (end && *end == 0 && x >= 0 && x < (1 << 30)) ? (int)x : dflt;
 }
 
-// Shape for one image: 16 pixels per lane when a strip of four 256-column
-// tiles is mostly inside the image, else 8; directional outputs use 8 (their
-// kernel keeps more values live).  SOBEL4X5_U8_PPL (8 or 16),
-// SOBEL4X5_U8_WAVES (waves to launch) and SOBEL4X5_U8_MIN_ROWS (fewest rows
-// per wave) override the choice for tuning runs.
 // U8Shape::waves of a batched plan that launches one wave per tile (static
 // form, no work queue) instead of a persistent grid.
 constexpr int kStaticGrid = 1 << 30;
 
-// Compute units of the current device (cached per device; 256 if unknown).
-int device_cus()
+// Shape of a single-image launch: by size, unless SOBEL4X5_U8_WAVES (waves to
+// launch) overrides it for tuning runs.
+U8Shape single_shape()
 {
-    static std::atomic<int> cache[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int n = cache[dev].load(std::memory_order_relaxed);
-    if (n > 0) return n;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cache[dev].store(n, std::memory_order_relaxed);
-    return n;
-}
-
-U8Shape default_shape(int32_t Wo, int32_t Ho, int32_t dir_type, int32_t op = SOBEL4X5_OP_4DIR_5X5)
-{
-    U8Shape s;
-    // The four-directional magnitude kernel (binomial form) runs 8 pixels
-    // per lane at three waves per SIMD at every size: at 16 it needs more
-    // than the 256 registers of two waves per SIMD (8192^2: 46.2 against
-    // 60.4 us; 16384^2: 162 against 180 us).  The two-directional operators
-    // take 16 pixels per lane (1024-column strips) only where that shape
-    // alone fills one round of resident waves (2 per SIMD, 8 per CU) with
-    // its 2-row minimum ranges; smaller images have too few waves.
-    const int64_t strips16 = (Wo + 1023) / 1024;
-    const bool fills = strips16 * (Ho / 2) >= 8 * (int64_t)device_cus();
-    s.ppl = (fills && dir_type == SOBEL4X5_DIR_NONE && op != SOBEL4X5_OP_4DIR_5X5) ? 16 : 8;
-    // The binomial form does most of its work once per input row, so a
-    // wave that gets few rows pays heavily for the 4 rows above its range:
-    // below 8 rows per wave (one round of 12 waves per CU over 512-column
-    // strips) the four-directional magnitude takes the separable form
-    // (graph replay: 512^2 3.48 against 4.32 us, 1920x1080 6.92 against
-    // 9.33, 3840x2160 12.6 against 13.9; from 4096^2 on the binomial form
-    // wins: 17.4 against 18.1), with 4-row minimum ranges from 2048 rows on.
-    // The same holds for the 0 / 90 deg pair of the 5x5 operator at 8 pixels
-    // per lane (graph replay: 1024^2 4.00 against 4.34 us; 8192^2 binomial
-    // 31.2 against 37.2); at 16 (from 2048^2 on) its separable kernel that
-    // can also write planes runs one wave per SIMD fewer, and the binomial
-    // form stays (2048^2: 6.96 against 7.39 us).
-    if ((op == SOBEL4X5_OP_4DIR_5X5 || (op == SOBEL4X5_OP_2DIR_5X5 && s.ppl == 8)) &&
-        dir_type == SOBEL4X5_DIR_NONE) {
-        const int64_t strips8 = (Wo + 511) / 512;
-        const int64_t nchunk = std::max<int64_t>(1, std::min<int64_t>(12 * (int64_t)device_cus() / strips8, Ho / 2));
-        if (Ho < 8 * nchunk) {
-            s.sep = true;
-            if (op == SOBEL4X5_OP_4DIR_5X5 && Ho >= 2048) s.min_rows = 4;
-        }
-    }
-    const int ppl = env_int("SOBEL4X5_U8_PPL", 0);
-    if (ppl == 8 || ppl == 16) s.ppl = ppl;
-    s.th = 32;
-    s.wpg = 4;
-    // Directional planes (up to 17 B/px) are bound by the stores: many short
-    // row ranges, 4 rows each, beat one round of resident waves (8192^2 int16
-    // planes: 487 against 432 Gpx/s).
-    if (dir_type != SOBEL4X5_DIR_NONE) {
-        s.waves = 1 << 30;
-        s.min_rows = 4;
-    }
-    const int waves = env_int("SOBEL4X5_U8_WAVES", 0);
-    if (waves > 0) s.waves = waves;
-    const int mr = env_int("SOBEL4X5_U8_MIN_ROWS", 0);
-    if (mr >= 1 && mr <= 64) s.min_rows = mr;
-    const int sep = env_int("SOBEL4X5_U8_SEP", -1);
-    if (sep == 0 || sep == 1) s.sep = sep == 1;
+    U8Shape s{};
+    s.waves = env_int("SOBEL4X5_U8_WAVES", 0);
     return s;
 }
 
@@ -890,14 +827,7 @@ int sobel4x5_u8(const uint8_t *src, int32_t width, int32_t height, int64_t src_p
     if (int rc = validate_u8(src, width, height, src_pitch, border, out, &Wo, &Ho)) return rc;
     U8Job j = make_job(src, width, height, src_pitch, Wo, Ho, out->mag, out->mag_pitch,
                        out->dir_type ? out->dir : nullptr, out->dir_pitch, out->dir_type);
-    U8Shape s{};
-    if (out->dir_type) {
-        s = default_shape(Wo, Ho, out->dir_type);
-        u8_tile(j, s);
-    } else {
-        s.waves = env_int("SOBEL4X5_U8_WAVES", 0);
-    }
-    hipError_t e = guard(launch_u8_single(j, border, s, static_cast<hipStream_t>(stream)));
+    hipError_t e = guard(launch_u8_single(j, border, single_shape(), static_cast<hipStream_t>(stream)));
     return e == hipSuccess ? ok() : hip_fail(e, "sobel4x5_u8 launch");
 }
 
@@ -921,16 +851,7 @@ int sobel4x5_u8_op(const uint8_t *src, int32_t width, int32_t height, int64_t sr
     }
     U8Job j = make_job(src, width, height, src_pitch, Wo, Ho, out->mag, out->mag_pitch,
                        out->dir_type ? dirs : nullptr, out->dir_pitch, out->dir_type);
-    U8Shape s = default_shape(Wo, Ho, out->dir_type, op);
-    u8_tile(j, s);
-    // The two-directional operators are lighter on arithmetic, so the 4-row
-    // prologue each wave re-reads weighs more: on large images they take
-    // 32-row ranges as long as one round of resident waves (8 per CU)
-    // remains (8192^2 3x3: 2128 -> 2232 Gpx/s).
-    if (out->dir_type == SOBEL4X5_DIR_NONE && env_int("SOBEL4X5_U8_MIN_ROWS", 0) == 0 &&
-        (int64_t)((j.ntx + 3) / 4) * (Ho / 32) >= 8 * (int64_t)device_cus())
-        s.min_rows = 32;
-    hipError_t e = launch_u8_2dir(j, op, border, s, static_cast<hipStream_t>(stream));
+    hipError_t e = launch_u8_2dir(j, op, border, single_shape(), static_cast<hipStream_t>(stream));
     return e == hipSuccess ? ok() : hip_fail(e, "sobel4x5_u8_op launch");
 }
 

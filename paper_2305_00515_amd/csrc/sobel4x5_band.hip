@@ -33,15 +33,21 @@ int64_t band_slots()
 //   steps, 10.0 at 3).  At most 8 steps: larger images run several rounds,
 //   which hide each other's first loads and end more evenly (16384^2: 103.6
 //   us at 8 steps, 114.8 at 64; 8192^2: 25.8 at 8 and 25.7 at 16).
+// - With planes one step: the stores bound it, and many short waves store in
+//   the order of memory (4096^2 with int16 planes 24.6 us at 1 step, 27.8 at
+//   2, 31.5 at 8; int32 52.5, 53.3, 55.0).
 template <int NB>
-BandGrid band_grid(const U8Job &j, int off, int border, int64_t slots)
+BandGrid band_grid(const U8Job &j, int off, int border, int64_t slots, bool planes)
 {
     int64_t nt = (j.Wo + 4 * NB - 1) / (4 * NB);
     const int64_t nq = (j.Ho + 3) / 4, whole = (nt + 7) / 8 * 8;
     if ((whole - nt) * 16 <= nt) nt = whole;
     const int64_t bands = std::max<int64_t>(1, slots * 16 / nt);
     int64_t bq = (nq + bands - 1) / bands;
-    if (bq > 1) bq = std::min<int64_t>((bq + 1) / 2 * 2, 8);
+    if (planes)
+        bq = 1;
+    else if (bq > 1)
+        bq = std::min<int64_t>((bq + 1) / 2 * 2, 8);
     while (nt * ((nq + bq - 1) / bq) > INT32_MAX) bq *= 2;   // tiles are numbered in 32 bits
     BandGrid g;
     g.nt = (u32)nt;
@@ -53,22 +59,37 @@ BandGrid band_grid(const U8Job &j, int off, int border, int64_t slots)
     return g;
 }
 
-template <int NB, int NR, bool CLAMP>
+template <int NB, int NR, bool CLAMP, int DIR>
 hipError_t launch_band(const U8Job &j, const BandTaps &taps, int off, int border, int waves, hipStream_t st)
 {
     if (j.Wo <= 0 || j.Ho <= 0) return hipSuccess;
-    const BandGrid g = band_grid<NB>(j, off, border, waves > 0 ? waves : band_slots());
+    const BandGrid g = band_grid<NB>(j, off, border, waves > 0 ? waves : band_slots(), DIR != 0);
     const u32 groups = (g.tiles + 16 * kBandWaves - 1) / (16 * kBandWaves);
     void *args[] = {const_cast<U8Job *>(&j), const_cast<BandTaps *>(&taps), const_cast<BandGrid *>(&g)};
-    return hipLaunchKernel(reinterpret_cast<const void *>(&k_band_single<NB, NR, CLAMP>), dim3(groups),
+    return hipLaunchKernel(reinterpret_cast<const void *>(&k_band_single<NB, NR, CLAMP, DIR>), dim3(groups),
                            dim3(64 * kBandWaves), args, 0, st);
 }
 
 }  // namespace
 
-hipError_t launch_band_mag(const U8Job &j, int border, int waves, hipStream_t st)
+hipError_t launch_u8_single(const U8Job &j, int border, const U8Shape &s, hipStream_t st)
 {
-    return launch_band<4, 4, false>(j, kTaps4x5, border == 1 ? 2 : 0, border, waves, st);
+    const int off = border == 1 ? 2 : 0;
+    if (!j.dir_type) return launch_band<4, 4, false, 0>(j, kTaps4x5, off, border, s.waves, st);
+    // planes: 16 bytes of a plane a lane, so that a wave's stores are whole
+    // lines (int32 planes of 4096^2: 52.5 us, with two stores a lane 113)
+    if (j.dir_type == 1) return launch_band<2, 4, false, kPlanes16>(j, kTaps4x5, off, border, s.waves, st);
+    return launch_band<1, 4, false, kPlanes32>(j, kTaps4x5, off, border, s.waves, st);
+}
+
+hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, hipStream_t st)
+{
+    const bool small = op == 2;
+    const int off = border != 1 ? 0 : small ? 1 : 2;
+    const BandTaps &taps = small ? kTaps2x3 : kTaps2x5;
+    if (!j.dir_type) return launch_band<4, 2, false, 0>(j, taps, off, border, s.waves, st);
+    if (j.dir_type == 1) return launch_band<2, 2, false, kPlanes16>(j, taps, off, border, s.waves, st);
+    return launch_band<1, 2, false, kPlanes32>(j, taps, off, border, s.waves, st);
 }
 
 }  // namespace s4x5

@@ -1,9 +1,8 @@
-// uint8 four-directional 5x5 kernel for CDNA4 (gfx950): the single-image
-// launch of the sweep in u8_sweep.hpp for the replicate and valid borders
-// (zero and reflect-101: sobel4x5_u8_border.hip), and a plain copy kernel
-// that serves as the bandwidth reference.
+// A plain copy kernel that serves as the bandwidth reference, the
+// autotuner's fingerprint of output planes, and the diagnostics of the uint8
+// roundings.
 
-#include "u8_launch.hpp"
+#include "u8_sweep.hpp"
 
 namespace s4x5 {
 namespace {
@@ -115,13 +114,6 @@ void u8_tile(U8Job &j, const U8Shape &s)
     j.nty4 = (j.nty + 3) / 4;
     j.nwt = j.ntx * j.nty4;
     j.nwt_h = ((j.ntx + 3) / 4) * j.nty;
-}
-
-hipError_t launch_u8_single(const U8Job &j, int border, const U8Shape &s, hipStream_t st)
-{
-    if (!j.dir_type) return launch_band_mag(j, border, s.waves, st);
-    if (border == 2 || border == 3) return launch_u8_single_zr(j, border, s, st);
-    return launch_single_border<kOp4x5, 2, kBmRep>(j, border == 1, s, st);
 }
 
 hipError_t launch_copy16(const void *src, void *dst, int64_t n16, hipStream_t st)

@@ -60,6 +60,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned int u32;
 typedef unsigned long long u64;
 typedef u32 bv4 __attribute__((ext_vector_type(4)));
+typedef u32 bv3 __attribute__((ext_vector_type(3)));
 typedef u32 bv2 __attribute__((ext_vector_type(2)));
 // global memory at any byte address (the runtime runs the GPU in unaligned
 // access mode)
@@ -67,6 +68,7 @@ typedef u32 bv2 __attribute__((ext_vector_type(2)));
 typedef bv4 bv4_u __attribute__((aligned(1)));
 typedef bv2 bv2_u __attribute__((aligned(1)));
 typedef bv4 bv4_a __attribute__((aligned(4)));
+typedef bv3 bv3_a __attribute__((aligned(4)));
 typedef bv2 bv2_a __attribute__((aligned(4)));
 typedef u32 u32_u1 __attribute__((aligned(1)));
 typedef const BAND_G uint8_t *gsrc;
@@ -97,7 +99,15 @@ constexpr int kSobel5[4][5][5] = {
     {{-1, -4, -6, -4, -1}, {-2, -8, -12, -8, -2}, {0, 0, 0, 0, 0}, {2, 8, 12, 8, 2}, {1, 4, 6, 4, 1}},
     {{0, -2, -1, -4, -6}, {2, 0, -8, -12, -4}, {1, 8, 0, -8, -1}, {4, 12, 8, 0, -2}, {6, 4, 1, 2, 0}},
 };
-constexpr BandTaps kTaps4x5 = band_taps(kSobel5, 4);
+// Eq. (sobel3_1), 0 and 90 degrees, in the middle of a 5x5 window.
+constexpr int kSobel3[2][5][5] = {
+    {{0, 0, 0, 0, 0}, {0, -1, 0, 1, 0}, {0, -2, 0, 2, 0}, {0, -1, 0, 1, 0}, {0, 0, 0, 0, 0}},
+    {{0, 0, 0, 0, 0}, {0, -1, -2, -1, 0}, {0, 0, 0, 0, 0}, {0, 1, 2, 1, 0}, {0, 0, 0, 0, 0}},
+};
+struct Pair5 {   // the 0 and 90 degree filters of Eq. (sobel5_1)
+    constexpr const int (&operator[](int f) const)[5][5] { return kSobel5[2 * f]; }
+};
+constexpr BandTaps kTaps4x5 = band_taps(kSobel5, 4), kTaps2x5 = band_taps(Pair5{}, 2), kTaps2x3 = band_taps(kSobel3, 2);
 
 // Operand word of the lane's weights: bytes 0..4 of the result are the five
 // weights of row dy of response f (zero outside the filter).  The twenty
@@ -169,7 +179,7 @@ constexpr int kInside = 0, kShift = 1, kEdge = 2, kNarrow = 3;
 // next quad into `d`, words(d) puts the oldest loaded quad's words in place.
 template <int NB, int MODE>
 struct BandSource {
-    static_assert(NB == 2 || NB == 4, "words per lane");
+    static_assert(NB == 1 || NB == 2 || NB == 4, "words per lane");
     static constexpr int kWords = NB + 2;
     static constexpr int kRaw = MODE == kShift ? NB + 3 : NB + 2;
     static constexpr int kCols = MODE == kNarrow ? kWords : 2;
@@ -226,15 +236,22 @@ struct BandSource {
             if constexpr (NB == 4) {
                 const bv4 v = *reinterpret_cast<const BAND_G bv4_u *>(r);
                 d[1] = v.x, d[2] = v.y, d[3] = v.z, d[4] = v.w;
-            } else {
+            } else if constexpr (NB == 2) {
                 const bv2 v = *reinterpret_cast<const BAND_G bv2_u *>(r);
                 d[1] = v.x, d[2] = v.y;
+            } else {
+                d[1] = *reinterpret_cast<const BAND_G u32_u1 *>(r);
             }
             d[0] = *reinterpret_cast<const BAND_G u32_u1 *>(r + col[0]);
             d[NB + 1] = *reinterpret_cast<const BAND_G u32_u1 *>(r + col[1]);
         } else if constexpr (MODE == kInside || MODE == kShift) {
-            const bv4 v = *reinterpret_cast<const BAND_G bv4_a *>(r);
-            d[0] = v.x, d[1] = v.y, d[2] = v.z, d[3] = v.w;
+            if constexpr (NB >= 2) {
+                const bv4 v = *reinterpret_cast<const BAND_G bv4_a *>(r);
+                d[0] = v.x, d[1] = v.y, d[2] = v.z, d[3] = v.w;
+            } else {
+                const bv3 v = *reinterpret_cast<const BAND_G bv3_a *>(r);
+                d[0] = v.x, d[1] = v.y, d[2] = v.z;
+            }
             if constexpr (NB == 4) {
                 const bv2 w = *reinterpret_cast<const BAND_G bv2_a *>(r + 16);
                 d[4] = w.x, d[5] = w.y;
@@ -309,8 +326,46 @@ __device__ __forceinline__ int sum_squares(const int (&G)[NR])
     return S;
 }
 
-// One lane's share of a wave: all steps of its tile.
-template <int NB, int NR, int MODE, bool CLAMP>
+// 4 N bytes at any address, past the L2: nothing here reads them again.
+template <int N>
+__device__ __forceinline__ void store_words(gdst p, const u32 (&w)[N])
+{
+    if constexpr (N % 4 == 0) {
+#pragma unroll
+        for (int i = 0; i < N; i += 4)
+            __builtin_nontemporal_store(bv4{w[i], w[i + 1], w[i + 2], w[i + 3]}, reinterpret_cast<BAND_G bv4_u *>(p + 4 * i));
+    } else if constexpr (N == 2) {
+        __builtin_nontemporal_store(bv2{w[0], w[1]}, reinterpret_cast<BAND_G bv2_u *>(p));
+    } else {
+        static_assert(N == 1, "words");
+        __builtin_nontemporal_store(w[0], reinterpret_cast<BAND_G u32_u1 *>(p));
+    }
+}
+
+// The same of a tile that is wider than the image: the first `left` of its
+// elements of ES bytes.
+template <int ES, int N>
+__device__ __forceinline__ void store_left(gdst p, const u32 (&w)[N], int left)
+{
+#pragma unroll
+    for (int c = 0; c < 4 * N / ES; ++c)
+        if (c < left) {
+            if constexpr (ES == 1)
+                p[c] = (uint8_t)(w[c / 4] >> (8 * (c % 4)));
+            else if constexpr (ES == 2)
+                *reinterpret_cast<BAND_G uint16_t *>(p + 2 * c) = (uint16_t)(w[c / 2] >> (16 * (c % 2)));
+            else
+                *reinterpret_cast<BAND_G u32 *>(p + 4 * c) = w[c];
+        }
+}
+
+// One lane's share of a wave: all steps of its tile.  DIR: the job may also
+// ask for the responses themselves (directional planes) and do without the
+// magnitude; the planes are int16 (kPlanes16), int32 (kPlanes32) or what the
+// job says, none included (kPlanesAny).
+constexpr int kPlanes16 = 1, kPlanes32 = 2, kPlanesAny = 3;
+
+template <int NB, int NR, int MODE, bool CLAMP, int DIR>
 __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T,
                                            bool rows_in)
 {
@@ -345,6 +400,7 @@ __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, in
     const int g = (threadIdx.x >> 4) & 3;
     int yo = t.yo + g;
     gdst mag = (gdst)J.mag + (int64_t)yo * J.mag_pitch + t.xo;
+    int64_t plane = DIR ? (int64_t)yo * J.dir_pitch + (int64_t)t.xo * (2 * J.dir_type) : 0;
     const int left = J.Wo - t.xo;
     auto step = [&](auto par) __attribute__((always_inline)) {
         constexpr int P = decltype(par)::value;
@@ -360,32 +416,60 @@ __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, in
                 D[b & 1][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A.w[P][p], B[b + (p >= NR / 2)], v4i{0, 0, 0, 0}, 0, 0, 0);
         };
         u32 m[NB];
+        u32 s16[NR][2 * NB], s32[NR][4 * NB];
         products(0);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             if (b + 1 < NB) products(b + 1);
+            int G[4][NR];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int f = 0; f < NR; ++f) G[c][f] = D[b & 1][c * NR / 4][(c * NR + f) & 3];
             m[b] = 0;
+            if (!DIR || J.mag) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                int G[NR];
+                for (int c = 0; c < 4; ++c) m[b] = mag_byte(sum_squares<NR, CLAMP>(G[c]), c, m[b]);
+            }
+            if constexpr (DIR) {
 #pragma unroll
-                for (int f = 0; f < NR; ++f) G[f] = D[b & 1][c * NR / 4][(c * NR + f) & 3];
-                m[b] = mag_byte(sum_squares<NR, CLAMP>(G), c, m[b]);
+                for (int f = 0; f < NR; ++f) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) s32[f][4 * b + c] = (u32)G[c][f];
+                    s16[f][2 * b] = __builtin_amdgcn_perm((u32)G[1][f], (u32)G[0][f], 0x05040100u);
+                    s16[f][2 * b + 1] = __builtin_amdgcn_perm((u32)G[3][f], (u32)G[2][f], 0x05040100u);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         if (IN || yo < J.Ho) {
-            if (IN || left >= NC) {
-                if constexpr (NB == 4)
-                    __builtin_nontemporal_store(bv4{m[0], m[1], m[2], m[3]}, reinterpret_cast<BAND_G bv4_u *>(mag));
+            const bool full = IN || left >= NC;
+            if (!DIR || J.mag) {
+                if (full)
+                    store_words(mag, m);
                 else
-                    __builtin_nontemporal_store(bv2{m[0], m[1]}, reinterpret_cast<BAND_G bv2_u *>(mag));
-            } else {
+                    store_left<1>(mag, m, left);
+            }
+            if constexpr (DIR) {
+                // the two-directional operators fill planes 0 and 2
 #pragma unroll
-                for (int c = 0; c < NC; ++c)
-                    if (c < left) mag[c] = (uint8_t)(m[c / 4] >> (8 * (c % 4)));
+                for (int f = 0; f < NR; ++f) {
+                    gdst p = (gdst)J.dir[f * 4 / NR] + plane;
+                    if ((DIR & kPlanes16) && (DIR != kPlanesAny || J.dir_type == 1)) {
+                        if (full)
+                            store_words(p, s16[f]);
+                        else
+                            store_left<2>(p, s16[f], left);
+                    } else if ((DIR & kPlanes32) && (DIR != kPlanesAny || J.dir_type == 2)) {
+                        if (full)
+                            store_words(p, s32[f]);
+                        else
+                            store_left<4>(p, s32[f], left);
+                    }
+                }
             }
         }
+        if (DIR) plane += 4 * J.dir_pitch;
         yo += 4;
         mag += 4 * J.mag_pitch;
     };
@@ -427,7 +511,7 @@ __device__ __forceinline__ BandTile band_tile(const U8Job &J, u32 id, u32 nt, u3
     return t;
 }
 
-template <int NB, int NR, bool CLAMP>
+template <int NB, int NR, bool CLAMP, int DIR>
 __device__ __forceinline__ void band_run(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T)
 {
     const int x = t.xo + off - 4, y = t.yo + off - 2;
@@ -436,13 +520,13 @@ __device__ __forceinline__ void band_run(const U8Job &J, const BandTile &t, int 
     const bool cols_in = all(x >= 0 && x + 4 * NB + 8 <= J.W && J.Wo >= 4 * NB);
     const bool word = all((((u32)(uintptr_t)J.src + (u32)x) & 3) == 0) && (J.src_pitch & 3) == 0;
     if (rows_in && cols_in && word)
-        band_sweep<NB, NR, kInside, CLAMP>(J, t, off, bm, T, true);
+        band_sweep<NB, NR, kInside, CLAMP, DIR>(J, t, off, bm, T, true);
     else if (rows_in && cols_in)
-        band_sweep<NB, NR, kShift, CLAMP>(J, t, off, bm, T, true);
+        band_sweep<NB, NR, kShift, CLAMP, DIR>(J, t, off, bm, T, true);
     else if (J.Wo >= 4 * NB)
-        band_sweep<NB, NR, kEdge, CLAMP>(J, t, off, bm, T, rows_in);
+        band_sweep<NB, NR, kEdge, CLAMP, DIR>(J, t, off, bm, T, rows_in);
     else
-        band_sweep<NB, NR, kNarrow, CLAMP>(J, t, off, bm, T, rows_in);
+        band_sweep<NB, NR, kNarrow, CLAMP, DIR>(J, t, off, bm, T, rows_in);
 }
 
 struct BandGrid {
@@ -460,15 +544,15 @@ __device__ __forceinline__ u32 band_workgroup(u32 b, u32 groups)
     return b < 8 * per ? (b & 7) * per + b / 8 : b;
 }
 
-template <int NB, int NR, bool CLAMP>
-__global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_band_single(
+template <int NB, int NR, bool CLAMP, int DIR>
+__global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(DIR ? 3 : 4, 4))) void k_band_single(
     const U8Job J, const BandTaps T, const BandGrid gr)
 {
     const u32 wave = band_workgroup(blockIdx.x, gridDim.x) * kBandWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const u32 id = min(16 * wave + (threadIdx.x & 15), gr.tiles - 1);
     const BandTile t = band_tile<NB>(J, id, gr.nt, gr.inv_nt, gr.bq);
     if (16 * wave >= gr.tiles) return;
-    band_run<NB, NR, CLAMP>(J, t, gr.off, gr.bm, T);
+    band_run<NB, NR, CLAMP, DIR>(J, t, gr.off, gr.bm, T);
 }
 
 }  // namespace

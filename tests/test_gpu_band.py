@@ -49,3 +49,36 @@ def test_bands_of_several_steps(oracle_mod, sobel_lib, gpu, h, w):
     img = synth.rect_image(h, w, h + w)
     for border in (0, 3):
         check_mag(oracle_mod, sobel_lib, img, gpu, border)
+
+
+# planes: tiles of 8 columns (int16) or 4 (int32), stores of 16 bytes a plane
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("dir_type", [1, 2])
+@pytest.mark.parametrize("w", [3, 4, 5, 7, 8, 9, 12, 17, 64, 65, 129, 270])
+def test_planes(oracle_mod, sobel_lib, gpu, op, dir_type, w):
+    """Planes of every operator, with and without the magnitude, rows at odd
+    element offsets, guard columns untouched."""
+    dt = torch.int16 if dir_type == 1 else torch.int32
+    r = 1 if op == 2 else 2
+    for h in (3, 5, 9, 22):
+        img = synth.rect_image(h, w, 31 * h + w) % 9
+        src = torch.from_numpy(img).to(gpu)
+        for border in (0, 1, 2, 3):
+            ho, wo = (h - 2 * r, w - 2 * r) if border == 1 else (h, w)
+            if ho < 1 or wo < 1:
+                continue
+            for want_mag in (True, False):
+                base = [torch.full((ho, wo + 3), 77, dtype=dt, device=gpu) for _ in range(4 if op == 0 else 2)]
+                mag, _ = sobel_lib.sobel4x5_u8_op(src, op, border, want_mag=want_mag, dir_type=dir_type,
+                                                  dirs=[b[:, 1:wo + 1] for b in base])
+                if op == 0:
+                    om, od = oracle_mod.sobel_u8(img, border)
+                else:
+                    om, od = oracle_mod.sobel_u8_2dir(img, 5 if op == 1 else 3, border)
+                torch.cuda.synchronize()
+                got = np.stack([b.cpu().numpy() for b in base])
+                what = "op %d, border %d, %dx%d" % (op, border, h, w)
+                assert np.array_equal(got[:, :, 1:wo + 1], od), what
+                assert (got[:, :, 0] == 77).all() and (got[:, :, wo + 1:] == 77).all(), what
+                if want_mag:
+                    assert np.array_equal(mag.cpu().numpy(), om), what
