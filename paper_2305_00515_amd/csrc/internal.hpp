@@ -52,9 +52,9 @@ void u8_tile(U8Job &j, const U8Shape &s);
 // (replicate 0, valid 1, zero 2, reflect-101 3).
 hipError_t launch_u8_single(const U8Job &j, int border, const U8Shape &s, hipStream_t stream);
 
-// Magnitudes of four run-time kernels (HOST array of 4*25 int32, the layout
-// of sobel4x5_u8_weighted, already validated) on the matrix cores, when
-// every weight fits int8 (mfma_weights_fit).
+// Four run-time kernels (HOST array of 4*25 int32, the layout of
+// sobel4x5_u8_weighted, already validated) on the banded kernels, when every
+// weight fits int8 (mfma_weights_fit).
 bool mfma_weights_fit(const int32_t *weights);
 hipError_t launch_u8_mfma_weighted(const U8Job &j, int border, const int32_t *weights, int waves, hipStream_t stream);
 

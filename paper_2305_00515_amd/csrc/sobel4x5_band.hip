@@ -92,4 +92,40 @@ hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, 
     return launch_band<1, 2, false, kPlanes32>(j, taps, off, border, s.waves, st);
 }
 
+bool mfma_weights_fit(const int32_t *weights)
+{
+    for (int i = 0; i < 100; ++i)
+        if (weights[i] < -128 || weights[i] > 127) return false;
+    return true;
+}
+
+hipError_t launch_u8_mfma_weighted(const U8Job &j, int border, const int32_t *weights, int waves, hipStream_t st)
+{
+    struct Kernels {
+        const int32_t *w;
+        struct Kernel {
+            const int32_t *k;
+            const int32_t *operator[](int dy) const { return k + 5 * dy; }
+        };
+        Kernel operator[](int f) const { return {w + 25 * f}; }
+    };
+    const BandTaps taps = band_taps(Kernels{weights}, 4);
+    // |G| is at most 255 times half the sum of |weights|; without the clamp,
+    // four squares must stay below 2^31
+    int64_t most = 0;
+    for (int f = 0; f < 4; ++f) {
+        int64_t sum = 0;
+        for (int t = 0; t < 25; ++t) sum += weights[25 * f + t] < 0 ? -(int64_t)weights[25 * f + t] : weights[25 * f + t];
+        most = std::max(most, sum);
+    }
+    const bool clamp = most > 181;
+    const int off = border == 1 ? 2 : 0;
+    if (j.dir_type == 1) return launch_band<2, 4, false, kPlanes16>(j, taps, off, border, waves, st);   // sums <= 128
+    if (j.dir_type == 2)
+        return clamp ? launch_band<1, 4, true, kPlanes32>(j, taps, off, border, waves, st)
+                     : launch_band<1, 4, false, kPlanes32>(j, taps, off, border, waves, st);
+    return clamp ? launch_band<4, 4, true, 0>(j, taps, off, border, waves, st)
+                 : launch_band<4, 4, false, 0>(j, taps, off, border, waves, st);
+}
+
 }  // namespace s4x5

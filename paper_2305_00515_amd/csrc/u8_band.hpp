@@ -314,6 +314,8 @@ __device__ __forceinline__ u32 mag_byte(int S, int at, u32 w)
     return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_sqrtf((float)S), at, w);
 }
 
+// CLAMP, for run-time weights of large sums: a response beyond 256 saturates
+// the magnitude alone, and clamped responses keep the sum below 2^31.
 template <int NR, bool CLAMP>
 __device__ __forceinline__ int sum_squares(const int (&G)[NR])
 {

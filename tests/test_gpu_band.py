@@ -82,3 +82,35 @@ def test_planes(oracle_mod, sobel_lib, gpu, op, dir_type, w):
                 assert (got[:, :, 0] == 77).all() and (got[:, :, wo + 1:] == 77).all(), what
                 if want_mag:
                     assert np.array_equal(mag.cpu().numpy(), om), what
+
+
+def antisymmetric(rng, amp, nonzero):
+    """Four kernels of `nonzero` random pairs of weights up to amp."""
+    w = np.zeros((4, 5, 5), np.int64)
+    taps = [(i, j) for i in range(3) for j in range(5) if (i, j) < (2, 2)]
+    for k in range(4):
+        for t in rng.choice(12, nonzero, replace=False):
+            i, j = taps[t]
+            w[k, i, j] = rng.integers(-amp, amp + 1)
+            w[k, 4 - i, 4 - j] = -w[k, i, j]
+    return w.astype(np.int32)
+
+
+# sums of |weights| below and above 181 (squares with and without the clamp),
+# and up to 128 for int16 planes
+@pytest.mark.parametrize("amp,nonzero,dir_type", [(7, 12, 2), (127, 12, 2), (127, 1, 2), (5, 12, 1), (64, 1, 1)])
+def test_weighted_planes(oracle_mod, sobel_lib, gpu, amp, nonzero, dir_type):
+    rng = np.random.default_rng(amp + nonzero)
+    w = antisymmetric(rng, amp, nonzero)
+    for h, wd in [(3, 2), (9, 17), (33, 70), (21, 300)]:
+        img = synth.rect_image(h, wd, h + wd)
+        for im in (img, img % 3):
+            src = torch.from_numpy(im).to(gpu)
+            for border in (0, 1, 2, 3):
+                if border == 1 and min(h, wd) < 5:
+                    continue
+                mag, dirs = sobel_lib.sobel4x5_u8_weighted(src, w, border, dir_type=dir_type)
+                om, od = oracle_mod.sobel_u8(im, border, weights=w)
+                torch.cuda.synchronize()
+                assert np.array_equal(mag.cpu().numpy(), om), (h, wd, border)
+                assert np.array_equal(np.stack([d.cpu().numpy() for d in dirs]), od), (h, wd, border)
