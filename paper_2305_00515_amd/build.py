@@ -18,7 +18,7 @@ CSRC = PKG / "csrc"
 LIB = PKG / "libsobel4x5.so"
 ARCH = os.environ.get("SOBEL4X5_ARCH", "gfx950")
 
-SOURCES = ["sobel4x5_api.cpp", "sobel4x5_u8.hip", "sobel4x5_batched.hip", "sobel4x5_f32.hip",
+SOURCES = ["sobel4x5_api.cpp", "sobel4x5_u8.hip", "sobel4x5_f32.hip",
            "sobel4x5_weighted.hip", "sobel4x5_band.hip"]
 
 FLAGS = [

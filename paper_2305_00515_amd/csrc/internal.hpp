@@ -23,29 +23,52 @@ struct U8Job {
     int32_t W, H;          // input size
     int32_t Wo, Ho;        // output size
     int32_t dir_type;      // 0 none, 1 int16, 2 int32
-    int32_t ntx;           // tile columns (tile width = 16 lanes * px_per_lane)
-    int32_t nty4;          // ceil(tile rows / 4): a wave takes 4 stacked tiles
-    int32_t nty;           // tile rows
-    int32_t nwt;           // wave tiles, 4 tiles stacked per wave = ntx * nty4
-    int32_t nwt_h;         // wave tiles, 4 tiles side by side = ceil(ntx / 4) * nty
+    uint32_t nt;           // tile columns (u8_tile)
+    uint32_t inv_nt;       // floor(2^32 / nt), at most 2^32 - 1
 };
 
-// Tile shape.  A 16-lane group owns a tile of (16 * ppl) columns x th rows;
-// a wave owns 4 vertically stacked tiles.
+// Shape of a launch.
 struct U8Shape {
-    int ppl;        // pixels per lane: 8 or 16
-    int th;         // rows per tile (batched kernel)
+    int ppl;        // batched: pixels per lane (16, or 8 with directional planes)
+    int th;         // batched: rows of a wave's tiles, a multiple of 4
     int wpg;        // waves per workgroup (4)
     int waves = 0;  // single image: waves to launch (0 = by size); batched: kStaticGrid or a persistent grid
-    int tallx = 0;      // batched kernel: tall chunks of tallx tile heights (0: batched_split())
 };
 
-// True when the fast (vector-load) kernel may read this image: 16-byte
-// aligned base and pitch.
-bool u8_rows_aligned(const U8Job &j);
-
-// Fills the tiling fields of `j` for shape `s`.
+// Fills the tile columns of `j` for tiles of s.ppl pixels.  Rows of tiles
+// start at multiples of 8 tiles (128 bytes of magnitudes) where that adds at
+// most a sixteenth of the tiles, so that a wave's bytes of a row are whole
+// lines.
 void u8_tile(U8Job &j, const U8Shape &s);
+
+// Whether a launch's outputs are stored past the L2 (nontemporal).  Measured on
+// one image, stores past the L2 against stores through it:
+// - rows of whole 64-byte pieces: past it (8192^2 magnitudes 25.1 against
+//   31.0 us, 16384^2 103 against 113; 4096^2 int16 planes 24.6 against 40.5);
+// - other rows, whose ends share lines with a neighbouring wave: planes
+//   through it (4096 x 4104 int16 51.0 against 39.7 us), magnitudes past it
+//   up to 128 MiB of outputs, half of what the Infinity Cache holds to put
+//   the pieces together (8193 x 8192 29.3 against 35.6 us; 11001 x 11000 49.6
+//   against 59.0; 12001 x 12000 74.5 against 70.9; 15001 x 15000 121 against
+//   104).
+struct OutputStores {
+    bool planes = false, whole = true;
+    int64_t bytes = 0;
+    void add(const U8Job &j)
+    {
+        uint64_t low = 0;
+        if (j.mag) low |= reinterpret_cast<uintptr_t>(j.mag) | (uint64_t)j.mag_pitch;
+        if (j.dir_type) {
+            planes = true;
+            low |= (uint64_t)j.dir_pitch;
+            for (const void *d : j.dir) low |= reinterpret_cast<uintptr_t>(d);
+        }
+        whole = whole && (low & 63) == 0;
+        bytes += (int64_t)j.Wo * j.Ho;
+    }
+    bool large() const { return bytes > ((int64_t)128 << 20); }
+    bool past_l2() const { return whole || (!planes && !large()); }
+};
 
 // Single image: one launch of the banded matrix-core kernels (u8_band.hpp),
 // magnitude and/or planes.  `border` is the public SOBEL4X5_BORDER_* code
@@ -63,51 +86,44 @@ hipError_t launch_u8_mfma_weighted(const U8Job &j, int border, const int32_t *we
 // input (1, 1)).  The job's Wo, Ho are those of the operator's own border rule.
 hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, hipStream_t stream);
 
-// Batched persistent launch (`aligned`: every image may take the vector
-// path: 16-byte aligned src rows, and at least 3 columns under reflect-101).
-// `jobs` (device) holds the images; `tiles` (device, `total` entries) lists
-// every wave-tile of the batch as {image, kind | rows << 1, tx, y0}
-// (batched_tiles); `queue` (device, 2 words, zero before the first launch)
-// is the work counter and the exit counter, reset by the last wave to
-// finish.  `border`: the public code; `dir`: some job asks for directional
-// planes.  `claims` (device, `total` counters, or null): each tile's counter
-// gains one for every wave that takes the tile.
+// Batched launch.  `jobs` (device) holds the images; `tiles` (device, `total`
+// entries) lists every wave-tile of the batch (batched_tiles); `queue`
+// (device, 2 words, zero before the first launch) is the work counter and
+// the exit counter of a persistent grid, reset by the last wave to finish,
+// or null for one wave per wave-tile.  `border`: the public code; `dir`: some
+// job asks for directional planes.  `claims` (device, `total` counters, or
+// null): each wave-tile's counter gains one for every wave that takes it.
+// `past`: outputs are stored past the L2 (OutputStores).
 hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border,
-                             bool aligned, bool dir, const U8Shape &s, int grid, hipStream_t stream,
+                             bool past, bool dir, const U8Shape &s, int grid, hipStream_t stream,
                              uint32_t *claims = nullptr);
 
-// Wave-tiles of image `img` (tiled by u8_tile with th rows per tile): the
-// complete four-tile strips side by side (kind 0) in tall row chunks
-// (passed to `first`) and short ones (passed to `last`, queued after every
-// tall chunk of the batch), then the remaining tile columns with four row
-// blocks stacked (kind 1, passed to `first`).
-struct BatchSplit {
-    int tallx;    // tall chunks: tallx tile heights
-    int shortq;   // the last 1/shortq of the rows in chunks of one tile height
-};
-BatchSplit batched_split();
-
-template <class First, class Last>
-void batched_tiles_each(const U8Job &j, int32_t img, int th, int tallx, First &&first, Last &&last)
+// Wave-tiles of image `img` (tiled by u8_tile): 16 consecutive tiles of its
+// tile grid each, in bands of `th` rows, as {image, first tile, steps of four
+// rows, tiles of the image}.
+inline int64_t batched_bands(const U8Job &j, int th) { return ((int64_t)j.Ho + th - 1) / th; }
+inline int64_t batched_count(const U8Job &j, int th) { return (j.nt * batched_bands(j, th) + 15) / 16; }
+template <class Push>
+void batched_tiles_each(const U8Job &j, int32_t img, int th, Push &&push)
 {
-    const BatchSplit sp = batched_split();
-    const int strips = j.ntx / 4, tall = (tallx > 0 ? tallx : sp.tallx) * th;
-    const int htall = (j.Ho - j.Ho / sp.shortq) / tall * tall;
-    for (int y = 0; y < htall; y += tall)
-        for (int s = 0; s < strips; ++s) first(make_int4(img, tall << 1, 4 * s, y));
-    for (int y = htall; y < j.Ho; y += th)
-        for (int s = 0; s < strips; ++s) last(make_int4(img, th << 1, 4 * s, y));
-    for (int tx = 4 * strips; tx < j.ntx; ++tx)
-        for (int y = 0; y < j.Ho; y += 4 * th) first(make_int4(img, 1, tx, y));
+    const int64_t tiles = j.nt * batched_bands(j, th);
+    for (int64_t t = 0; t < tiles; t += 16) push(make_int4(img, (int)t, th / 4, (int)tiles));
 }
 
-// The same into two vectors.
-void batched_tiles(const U8Job &j, int32_t img, int th, int tallx, std::vector<int4> &first,
-                   std::vector<int4> &last);
-
-// Reorders tiles [b, e) of a static-grid table so that each XCD's
-// workgroups take a contiguous stretch of it (sobel4x5_batched.hip).
-void xcd_order(std::vector<int4> &v, size_t b, size_t e);
+// The unit in which the allocation-free call's public limit is counted: per
+// image, strips of 512 columns in chunks of `tallx` * 32 rows, the last
+// 1 / `shortq` of the rows in chunks of 32; the 128-column tiles that no whole
+// strip holds in chunks of 128 rows.
+struct BatchSplit {
+    int tallx;
+    int shortq;
+};
+inline int64_t budget_tiles(int32_t Wo, int32_t Ho, const BatchSplit &sp = BatchSplit{2, 4})
+{
+    const int64_t ntx = ((int64_t)Wo + 127) / 128, strips = ntx / 4, tall = 32 * sp.tallx;
+    const int64_t rows = (Ho - Ho / sp.shortq) / tall * tall;
+    return strips * (rows / tall + (Ho - rows + 31) / 32) + (ntx - 4 * strips) * (((int64_t)Ho + 127) / 128);
+}
 
 // Allocation-free batched call (sobel4x5_batched_noalloc): the queue
 // words, the job table and the tile table of one batch live in a fixed
@@ -115,9 +131,12 @@ void xcd_order(std::vector<int4> &v, size_t b, size_t e);
 // are the public SOBEL4X5_NOALLOC_MAX_*.
 constexpr int32_t kNoallocMaxImages = 1024;
 constexpr int32_t kNoallocMaxTiles = 65536;
+// entries of the tile table: a wave-tile is half as wide as the budget's
+// strip, and rows of tiles are rounded up by at most a sixteenth
+constexpr int32_t kNoallocTable = 2 * kNoallocMaxTiles + kNoallocMaxTiles / 4 + kNoallocMaxImages;
 constexpr size_t kNoallocJobsOff = 256;   // bytes [0, 8): queue[0], queue[1]
 constexpr size_t kNoallocTilesOff = (kNoallocJobsOff + sizeof(U8Job) * kNoallocMaxImages + 255) / 256 * 256;
-constexpr size_t kNoallocBytes = kNoallocTilesOff + sizeof(int4) * kNoallocMaxTiles;
+constexpr size_t kNoallocBytes = kNoallocTilesOff + sizeof(int4) * kNoallocTable;
 
 // Device address of this device's buffer (looked up once per device, with
 // that device current).
@@ -125,7 +144,7 @@ hipError_t noalloc_scratch(void **out);
 
 // Number of workgroups of the persistent kernel that fit on the device at
 // once for shape `s` (occupancy x CUs), or 0 on error.
-int u8_persistent_grid(const U8Shape &s, int border, bool aligned, bool dir);
+int u8_persistent_grid(const U8Shape &s, int border, bool past, bool dir);
 
 // uint8 operator with run-time weights (four integer kernels that are
 // antisymmetric under a half turn), as coefficients of the 12 upper-half

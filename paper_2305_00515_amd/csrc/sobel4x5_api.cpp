@@ -283,12 +283,13 @@ struct sobel4x5_plan_s {
     U8Shape shape{};
     int grid = 0;
     bool use_graph = true;
-    bool aligned = true;
     std::vector<sobel4x5_image> imgs;
     std::vector<sobel4x5_outputs> outs;   // per image: mag and/or directional planes
     bool dir = false;                     // some image asks for directional planes
+    OutputStores stores;
+    unsigned char *d_base = nullptr;   // the tables' device memory
     U8Job *d_jobs = nullptr;
-    int4 *d_tiles = nullptr;      // {image, kind | rows << 1, tx, y0} per queue ticket
+    int4 *d_tiles = nullptr;      // wave-tiles, one per queue ticket (batched_tiles_each)
     int32_t total = 0;            // wave-tiles of the batch
     uint32_t *d_queue = nullptr;
     hipGraph_t graph = nullptr;
@@ -301,68 +302,61 @@ void plan_free_device(sobel4x5_plan_s *p)
 {
     if (p->exec) hipGraphExecDestroy(p->exec);
     if (p->graph) hipGraphDestroy(p->graph);
-    if (p->d_jobs) hipFree(p->d_jobs);
-    if (p->d_tiles) hipFree(p->d_tiles);
-    if (p->d_queue) hipFree(p->d_queue);
+    if (p->d_base) hipFree(p->d_base);
     p->exec = nullptr;
     p->graph = nullptr;
-    p->d_jobs = nullptr;
-    p->d_tiles = nullptr;
-    p->d_queue = nullptr;
+    p->d_base = nullptr;
 }
 
-// Build device tables for `shape` (no graph).
+U8Job plan_job(const sobel4x5_plan_s *p, int32_t i)
+{
+    const sobel4x5_image &m = p->imgs[i];
+    const sobel4x5_outputs &o = p->outs[i];
+    int32_t Wo, Ho;
+    out_dims(m.width, m.height, p->border, &Wo, &Ho);
+    return make_job(m.src, m.width, m.height, m.src_pitch, Wo, Ho, o.mag, o.mag_pitch, o.dir_type ? o.dir : nullptr,
+                    o.dir_pitch, o.dir_type);
+}
+
+// Build device tables for `shape` (no graph): the queue words, the jobs and
+// the wave-tiles in one allocation, uploaded by one copy.
 int plan_setup(sobel4x5_plan_s *p, const U8Shape &shape)
 {
     plan_free_device(p);
     p->shape = shape;
     std::vector<U8Job> jobs(p->count);
-    bool aligned = true;
+    int64_t total = 0, most = 0;
     for (int32_t i = 0; i < p->count; ++i) {
-        const sobel4x5_image &m = p->imgs[i];
-        const sobel4x5_outputs &o = p->outs[i];
-        int32_t Wo, Ho;
-        out_dims(m.width, m.height, p->border, &Wo, &Ho);
-        jobs[i] = make_job(m.src, m.width, m.height, m.src_pitch, Wo, Ho, o.mag, o.mag_pitch,
-                           o.dir_type ? o.dir : nullptr, o.dir_pitch, o.dir_type);
+        jobs[i] = plan_job(p, i);
         u8_tile(jobs[i], shape);
-        // reflect-101 on an image narrower than 3 columns needs the byte path
-        aligned = aligned && u8_rows_aligned(jobs[i]) &&
-                  !(p->border == SOBEL4X5_BORDER_REFLECT101 && m.width < 3);
+        total += batched_count(jobs[i], shape.th);
+        most = std::max(most, jobs[i].nt * batched_bands(jobs[i], shape.th));
     }
-    p->aligned = aligned;
-    std::vector<int4> tiles, tail;
-    for (int32_t i = 0; i < p->count; ++i) {
-        batched_tiles(jobs[i], i, shape.th, shape.tallx, tiles, tail);
-        if (tiles.size() + tail.size() > (size_t)INT32_MAX) return fail(SOBEL4X5_EINVAL, "batch too large for one plan");
-    }
-    const size_t nfirst = tiles.size();
-    tiles.insert(tiles.end(), tail.begin(), tail.end());
-    if (shape.waves == kStaticGrid) {   // each part from a workgroup boundary (4 tiles)
-        xcd_order(tiles, 0, nfirst);
-        xcd_order(tiles, std::min(tiles.size(), (nfirst + 3) / 4 * 4), tiles.size());
-    }
-    p->total = (int32_t)tiles.size();
+    if (total > INT32_MAX || most > INT32_MAX) return fail(SOBEL4X5_EINVAL, "batch too large for one plan");
+    p->total = (int32_t)total;
+    const size_t tiles_off = kNoallocJobsOff + (sizeof(U8Job) * p->count + 255) / 256 * 256;
+    std::vector<unsigned char> host(tiles_off + sizeof(int4) * (size_t)total);
+    std::memcpy(host.data() + kNoallocJobsOff, jobs.data(), sizeof(U8Job) * p->count);
+    int4 *t = reinterpret_cast<int4 *>(host.data() + tiles_off);
+    for (int32_t i = 0; i < p->count; ++i) batched_tiles_each(jobs[i], i, shape.th, [&](int4 e) { *t++ = e; });
     hipError_t e;
-    if ((e = hipMalloc(&p->d_jobs, sizeof(U8Job) * p->count)) != hipSuccess ||
-        (e = hipMalloc(&p->d_tiles, sizeof(int4) * std::max<size_t>(1, tiles.size()))) != hipSuccess ||
-        (e = hipMalloc(&p->d_queue, 2 * sizeof(uint32_t))) != hipSuccess) {
-        plan_free_device(p);
+    if ((e = hipMalloc(&p->d_base, host.size())) != hipSuccess) {
+        p->d_base = nullptr;
         return fail(SOBEL4X5_ENOMEM, "hipMalloc for plan tables: %s", hipGetErrorString(e));
     }
-    if ((e = hipMemcpy(p->d_jobs, jobs.data(), sizeof(U8Job) * p->count, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(p->d_tiles, tiles.data(), sizeof(int4) * tiles.size(), hipMemcpyHostToDevice)) !=
-            hipSuccess ||
-        (e = hipMemset(p->d_queue, 0, 2 * sizeof(uint32_t))) != hipSuccess) {
+    if ((e = hipMemcpy(p->d_base, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess) {
         plan_free_device(p);
         return hip_fail(e, "uploading plan tables");
     }
+    p->d_queue = reinterpret_cast<uint32_t *>(p->d_base);
+    p->d_jobs = reinterpret_cast<U8Job *>(p->d_base + kNoallocJobsOff);
+    p->d_tiles = reinterpret_cast<int4 *>(p->d_base + tiles_off);
     const int need = (p->total + 3) / 4;   // never more workgroups than work (4 waves each)
-    if (shape.waves == kStaticGrid) {       // one wave per tile, no queue
+    if (shape.waves == kStaticGrid) {       // one wave per wave-tile, no queue
         p->grid = std::max(1, need);
         return ok();
     }
-    p->grid = u8_persistent_grid(shape, p->border, p->aligned, p->dir);
+    p->grid = u8_persistent_grid(shape, p->border, p->stores.past_l2(), p->dir);
     if (p->grid <= 0) {
         plan_free_device(p);
         return fail(SOBEL4X5_EHIP, "could not query occupancy");
@@ -374,7 +368,7 @@ int plan_setup(sobel4x5_plan_s *p, const U8Shape &shape)
 int plan_direct_launch(sobel4x5_plan_s *p, hipStream_t st, uint32_t *claims = nullptr)
 {
     uint32_t *queue = p->shape.waves == kStaticGrid ? nullptr : p->d_queue;
-    hipError_t e = launch_u8_batched(p->d_jobs, p->d_tiles, p->total, queue, p->border, p->aligned, p->dir,
+    hipError_t e = launch_u8_batched(p->d_jobs, p->d_tiles, p->total, queue, p->border, p->stores.past_l2(), p->dir,
                                      p->shape, p->grid, st, claims);
     return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
 }
@@ -530,19 +524,17 @@ bool tune_lookup(const std::string &key, U8Shape &s)
 {
     FILE *f = std::fopen(tune_cache_path().c_str(), "r");
     if (!f) return false;
-    // one entry a line: key ppl th wpg [static [tallx]]; a line without
-    // the static field is a persistent grid, one without tallx takes the
-    // default split
+    // one entry a line: key ppl th wpg [static]; a line without the static
+    // field is a persistent grid
     char line[1024], k[512];
     bool found = false;
     while (std::fgets(line, sizeof line, f)) {
-        int ppl = 0, th = 0, wpg = 0, st = 0, tx = 0;
-        const int n = std::sscanf(line, "%511s %d %d %d %d %d", k, &ppl, &th, &wpg, &st, &tx);
-        if (n >= 4 && key == k && (ppl == 8 || ppl == 16) && th >= 4 && th <= 256 && wpg == 4 &&
-            (st == 0 || st == 1) && tx >= 0 && tx <= 64) {
+        int ppl = 0, th = 0, wpg = 0, st = 0;
+        const int n = std::sscanf(line, "%511s %d %d %d %d", k, &ppl, &th, &wpg, &st);
+        if (n >= 4 && key == k && ppl == s.ppl && th >= 4 && th <= 256 && th % 4 == 0 && wpg == 4 &&
+            (st == 0 || st == 1)) {
             s = U8Shape{ppl, th, wpg};
             if (n >= 5 && st == 1) s.waves = kStaticGrid;
-            if (n == 6) s.tallx = tx;
             found = true;   // last entry wins
         }
     }
@@ -557,35 +549,27 @@ void tune_store(const std::string &key, const U8Shape &s)
     if (slash != std::string::npos && slash > 0) mkdir(path.substr(0, slash).c_str(), 0755);   // best effort
     FILE *f = std::fopen(path.c_str(), "a");
     if (!f) return;
-    std::fprintf(f, "%s %d %d %d %d %d\n", key.c_str(), s.ppl, s.th, s.wpg, s.waves == kStaticGrid ? 1 : 0, s.tallx);
+    std::fprintf(f, "%s %d %d %d %d\n", key.c_str(), s.ppl, s.th, s.wpg, s.waves == kStaticGrid ? 1 : 0);
     std::fclose(f);
 }
 
-// Shape of a batched plan without autotuning.
-// - Magnitudes only: 8 pixels per lane (the binomial kernel runs three
-//   waves per SIMD there; at 16 it needs more registers than two waves per
-//   SIMD have), 32-row tiles and the static grid: on 256 mixed images 0.848
-//   against 0.970 ms for the persistent grid, whose per-tile ticket, table
-//   and job loads run in series before each tile's first row.
-// - With directional planes, which are bound by their stores: 8 pixels per
-//   lane (the plane stores keep more values live), 4-row tiles and the
-//   static grid, one wave per tile, so that many short-lived waves keep the
-//   stores in flight: 352 Gpx/s against 299 for the persistent grid with
-//   8-row tiles.
-// SOBEL4X5_BATCH_PPL (8 or 16), SOBEL4X5_BATCH_TH (4..256) and
-// SOBEL4X5_BATCH_STATIC (0 or 1) override it.
-U8Shape batch_default_shape(const std::vector<sobel4x5_image> &imgs, bool dir)
+// Shape of a batch without autotuning: the static grid (a persistent grid
+// loads ticket, table entry and job in series before each wave-tile's first
+// row), and bands of
+// - 16 rows for magnitudes, 32 in a large batch (256 images of 128..4096, 1182
+//   Mpx: 527 us at 32 rows, 560 at 16; 64 of 2048^2: 117 and 126; but 12 of
+//   2101^2: 36.2 and 34.6, 40 of 64..1080: 18.1 and 16.6);
+// - 4 rows with directional planes, which are bound by their stores, or 8
+//   where rows share lines (32 images of 128..4096 with int16 planes: 312 us
+//   at 8 rows, 361 at 4 and at 16).
+// SOBEL4X5_BATCH_TH (4..256) and SOBEL4X5_BATCH_STATIC (0 or 1) override it.
+U8Shape batch_default_shape(const OutputStores &o)
 {
-    (void)imgs;
-    U8Shape s{8, dir ? 4 : 32, 4};
+    U8Shape s{o.planes ? 8 : 16, o.planes ? (o.whole ? 4 : 8) : o.large() ? 32 : 16, 4};
     s.waves = kStaticGrid;
-    const int ppl = env_int("SOBEL4X5_BATCH_PPL", 0);
-    if (ppl == 8 || ppl == 16) s.ppl = ppl;
     const int th = env_int("SOBEL4X5_BATCH_TH", 0);
-    if (th >= 4 && th <= 256) s.th = th;
-    const int st = env_int("SOBEL4X5_BATCH_STATIC", -1);
-    if (st == 0) s.waves = 0;
-    if (st == 1) s.waves = kStaticGrid;
+    if (th >= 4 && th <= 256) s.th = th / 4 * 4;
+    if (env_int("SOBEL4X5_BATCH_STATIC", -1) == 0) s.waves = 0;
     return s;
 }
 
@@ -617,7 +601,7 @@ int plan_autotune(sobel4x5_plan_s *p)
     const std::string key = tune_key(p);
 
     // reference bytes with the default shape
-    const U8Shape ref = batch_default_shape(p->imgs, p->dir);
+    const U8Shape ref = batch_default_shape(p->stores);
     if (int rc = plan_setup(p, ref)) return rc;
     if (int rc = plan_direct_launch(p, nullptr)) return rc;
     if (hipError_t e = hipDeviceSynchronize(); e != hipSuccess) return hip_fail(e, "autotune reference run");
@@ -626,7 +610,7 @@ int plan_autotune(sobel4x5_plan_s *p)
 
     // a cached shape is used only after it has reproduced the reference
     // bytes once on these images
-    U8Shape cached;
+    U8Shape cached = ref;
     if (tune_lookup(key, cached)) {
         int rc;
         if (candidate_matches(p, cached, want, &rc)) return ok();
@@ -636,41 +620,23 @@ int plan_autotune(sobel4x5_plan_s *p)
 
     U8Shape best = ref;
     double best_ms = time_plan(p, 10);
-    const int ppls[] = {8, 16};
     const int ths[] = {8, 16, 32, 64, 128};
     for (int grid_form = 0; grid_form < 2; ++grid_form)   // persistent, static
-        for (int ppl : ppls)
-            for (int th : ths) {
-                U8Shape c{ppl, th, 4};
-                if (grid_form == 1) c.waves = kStaticGrid;
-                if (c.ppl == ref.ppl && c.th == ref.th && c.waves == ref.waves) continue;
-                int rc;
-                if (!candidate_matches(p, c, want, &rc)) {
-                    if (rc != SOBEL4X5_OK) return rc;
-                    continue;
-                }
-                const double ms = time_plan(p, 10);
-                if (ms > 0 && ms < best_ms) {
-                    best_ms = ms;
-                    best = c;
-                }
+        for (int th : ths) {
+            U8Shape c{ref.ppl, th, 4};
+            if (grid_form == 1) c.waves = kStaticGrid;
+            if (c.th == ref.th && c.waves == ref.waves) continue;
+            int rc;
+            if (!candidate_matches(p, c, want, &rc)) {
+                if (rc != SOBEL4X5_OK) return rc;
+                continue;
             }
-    // then the height of the tall chunks around the best shape (the default
-    // split takes 2 tile heights)
-    for (int tx : {1, 4}) {
-        U8Shape c = best;
-        c.tallx = tx;
-        int rc;
-        if (!candidate_matches(p, c, want, &rc)) {
-            if (rc != SOBEL4X5_OK) return rc;
-            continue;
+            const double ms = time_plan(p, 10);
+            if (ms > 0 && ms < best_ms) {
+                best_ms = ms;
+                best = c;
+            }
         }
-        const double ms = time_plan(p, 10);
-        if (ms > 0 && ms < best_ms) {
-            best_ms = ms;
-            best = c;
-        }
-    }
     tune_store(key, best);
     return plan_setup(p, best);
 }
@@ -884,9 +850,10 @@ int sobel4x5_plan_create_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *
     for (int32_t i = 0; i < count; ++i) {
         p->outs[i] = batch_outputs(imgs, outs, i);
         p->dir = p->dir || p->outs[i].dir_type != SOBEL4X5_DIR_NONE;
+        p->stores.add(plan_job(p, i));
     }
     hipGetDevice(&p->device);
-    int rc = (flags & SOBEL4X5_PLAN_AUTOTUNE) ? plan_autotune(p) : plan_setup(p, batch_default_shape(p->imgs, p->dir));
+    int rc = (flags & SOBEL4X5_PLAN_AUTOTUNE) ? plan_autotune(p) : plan_setup(p, batch_default_shape(p->stores));
     if (rc == SOBEL4X5_OK && p->use_graph) rc = plan_capture(p);
     if (rc != SOBEL4X5_OK) {
         plan_free_device(p);
@@ -1004,37 +971,39 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     // has read its source when hipMemcpyAsync returns.
     static std::mutex mu;
     static unsigned char stage[kNoallocBytes];     // queue words, jobs, tiles: the device layout
-    static int4 tail[kNoallocMaxTiles];            // short chunks, queued after every other tile
     std::lock_guard<std::mutex> lk(mu);
-    const std::vector<sobel4x5_image> none;
-    const U8Shape shape = batch_default_shape(none, false);
     std::memset(stage, 0, kNoallocJobsOff);   // queue words start at zero
-    int4 *first = reinterpret_cast<int4 *>(stage + kNoallocTilesOff);
-    int32_t nfirst = 0, ntail = 0;
-    bool over = false;
-    bool aligned = true;
-    for (int32_t i = 0; i < count && !over; ++i) {
+    U8Job *jobs = reinterpret_cast<U8Job *>(stage + kNoallocJobsOff);
+    int64_t budget = 0;
+    OutputStores stores;
+    for (int32_t i = 0; i < count; ++i) {
         const sobel4x5_image &m = imgs[i];
         int32_t Wo, Ho;
         out_dims(m.width, m.height, border, &Wo, &Ho);
-        U8Job j = make_job(m.src, m.width, m.height, m.src_pitch, Wo, Ho, m.mag, m.mag_pitch, nullptr, 0, 0);
-        u8_tile(j, shape);
-        aligned = aligned && u8_rows_aligned(j) && !(border == SOBEL4X5_BORDER_REFLECT101 && m.width < 3);
-        std::memcpy(stage + kNoallocJobsOff + sizeof(U8Job) * i, &j, sizeof(U8Job));
-        batched_tiles_each(
-            j, i, shape.th, shape.tallx,
-            [&](int4 t) {
-                if (nfirst + ntail < kNoallocMaxTiles) first[nfirst++] = t; else over = true;
-            },
-            [&](int4 t) {
-                if (nfirst + ntail < kNoallocMaxTiles) tail[ntail++] = t; else over = true;
-            });
+        jobs[i] = make_job(m.src, m.width, m.height, m.src_pitch, Wo, Ho, m.mag, m.mag_pitch, nullptr, 0, 0);
+        stores.add(jobs[i]);
+        budget += budget_tiles(Wo, Ho);
     }
-    if (over)
+    U8Shape shape = batch_default_shape(stores);
+    for (int32_t i = 0; i < count; ++i) u8_tile(jobs[i], shape);
+    if (budget > kNoallocMaxTiles)
         return fail(SOBEL4X5_EINVAL, "the batch needs more than %d wave-tiles, the allocation-free call's limit",
                     kNoallocMaxTiles);
-    const int32_t total = nfirst + ntail;
-    std::memcpy(first + nfirst, tail, sizeof(int4) * ntail);
+    // bands high enough for the table: a batch within the budget fits with
+    // one band an image at the latest
+    int64_t total = 0;
+    for (;; shape.th *= 2) {
+        total = 0;
+        int32_t rows = 0;
+        for (int32_t i = 0; i < count; ++i) {
+            total += batched_count(jobs[i], shape.th);
+            rows = std::max(rows, jobs[i].Ho);
+        }
+        if (total <= kNoallocTable) break;
+        if (shape.th >= rows) return fail(SOBEL4X5_EINVAL, "the batch does not fit the allocation-free call's table");
+    }
+    int4 *t = reinterpret_cast<int4 *>(stage + kNoallocTilesOff);
+    for (int32_t i = 0; i < count; ++i) batched_tiles_each(jobs[i], i, shape.th, [&](int4 e) { *t++ = e; });
     void *scr = nullptr;
     hipError_t e = guard(noalloc_scratch(&scr));
     if (e != hipSuccess) return hip_fail(e, "looking up the fixed device buffer");
@@ -1048,18 +1017,18 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
         return hip_fail(e, "copying the batch tables");
     // the default shape's grid form: one wave per tile, or a persistent grid
     // on the queue words
-    const int need = (total + 3) / 4;
+    const int need = (int)((total + 3) / 4);
     int grid = std::max(1, need);
     uint32_t *queue = nullptr;
     if (shape.waves != kStaticGrid) {
-        grid = u8_persistent_grid(shape, border, aligned, false);
+        grid = u8_persistent_grid(shape, border, stores.past_l2(), false);
         if (grid <= 0) return fail(SOBEL4X5_EHIP, "could not query occupancy");
         grid = std::max(1, std::min(grid, need));
         queue = reinterpret_cast<uint32_t *>(base);
     }
     e = guard(launch_u8_batched(reinterpret_cast<const U8Job *>(base + kNoallocJobsOff),
-                                reinterpret_cast<const int4 *>(base + kNoallocTilesOff), total, queue, border,
-                                aligned, false, shape, grid, st));
+                                reinterpret_cast<const int4 *>(base + kNoallocTilesOff), (int32_t)total, queue,
+                                border, stores.past_l2(), false, shape, grid, st));
     return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
 }
 

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <mutex>
 
 namespace s4x5 {
 namespace {
@@ -22,64 +23,78 @@ int64_t band_slots()
     return (int64_t)n * kBandResident;
 }
 
-// The tile grid of one image.
-// - Rows of tiles start at multiples of 8 tiles (128 bytes of magnitudes)
-//   where that adds at most a sixteenth of the tiles, so that a wave's 256
-//   bytes of a row are whole lines.
-// - Bands: the fewest steps with which all waves are resident at once, as a
-//   wave that waits for a slot starts with a trip to memory (4096^2 at 4
-//   steps 10.7 us, at 2 12.1; 3840x2160 at 2 steps 6.9 us, at 1 8.5).  Above
-//   one step an even number (the steps come in pairs: 4001x2999 9.1 us at 4
-//   steps, 10.0 at 3).  At most 8 steps: larger images run several rounds,
-//   which hide each other's first loads and end more evenly (16384^2: 103.6
-//   us at 8 steps, 114.8 at 64; 8192^2: 25.8 at 8 and 25.7 at 16).
+// Bands of an image of nt tile columns and nq quads of rows.
+// - The fewest steps with which all waves are resident at once, as a wave that
+//   waits for a slot starts with a trip to memory (4096^2 at 4 steps 10.7 us,
+//   at 2 12.1; 3840x2160 at 2 steps 6.9 us, at 1 8.5).  Above one step an
+//   even number (the steps come in pairs: 4001x2999 9.1 us at 4 steps, 10.0
+//   at 3).  At most 8 steps: larger images run several rounds, which hide
+//   each other's first loads and end more evenly (16384^2: 103.6 us at 8
+//   steps, 114.8 at 64; 8192^2: 25.8 at 8 and 25.7 at 16).
 // - With planes one step: the stores bound it, and many short waves store in
 //   the order of memory (4096^2 with int16 planes 24.6 us at 1 step, 27.8 at
 //   2, 31.5 at 8; int32 52.5, 53.3, 55.0).
-template <int NB>
-BandGrid band_grid(const U8Job &j, int off, int border, int64_t slots, bool planes)
+int band_steps(int64_t nt, int64_t nq, int64_t slots, bool planes)
 {
-    int64_t nt = (j.Wo + 4 * NB - 1) / (4 * NB);
-    const int64_t nq = (j.Ho + 3) / 4, whole = (nt + 7) / 8 * 8;
-    if ((whole - nt) * 16 <= nt) nt = whole;
     const int64_t bands = std::max<int64_t>(1, slots * 16 / nt);
-    int64_t bq = (nq + bands - 1) / bands;
-    if (planes)
-        bq = 1;
-    else if (bq > 1)
-        bq = std::min<int64_t>((bq + 1) / 2 * 2, 8);
+    int64_t bq = planes ? 1 : (nq + bands - 1) / bands;
+    if (bq > 1) bq = std::min<int64_t>((bq + 1) / 2 * 2, 8);
     while (nt * ((nq + bq - 1) / bq) > INT32_MAX) bq *= 2;   // tiles are numbered in 32 bits
-    BandGrid g;
-    g.nt = (u32)nt;
-    g.inv_nt = (u32)std::min<uint64_t>((1ull << 32) / (uint64_t)nt, 0xffffffffull);
-    g.tiles = (u32)(nt * ((nq + bq - 1) / bq));
-    g.bq = (int)bq;
-    g.off = off;
-    g.bm = border == 2 ? kBandZero : border == 3 ? kBandRefl : kBandRep;
-    return g;
+    return (int)bq;
 }
 
-template <int NB, int NR, bool CLAMP, int DIR>
+const void *batched_fn(bool dir, bool past)
+{
+    if (dir)
+        return past ? reinterpret_cast<const void *>(&k_band_batched<2, kPlanesAny, true>)
+                    : reinterpret_cast<const void *>(&k_band_batched<2, kPlanesAny, false>);
+    return past ? reinterpret_cast<const void *>(&k_band_batched<4, 0, true>)
+                : reinterpret_cast<const void *>(&k_band_batched<4, 0, false>);
+}
+
+int border_mode(int border) { return border == 2 ? kBandZero : border == 3 ? kBandRefl : kBandRep; }
+
+template <int NB, int NR, bool CLAMP, int DIR, bool PAST>
 hipError_t launch_band(const U8Job &j, const BandTaps &taps, int off, int border, int waves, hipStream_t st)
 {
     if (j.Wo <= 0 || j.Ho <= 0) return hipSuccess;
-    const BandGrid g = band_grid<NB>(j, off, border, waves > 0 ? waves : band_slots(), DIR != 0);
+    U8Job job = j;
+    u8_tile(job, U8Shape{4 * NB, 0, kBandWaves});
+    const int64_t nq = ((int64_t)j.Ho + 3) / 4;
+    const int bq = band_steps(job.nt, nq, waves > 0 ? waves : band_slots(), DIR != 0);
+    const BandGrid g{(u32)(job.nt * ((nq + bq - 1) / bq)), bq, off, border_mode(border)};
     const u32 groups = (g.tiles + 16 * kBandWaves - 1) / (16 * kBandWaves);
-    void *args[] = {const_cast<U8Job *>(&j), const_cast<BandTaps *>(&taps), const_cast<BandGrid *>(&g)};
-    return hipLaunchKernel(reinterpret_cast<const void *>(&k_band_single<NB, NR, CLAMP, DIR>), dim3(groups),
+    void *args[] = {&job, const_cast<BandTaps *>(&taps), const_cast<BandGrid *>(&g)};
+    return hipLaunchKernel(reinterpret_cast<const void *>(&k_band_single<NB, NR, CLAMP, DIR, PAST>), dim3(groups),
                            dim3(64 * kBandWaves), args, 0, st);
+}
+
+template <int NB, int NR, bool CLAMP, int DIR>
+hipError_t launch_any(const U8Job &j, const BandTaps &taps, int off, int border, int waves, hipStream_t st)
+{
+    OutputStores o;
+    o.add(j);
+    return o.past_l2() ? launch_band<NB, NR, CLAMP, DIR, true>(j, taps, off, border, waves, st)
+                       : launch_band<NB, NR, CLAMP, DIR, false>(j, taps, off, border, waves, st);
 }
 
 }  // namespace
 
+void u8_tile(U8Job &j, const U8Shape &s)
+{
+    const int64_t nt = ((int64_t)j.Wo + s.ppl - 1) / s.ppl, whole = (nt + 7) / 8 * 8;
+    j.nt = (u32)((whole - nt) * 16 <= nt ? whole : nt);
+    j.inv_nt = (u32)std::min<uint64_t>((1ull << 32) / std::max<u32>(1, j.nt), 0xffffffffull);
+}
+
 hipError_t launch_u8_single(const U8Job &j, int border, const U8Shape &s, hipStream_t st)
 {
     const int off = border == 1 ? 2 : 0;
-    if (!j.dir_type) return launch_band<4, 4, false, 0>(j, kTaps4x5, off, border, s.waves, st);
+    if (!j.dir_type) return launch_any<4, 4, false, 0>(j, kTaps4x5, off, border, s.waves, st);
     // planes: 16 bytes of a plane a lane, so that a wave's stores are whole
     // lines (int32 planes of 4096^2: 52.5 us, with two stores a lane 113)
-    if (j.dir_type == 1) return launch_band<2, 4, false, kPlanes16>(j, kTaps4x5, off, border, s.waves, st);
-    return launch_band<1, 4, false, kPlanes32>(j, kTaps4x5, off, border, s.waves, st);
+    if (j.dir_type == 1) return launch_any<2, 4, false, kPlanes16>(j, kTaps4x5, off, border, s.waves, st);
+    return launch_any<1, 4, false, kPlanes32>(j, kTaps4x5, off, border, s.waves, st);
 }
 
 hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, hipStream_t st)
@@ -87,9 +102,9 @@ hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, 
     const bool small = op == 2;
     const int off = border != 1 ? 0 : small ? 1 : 2;
     const BandTaps &taps = small ? kTaps2x3 : kTaps2x5;
-    if (!j.dir_type) return launch_band<4, 2, false, 0>(j, taps, off, border, s.waves, st);
-    if (j.dir_type == 1) return launch_band<2, 2, false, kPlanes16>(j, taps, off, border, s.waves, st);
-    return launch_band<1, 2, false, kPlanes32>(j, taps, off, border, s.waves, st);
+    if (!j.dir_type) return launch_any<4, 2, false, 0>(j, taps, off, border, s.waves, st);
+    if (j.dir_type == 1) return launch_any<2, 2, false, kPlanes16>(j, taps, off, border, s.waves, st);
+    return launch_any<1, 2, false, kPlanes32>(j, taps, off, border, s.waves, st);
 }
 
 bool mfma_weights_fit(const int32_t *weights)
@@ -120,12 +135,62 @@ hipError_t launch_u8_mfma_weighted(const U8Job &j, int border, const int32_t *we
     }
     const bool clamp = most > 181;
     const int off = border == 1 ? 2 : 0;
-    if (j.dir_type == 1) return launch_band<2, 4, false, kPlanes16>(j, taps, off, border, waves, st);   // sums <= 128
+    if (j.dir_type == 1) return launch_any<2, 4, false, kPlanes16>(j, taps, off, border, waves, st);   // sums <= 128
     if (j.dir_type == 2)
-        return clamp ? launch_band<1, 4, true, kPlanes32>(j, taps, off, border, waves, st)
-                     : launch_band<1, 4, false, kPlanes32>(j, taps, off, border, waves, st);
-    return clamp ? launch_band<4, 4, true, 0>(j, taps, off, border, waves, st)
-                 : launch_band<4, 4, false, 0>(j, taps, off, border, waves, st);
+        return clamp ? launch_any<1, 4, true, kPlanes32>(j, taps, off, border, waves, st)
+                     : launch_any<1, 4, false, kPlanes32>(j, taps, off, border, waves, st);
+    return clamp ? launch_any<4, 4, true, 0>(j, taps, off, border, waves, st)
+                 : launch_any<4, 4, false, 0>(j, taps, off, border, waves, st);
+}
+
+void batched_tiles(const U8Job &j, int32_t img, int th, int, std::vector<int4> &first, std::vector<int4> &)
+{
+    batched_tiles_each(j, img, th, [&](int4 t) { first.push_back(t); });
+}
+
+hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border, bool past,
+                             bool dir, const U8Shape &, int grid, hipStream_t st, uint32_t *claims)
+{
+    int off = border == 1 ? 2 : 0, bm = border_mode(border);
+    void *args[] = {(void *)&jobs, (void *)&tiles, (void *)&total, (void *)&queue, (void *)&claims,
+                    const_cast<BandTaps *>(&kTaps4x5), (void *)&off, (void *)&bm};
+    return hipLaunchKernel(batched_fn(dir, past), dim3(grid), dim3(64 * kBandWaves), args, 0, st);
+}
+
+int u8_persistent_grid(const U8Shape &, int, bool past, bool dir)
+{
+    int dev = 0, ncu = 0, per_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_fn(dir, past), 64 * kBandWaves, 0) != hipSuccess)
+        return 0;
+    if (per_cu < 1) per_cu = 1;
+    return ncu * per_cu;
+}
+
+// The fixed buffer of the allocation-free batched call.  In host code this
+// name is only a handle for hipGetSymbolAddress; kernels get the device
+// address that call returns.
+static __device__ __align__(256) unsigned char scratch[kNoallocBytes];
+
+hipError_t noalloc_scratch(void **out)
+{
+    constexpr int kMaxDevices = 64;
+    static std::mutex mu;
+    static void *addr[kMaxDevices] = {};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    std::lock_guard<std::mutex> lk(mu);
+    if (!addr[dev]) {
+        void *p = nullptr;
+        if ((e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch))) != hipSuccess) return e;
+        if (!p) return hipErrorInvalidSymbol;
+        addr[dev] = p;
+    }
+    *out = addr[dev];
+    return hipSuccess;
 }
 
 }  // namespace s4x5

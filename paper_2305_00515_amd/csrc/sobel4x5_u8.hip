@@ -2,7 +2,7 @@
 // autotuner's fingerprint of output planes, and the diagnostics of the uint8
 // roundings.
 
-#include "u8_sweep.hpp"
+#include "u8_band.hpp"
 
 namespace s4x5 {
 namespace {
@@ -56,65 +56,39 @@ __global__ __launch_bounds__(256) void k_fingerprint(const uint8_t *__restrict__
     if (threadIdx.x == 0) out[blockIdx.x] = red[0];
 }
 
+// The kernels' rounding of a magnitude (method 0), and the same by an integer
+// root (method 1).
 __global__ void k_round_mag(const int32_t *S, uint8_t *out, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (uint8_t)round_mag(S[i]);
+    if (i < n) out[i] = (uint8_t)mag_byte(S[i], 0, 0);
 }
 
-// The same rounding through the LDS table, filled and read exactly as the
-// sweep does.
-__global__ __launch_bounds__(256) void k_round_mag_lut(const int32_t *S, uint8_t *out, int64_t n)
+// round(sqrt(S)) is the number of r in 1..255 with (r - 1/2)^2 < S, that is
+// r^2 - r < S for whole S: a bitwise search.
+__global__ void k_round_mag_int(const int32_t *S, uint8_t *out, int64_t n)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lut[kLutSize];
-    lut_fill<256>(lut);
-    __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (uint8_t)lut_mag((lds_u8 *)lut, S[i]);
+    if (i >= n) return;
+    int r = 0;
+    for (int b = 128; b > 0; b >>= 1)
+        if ((r + b) * (r + b - 1) < S[i]) r += b;
+    out[i] = (uint8_t)r;
 }
 
-// The four-directional sweep's rounding, step for step: quadruples
-// (E1, E2, Hp, Hm) of int16 in pairs on the packed halves of a register,
-// T = E1^2 + E2^2 + Hp^2 + Hm^2 saturated at 2^15 - 1 by the clamped
-// multiply-adds, then the table of round(sqrt(2 T)) in LDS.
+// Quadruples (E1, E2, Hp, Hm) of int16, S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2): the
+// clamp, the 24-bit squares and the rounding of the kernels.  The halves
+// E1 = (Gx + Gy) / 2, ... reach sqrt(S / 2), so they are clamped at 256 like
+// a response: one that is larger saturates the magnitude alone.
 __global__ __launch_bounds__(256) void k_round_quad(const int16_t *q, uint8_t *out, int64_t n)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lut[kLutTSize];
-    lut_fill_t<256>(lut);
-    __syncthreads();
-    const int64_t i = 2 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    u32 c[4];
-    for (int k = 0; k < 4; ++k) {
-        const u32 lo = (uint16_t)q[4 * i + k];
-        const u32 hi = i + 1 < n ? (uint16_t)q[4 * (i + 1) + k] : 0u;
-        c[k] = lo | (hi << 16);
-    }
-    u32 T = sq_sat(c[0]);
-    T = sq_sat_acc(c[1], T);
-    T = sq_sat_acc(c[2], T);
-    T = sq_sat_acc(c[3], T);
-    const lds_u8 *lp = (lds_u8 *)lut;
-    out[i] = (uint8_t)lp[T & 0xffffu];
-    if (i + 1 < n) out[i + 1] = (uint8_t)lp[T >> 16];
+    const int G[4] = {q[4 * i], q[4 * i + 1], q[4 * i + 2], q[4 * i + 3]};
+    out[i] = (uint8_t)mag_byte(2 * sum_squares<4, true>(G), 0, 0);
 }
 
 }  // namespace
-
-bool u8_rows_aligned(const U8Job &j)
-{
-    return ((reinterpret_cast<uintptr_t>(j.src) | (uintptr_t)j.src_pitch) & 15u) == 0;
-}
-
-void u8_tile(U8Job &j, const U8Shape &s)
-{
-    const int tw = 16 * s.ppl;
-    j.ntx = (j.Wo + tw - 1) / tw;
-    j.nty = (j.Ho + s.th - 1) / s.th;
-    j.nty4 = (j.nty + 3) / 4;
-    j.nwt = j.ntx * j.nty4;
-    j.nwt_h = ((j.ntx + 3) / 4) * j.nty;
-}
 
 hipError_t launch_copy16(const void *src, void *dst, int64_t n16, hipStream_t st)
 {
@@ -142,7 +116,7 @@ hipError_t launch_fingerprint(const void *base, int64_t pitch, int64_t row_bytes
 hipError_t launch_round_quad(const int16_t *q, uint8_t *out, int64_t n, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    const int64_t blocks = (n + 511) / 512;
+    const int64_t blocks = (n + 255) / 256;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_round_quad, dim3((unsigned)blocks), dim3(256), 0, st, q, out, n);
     return hipGetLastError();
@@ -154,7 +128,7 @@ hipError_t launch_round_mag(const int32_t *S, uint8_t *out, int64_t n, int metho
     const int64_t blocks = (n + 255) / 256;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     if (method == 1)
-        hipLaunchKernelGGL(k_round_mag_lut, dim3((unsigned)blocks), dim3(256), 0, st, S, out, n);
+        hipLaunchKernelGGL(k_round_mag_int, dim3((unsigned)blocks), dim3(256), 0, st, S, out, n);
     else
         hipLaunchKernelGGL(k_round_mag, dim3((unsigned)blocks), dim3(256), 0, st, S, out, n);
     return hipGetLastError();

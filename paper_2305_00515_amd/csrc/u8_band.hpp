@@ -169,34 +169,36 @@ struct BandTile {
 //   kShift:   the same at other addresses: the aligned words around a window
 //             are loaded and shifted (a load of several words at an address
 //             that is no multiple of 4 takes about twice as long);
-//   kEdge:    the words beside the lane's own columns are loaded inside the
-//             row and permuted, rows are mapped;
+//   kCols:    every row lies in the image; the words beside the lane's own
+//             columns are loaded inside the row and permuted;
+//   kEdge:    the same, and rows are mapped;
 //   kNarrow:  rows narrower than a tile: every word is loaded inside the row
 //             and permuted.
-constexpr int kInside = 0, kShift = 1, kEdge = 2, kNarrow = 3;
+constexpr int kInside = 0, kShift = 1, kCols = 2, kEdge = 3, kNarrow = 4;
 
 // Windows of the quads of one lane's tile.  load() issues the loads of the
 // next quad into `d`, words(d) puts the oldest loaded quad's words in place.
 template <int NB, int MODE>
 struct BandSource {
+    static constexpr bool kWhole = MODE != kEdge && MODE != kNarrow;   // every row of every lane lies in the image
+    static constexpr bool kBeside = MODE == kCols || MODE == kEdge;
     static_assert(NB == 1 || NB == 2 || NB == 4, "words per lane");
     static constexpr int kWords = NB + 2;
     static constexpr int kRaw = MODE == kShift ? NB + 3 : NB + 2;
-    static constexpr int kCols = MODE == kNarrow ? kWords : 2;
+    static constexpr int kMoved = MODE == kNarrow ? kWords : 2;   // words that are permuted
 
-    gsrc p;              // kInside: the lane's window, kEdge: its own columns, kNarrow: the row's start;
-                         // in its row of the next quad (without `whole`: in row 0)
+    gsrc p;              // kInside, kShift: the lane's window, kNarrow: the row's start, else its own
+                         // columns; in its row of the next quad (kEdge, kNarrow: in row 0)
     int64_t pitch;
     int quads;           // quads not loaded yet; the last one is loaded again when none is left
     int y, yf;           // the lane's row of the next quad to load / to put in place
     int H, W, bm;
-    bool whole;          // every row of every lane lies in the image
-    int col[kCols];      // kEdge: offsets of the words beside, kNarrow: columns of all words
-    u32 sel[kCols];
+    int col[kMoved];     // kNarrow: columns of the words; else offsets of the words beside
+    u32 sel[kMoved];
     u32 shift;           // kShift: bytes before the window in its first word
     int last;            // kShift: offset of the word that holds the window's last byte
 
-    __device__ __forceinline__ void init(const U8Job &J, const BandTile &t, int off, int border_mode, bool rows_in)
+    __device__ __forceinline__ void init(const U8Job &J, const BandTile &t, int off, int border_mode)
     {
         const int g = (threadIdx.x >> 4) & 3;
         const int x = t.xo + off - 4;
@@ -204,17 +206,16 @@ struct BandSource {
         H = J.H;
         W = J.W;
         bm = border_mode;
-        whole = MODE == kInside || MODE == kShift || rows_in;
         pitch = J.src_pitch;
         quads = t.steps + 1;
-        p = (gsrc)J.src + (MODE == kNarrow ? 0 : MODE == kEdge ? x + 4 : x);
-        if (whole) p += (int64_t)y * pitch;
+        p = (gsrc)J.src + (MODE == kNarrow ? 0 : kBeside ? x + 4 : x);
+        if (kWhole) p += (int64_t)y * pitch;
         if constexpr (MODE == kShift) {
             // four rows below, the shift is the same
             shift = (u32)(uintptr_t)p & 3;
             p -= shift;
             last = shift ? 4 * kWords : 4 * kWords - 4;
-        } else if constexpr (MODE == kEdge) {
+        } else if constexpr (kBeside) {
             col[0] = window_load(x, W) - (x + 4);
             sel[0] = window_sel(x, W, bm);
             col[1] = window_load(x + 4 + 4 * NB, W) - (x + 4);
@@ -231,8 +232,8 @@ struct BandSource {
     __device__ __forceinline__ void load(u32 (&d)[kRaw])
     {
         gsrc r = p;
-        if (!whole) r += (int64_t)band_index(y, H, bm) * pitch;
-        if constexpr (MODE == kEdge) {
+        if (!kWhole) r += (int64_t)band_index(y, H, bm) * pitch;
+        if constexpr (kBeside) {
             if constexpr (NB == 4) {
                 const bv4 v = *reinterpret_cast<const BAND_G bv4_u *>(r);
                 d[1] = v.x, d[2] = v.y, d[3] = v.z, d[4] = v.w;
@@ -268,7 +269,7 @@ struct BandSource {
             for (int b = 0; b < kWords; ++b) d[b] = v;
         }
         const bool more = --quads > 0;
-        if (whole)
+        if (kWhole)
             p += more ? 4 * pitch : 0;
         else
             y += more ? 4 : 0;
@@ -285,15 +286,15 @@ struct BandSource {
             else
                 e[b] = d[b];
         }
-        if constexpr (MODE == kEdge || MODE == kNarrow) {
-            if constexpr (MODE == kEdge) {
+        if constexpr (kBeside || MODE == kNarrow) {
+            if constexpr (kBeside) {
                 e[0] = __builtin_amdgcn_perm(0u, d[0], sel[0]);
                 e[NB + 1] = __builtin_amdgcn_perm(0u, d[NB + 1], sel[1]);
             } else {
 #pragma unroll
                 for (int b = 0; b < kWords; ++b) e[b] = __builtin_amdgcn_perm(0u, d[b], sel[b]);
             }
-            if (!whole) {
+            if (!kWhole) {
                 const u32 keep = bm == kBandZero && (yf < 0 || yf >= H) ? 0u : ~0u;
 #pragma unroll
                 for (int b = 0; b < kWords; ++b) e[b] &= keep;
@@ -328,19 +329,32 @@ __device__ __forceinline__ int sum_squares(const int (&G)[NR])
     return S;
 }
 
-// 4 N bytes at any address, past the L2: nothing here reads them again.
-template <int N>
+// 4 N bytes at any address.  PAST: past the L2 (a constant: the compiler makes
+// one ordinary store of a choice between the two).
+template <bool PAST, int N>
 __device__ __forceinline__ void store_words(gdst p, const u32 (&w)[N])
 {
     if constexpr (N % 4 == 0) {
 #pragma unroll
-        for (int i = 0; i < N; i += 4)
-            __builtin_nontemporal_store(bv4{w[i], w[i + 1], w[i + 2], w[i + 3]}, reinterpret_cast<BAND_G bv4_u *>(p + 4 * i));
+        for (int i = 0; i < N; i += 4) {
+            const bv4 v{w[i], w[i + 1], w[i + 2], w[i + 3]};
+            if constexpr (PAST)
+                __builtin_nontemporal_store(v, reinterpret_cast<BAND_G bv4_u *>(p + 4 * i));
+            else
+                *reinterpret_cast<BAND_G bv4_u *>(p + 4 * i) = v;
+        }
     } else if constexpr (N == 2) {
-        __builtin_nontemporal_store(bv2{w[0], w[1]}, reinterpret_cast<BAND_G bv2_u *>(p));
+        const bv2 v{w[0], w[1]};
+        if constexpr (PAST)
+            __builtin_nontemporal_store(v, reinterpret_cast<BAND_G bv2_u *>(p));
+        else
+            *reinterpret_cast<BAND_G bv2_u *>(p) = v;
     } else {
         static_assert(N == 1, "words");
-        __builtin_nontemporal_store(w[0], reinterpret_cast<BAND_G u32_u1 *>(p));
+        if constexpr (PAST)
+            __builtin_nontemporal_store(w[0], reinterpret_cast<BAND_G u32_u1 *>(p));
+        else
+            *reinterpret_cast<BAND_G u32_u1 *>(p) = w[0];
     }
 }
 
@@ -367,16 +381,14 @@ __device__ __forceinline__ void store_left(gdst p, const u32 (&w)[N], int left)
 // job says, none included (kPlanesAny).
 constexpr int kPlanes16 = 1, kPlanes32 = 2, kPlanesAny = 3;
 
-template <int NB, int NR, int MODE, bool CLAMP, int DIR>
-__device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T,
-                                           bool rows_in)
+template <int NB, int NR, int MODE, bool CLAMP, int DIR, bool PAST>
+__device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T)
 {
     constexpr int NC = 4 * NB;
-    constexpr bool IN = MODE == kInside || MODE == kShift;   // every lane's outputs lie in the image
     constexpr bool AHEAD = MODE != kNarrow;                    // two quads in flight; narrow images are small
     using Source = BandSource<NB, MODE>;
     Source src;
-    src.init(J, t, off, bm, rows_in);
+    src.init(J, t, off, bm);
     u32 raw[2][Source::kRaw];
     v4i B[NB + 1];   // windows (word b, word b + 1), of the quad in even and the one in odd place
     auto place = [&](const u32 (&d)[Source::kRaw], auto half) __attribute__((always_inline)) {
@@ -444,11 +456,11 @@ __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, in
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (IN || yo < J.Ho) {
-            const bool full = IN || left >= NC;
+        if (Source::kWhole || yo < J.Ho) {
+            const bool full = MODE != kNarrow || left >= NC;
             if (!DIR || J.mag) {
                 if (full)
-                    store_words(mag, m);
+                    store_words<PAST>(mag, m);
                 else
                     store_left<1>(mag, m, left);
             }
@@ -459,12 +471,12 @@ __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, in
                     gdst p = (gdst)J.dir[f * 4 / NR] + plane;
                     if ((DIR & kPlanes16) && (DIR != kPlanesAny || J.dir_type == 1)) {
                         if (full)
-                            store_words(p, s16[f]);
+                            store_words<PAST>(p, s16[f]);
                         else
                             store_left<2>(p, s16[f], left);
                     } else if ((DIR & kPlanes32) && (DIR != kPlanesAny || J.dir_type == 2)) {
                         if (full)
-                            store_words(p, s32[f]);
+                            store_words<PAST>(p, s32[f]);
                         else
                             store_left<4>(p, s32[f], left);
                     }
@@ -496,14 +508,14 @@ __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, in
     if (k > 0) step(std::integral_constant<int, 0>{});
 }
 
-// Tile `id` of an image's tile grid: nt tile columns of 4 NB pixels, bands
+// Tile `id` of an image's tile grid: J.nt tile columns of 4 NB pixels, bands
 // of bq steps.
 template <int NB>
-__device__ __forceinline__ BandTile band_tile(const U8Job &J, u32 id, u32 nt, u32 inv_nt, int bq)
+__device__ __forceinline__ BandTile band_tile(const U8Job &J, u32 id, int bq)
 {
     BandTile t;
-    u32 band = __umulhi(id, inv_nt), tx = id - band * nt;   // at most one short
-    if (tx >= nt) ++band, tx -= nt;
+    u32 band = __umulhi(id, J.inv_nt), tx = id - band * J.nt;   // at most one short
+    if (tx >= J.nt) ++band, tx -= J.nt;
     // a tile beyond the last one that fits ends at the edge (nt may be rounded up)
     t.xo = min((int)(tx * 4 * NB), max(J.Wo - 4 * NB, 0));
     t.yo = 4 * bq * (int)band;
@@ -513,7 +525,7 @@ __device__ __forceinline__ BandTile band_tile(const U8Job &J, u32 id, u32 nt, u3
     return t;
 }
 
-template <int NB, int NR, bool CLAMP, int DIR>
+template <int NB, int NR, bool CLAMP, int DIR, bool PAST>
 __device__ __forceinline__ void band_run(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T)
 {
     const int x = t.xo + off - 4, y = t.yo + off - 2;
@@ -522,17 +534,18 @@ __device__ __forceinline__ void band_run(const U8Job &J, const BandTile &t, int 
     const bool cols_in = all(x >= 0 && x + 4 * NB + 8 <= J.W && J.Wo >= 4 * NB);
     const bool word = all((((u32)(uintptr_t)J.src + (u32)x) & 3) == 0) && (J.src_pitch & 3) == 0;
     if (rows_in && cols_in && word)
-        band_sweep<NB, NR, kInside, CLAMP, DIR>(J, t, off, bm, T, true);
+        band_sweep<NB, NR, kInside, CLAMP, DIR, PAST>(J, t, off, bm, T);
     else if (rows_in && cols_in)
-        band_sweep<NB, NR, kShift, CLAMP, DIR>(J, t, off, bm, T, true);
+        band_sweep<NB, NR, kShift, CLAMP, DIR, PAST>(J, t, off, bm, T);
+    else if (rows_in && J.Wo >= 4 * NB)
+        band_sweep<NB, NR, kCols, CLAMP, DIR, PAST>(J, t, off, bm, T);
     else if (J.Wo >= 4 * NB)
-        band_sweep<NB, NR, kEdge, CLAMP, DIR>(J, t, off, bm, T, rows_in);
+        band_sweep<NB, NR, kEdge, CLAMP, DIR, PAST>(J, t, off, bm, T);
     else
-        band_sweep<NB, NR, kNarrow, CLAMP, DIR>(J, t, off, bm, T, rows_in);
+        band_sweep<NB, NR, kNarrow, CLAMP, DIR, PAST>(J, t, off, bm, T);
 }
 
 struct BandGrid {
-    u32 nt, inv_nt;  // tile columns; floor(2^32 / nt), at most 2^32 - 1
     u32 tiles;       // tiles of the image
     int bq;          // steps of a band
     int off, bm;     // output (0, 0) is centred at input (off, off); border rule
@@ -546,15 +559,58 @@ __device__ __forceinline__ u32 band_workgroup(u32 b, u32 groups)
     return b < 8 * per ? (b & 7) * per + b / 8 : b;
 }
 
-template <int NB, int NR, bool CLAMP, int DIR>
+template <int NB, int NR, bool CLAMP, int DIR, bool PAST>
 __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(DIR ? 3 : 4, 4))) void k_band_single(
     const U8Job J, const BandTaps T, const BandGrid gr)
 {
     const u32 wave = band_workgroup(blockIdx.x, gridDim.x) * kBandWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const u32 id = min(16 * wave + (threadIdx.x & 15), gr.tiles - 1);
-    const BandTile t = band_tile<NB>(J, id, gr.nt, gr.inv_nt, gr.bq);
+    const BandTile t = band_tile<NB>(J, id, gr.bq);
     if (16 * wave >= gr.tiles) return;
-    band_run<NB, NR, CLAMP, DIR>(J, t, gr.off, gr.bm, T);
+    band_run<NB, NR, CLAMP, DIR, PAST>(J, t, gr.off, gr.bm, T);
+}
+
+// Batch of images: wave-tile t of the host-built table is {image, first tile,
+// steps of a band, tiles of the image}.  With queue == nullptr the grid holds
+// one wave for each (static form).  Otherwise a persistent grid draws them
+// from queue[0] until none are left; each wave then counts itself out in
+// queue[1], and the last one resets both words for the next launch.  claims
+// (debug launches only, else nullptr): one counter per wave-tile, plus one
+// for every time a wave takes it, so a launch that leaves any counter other
+// than 1 has skipped or repeated one.
+template <int NB, int DIR, bool PAST>
+__global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(DIR ? 3 : 4, 4))) void k_band_batched(
+    const U8Job *__restrict__ jobs, const int4 *__restrict__ table, int32_t total, uint32_t *queue, uint32_t *claims,
+    const BandTaps T, int off, int bm)
+{
+    for (;;) {
+        int t;
+        if (queue == nullptr) {
+            t = (int)band_workgroup(blockIdx.x, gridDim.x) * kBandWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        } else {
+            u32 tv = 0;
+            if ((threadIdx.x & 63) == 0) tv = atomicAdd(&queue[0], 1u);
+            t = __builtin_amdgcn_readfirstlane((int)tv);
+        }
+        if (t >= total) break;
+        const int4 e = table[t];
+        const U8Job J = jobs[e.x];
+        if (claims != nullptr && (threadIdx.x & 63) == 0) atomicAdd(&claims[t], 1u);
+        const BandTile tile = band_tile<NB>(J, min((u32)e.y + (threadIdx.x & 15), (u32)e.w - 1), e.z);
+        band_run<NB, 4, false, DIR, PAST>(J, tile, off, bm, T);
+        if (queue == nullptr) break;
+    }
+    if (queue == nullptr) return;
+    const int lane = threadIdx.x & 63;
+    if (lane == 0) {
+        __threadfence();
+        const u32 nwaves = gridDim.x * kBandWaves;
+        if (atomicAdd(&queue[1], 1u) == nwaves - 1) {
+            queue[0] = 0;
+            queue[1] = 0;
+            __threadfence();
+        }
+    }
 }
 
 }  // namespace

@@ -114,3 +114,35 @@ def test_weighted_planes(oracle_mod, sobel_lib, gpu, amp, nonzero, dir_type):
                 torch.cuda.synchronize()
                 assert np.array_equal(mag.cpu().numpy(), om), (h, wd, border)
                 assert np.array_equal(np.stack([d.cpu().numpy() for d in dirs]), od), (h, wd, border)
+
+
+@pytest.mark.parametrize("sizes,planes", [
+    ([(1, 1), (3, 2), (2, 300), (64, 15), (17, 16), (33, 257), (5, 4099), (1030, 31)], 0),
+    ([(40, 64), (64, 128), (16, 32)], 1),           # rows of whole 64-byte pieces: stores past the L2
+    ([(40, 64), (9, 33), (31, 7), (2, 2)], 1),      # other rows
+    ([(40, 64), (9, 33), (31, 7), (2, 2)], 2),
+])
+def test_batches(oracle_mod, sobel_lib, gpu, sizes, planes):
+    """Wave-tiles that end inside a row of tiles, narrow images, both kinds of
+    plane stores; plan, one-shot and allocation-free call."""
+    imgs = [synth.rect_image(h, w, 7 * h + w) % 6 for h, w in sizes]
+    srcs = [torch.from_numpy(m).to(gpu) for m in imgs]
+    dt = {1: torch.int16, 2: torch.int32}.get(planes)
+    for border in (0, 2, 3):
+        want = [oracle_mod.sobel_u8(m, border) for m in imgs]
+        mags = [torch.full(m.shape, 9, dtype=torch.uint8, device=gpu) for m in imgs]
+        dirs = [[torch.full(m.shape, 9, dtype=dt, device=gpu) for _ in range(4)] for m in imgs] if planes else None
+        plan = sobel_lib.Plan(srcs, mags, border, dir_type=planes, dirs=dirs)
+        plan.launch()
+        shot = sobel_lib.sobel4x5_batched(srcs, border=border, dir_type=planes)
+        got = [[m] + (list(dirs[i]) if planes else []) for i, m in enumerate(mags)]
+        more = [[r[0]] + list(r[1]) for r in shot] if planes else [[r] for r in shot]
+        if not planes:
+            more = [a + b for a, b in zip(more, [[r] for r in sobel_lib.sobel4x5_batched_noalloc(srcs, border=border)])]
+        torch.cuda.synchronize()
+        for i, (om, od) in enumerate(want):
+            for k, t in enumerate(got[i] + more[i]):
+                plane = (k % 5) if planes else 0
+                ref = om if plane == 0 else od[plane - 1]
+                assert np.array_equal(t.cpu().numpy(), ref), (sizes[i], border, k)
+        plan.close()
