@@ -30,6 +30,25 @@
 // +-2 neighbourhood of a column pair).  A wave loads 128 columns and keeps
 // the ones whose whole stencil chain lies inside its lanes (forward: 2
 // columns of halo per side, adjoint: 6).
+//
+// What bounds it (32 x 1024^2): the forward memory, 268 MB in 59 us, 4.6 TB/s;
+// a plain copy of its bytes takes 54 us.  The adjoint its arithmetic: 72
+// vector instructions a column and row step, 77 us at the full issue rate with
+// the halo columns and the 8 warm-up rows of a 73-row range, in 97 us; a copy
+// of its 403 MB takes 81.  Together 147 us, 190 before:
+//   - strips inside the image load and store a lane's pair in one piece, past
+//     the L2 on the way out (forward 77 -> 67 us, adjoint 118 -> 105, with the
+//     next two);
+//   - rows are walked in scalar registers, and the loads add a 32-bit lane
+//     offset to them: no vector instruction addresses memory;
+//   - the warm-up steps compute only the stages whose rows are there;
+//   - halves of the diagonal responses, shared factors in the adjoint's
+//     sums, and the scaling of tiny S only in rows that hold one: 86 -> 72
+//     instructions (adjoint 105 -> 97 us);
+//   - short row ranges where a batch is small or memory is the bound
+//     (chunks_for: forward 67 -> 59 us; 1 x 256^2 38.6 -> 9.8 us).
+// Five waves a SIMD (96 registers) spill and take 156 us; each XCD on one
+// stretch of the batch takes the forward to 72 us.
 
 #include "internal.hpp"
 
@@ -42,6 +61,11 @@ namespace s4x5 {
 namespace {
 
 constexpr int kWavesPerGroup = 4;
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef f2v f2v_a4 __attribute__((aligned(4)));      // a pair at any element
+#define GF __attribute__((address_space(1)))
+typedef const GF char *gin;
+typedef GF char *gout;
 constexpr int kHaloF = 2, kOwnF = 128 - 2 * kHaloF;   // forward: 124 columns per wave
 constexpr int kHaloB = 6, kOwnB = 128 - 2 * kHaloB;   // adjoint: 116 columns per wave
 
@@ -107,9 +131,10 @@ __device__ __forceinline__ void hfilters(F2 v, F2 &hr, F2 &hs)
     hr = (n.p2 - n.m2) + 2.0f * hs;
 }
 
-// c = [1,4,6,4,1] and c'/d combination over five values a0..a4, b0..b4:
-//   C  = (a0 + a4) + 4 (a1 + a3) + 6 a2
-//   C' = 6 (a0 + a1 + a3 + a4) + 2 a2 - 10 (b0 + b4) + 12 b2
+// c = [1,4,6,4,1] and half the c'/d combination over five values a0..a4,
+// b0..b4 (halving is exact, and saves the multiplication of a2):
+//   C      = (a0 + a4) + 4 (a1 + a3) + 6 a2
+//   C' / 2 = 3 (a0 + a1 + a3 + a4) + a2 - 5 (b0 + b4) + 6 b2
 __device__ __forceinline__ float comb_c(float a0, float a1, float a2, float a3, float a4)
 {
     return (a0 + a4) + 4.0f * (a1 + a3) + 6.0f * a2;
@@ -117,7 +142,7 @@ __device__ __forceinline__ float comb_c(float a0, float a1, float a2, float a3, 
 __device__ __forceinline__ float comb_cd(float a0, float a1, float a2, float a3, float a4, float b0, float b2,
                                          float b4)
 {
-    return 6.0f * ((a0 + a4) + (a1 + a3)) + 2.0f * a2 - 10.0f * (b0 + b4) + 12.0f * b2;
+    return 3.0f * ((a0 + a4) + (a1 + a3)) + a2 - 5.0f * (b0 + b4) + 6.0f * b2;
 }
 __device__ __forceinline__ F2 comb_c(F2 a0, F2 a1, F2 a2, F2 a3, F2 a4)
 {
@@ -129,7 +154,7 @@ __device__ __forceinline__ F2 comb_cd(F2 a0, F2 a1, F2 a2, F2 a3, F2 a4, F2 b0, 
             comb_cd(a0.b, a1.b, a2.b, a3.b, a4.b, b0.b, b2.b, b4.b)};
 }
 
-// Columns-first pair (Gy, Gd+) from the lane's v_r and v_s of the centre
+// Columns-first pair (Gy, Gd+ / 2) from the lane's v_r and v_s of the centre
 // row: horizontal combination across the columns.
 __device__ __forceinline__ void hcombine(F2 vr, F2 vs, F2 &C, F2 &Cd)
 {
@@ -138,83 +163,123 @@ __device__ __forceinline__ void hcombine(F2 vr, F2 vs, F2 &C, F2 &Cd)
     Cd = comb_cd(r.m2, r.m1, vr, r.p1, r.p2, t.m2, vs, t.p2);
 }
 
-__device__ __forceinline__ float sum_sq(float Gx, float Gy, float Gp, float Gm)
+// Hp, Hm: halves of Gd+, Gd-
+__device__ __forceinline__ float sum_sq(float Gx, float Gy, float Hp, float Hm)
 {
-    return Gx * Gx + Gy * Gy + 0.5f * (Gp * Gp + Gm * Gm);
+    return Gx * Gx + Gy * Gy + 2.0f * (Hp * Hp + Hm * Hm);
 }
 
 // M = sqrt(S) by the hardware square root (within 1 ulp; below S = 2^-100,
 // i.e. M < 1e-15, its error is an absolute one far under the tolerance).
-__device__ __forceinline__ float mag_of(float Gx, float Gy, float Gp, float Gm)
+__device__ __forceinline__ float mag_of(float Gx, float Gy, float Hp, float Hm)
 {
-    return __builtin_amdgcn_sqrtf(sum_sq(Gx, Gy, Gp, Gm));
+    return __builtin_amdgcn_sqrtf(sum_sq(Gx, Gy, Hp, Hm));
 }
 
 // g / M = g / sqrt(S) for S > 0, 0 for S = 0: the hardware reciprocal square
 // root (within 1 ulp).  Below 2^-100 (down to the denormals, which the
 // hardware operation does not take) S is first scaled by 2^100 and the
 // result by 2^50; both scalings are exact, so the 1 ulp bound holds for
-// every S > 0.
-__device__ __forceinline__ float scale_of(float g, float S)
+// every S > 0.  Rows without such an S in any lane skip that (about five
+// instructions a pixel).
+__device__ __forceinline__ float scale_tiny(float g, float S)
 {
     const bool tiny = S < 0x1p-100f;
     const float r = __builtin_amdgcn_rsqf(S * (tiny ? 0x1p+100f : 1.0f)) * (tiny ? 0x1p+50f : 1.0f);
     return S > 0.f ? g * r : 0.f;
 }
+__device__ __forceinline__ F2 scale_of(F2 g, F2 S)
+{
+    F2 r{g.a * __builtin_amdgcn_rsqf(S.a), g.b * __builtin_amdgcn_rsqf(S.b)};
+    const bool plain = S.a >= 0x1p-100f && S.b >= 0x1p-100f;   // false for NaN too
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!plain) != 0, 0))
+        r = F2{scale_tiny(g.a, S.a), scale_tiny(g.b, S.b)};
+    return r;
+}
 
 template <int P>
 using Ph = std::integral_constant<int, P>;
 
-// Steps 0 .. T-1 of a five-slot ring: whole blocks of five in a loop with a
-// single exit, then the 0..4 remaining steps.  (Breaking out of the loop
-// after any step makes flow blocks with edges back to the loop header; the
-// memory-wait analysis merges their state into the header and waits there
-// for every row in flight.)
-template <class Step>
-__device__ __forceinline__ void run_steps(int T, Step &step)
+// Steps t0 .. t1-1 of a five-slot ring, t0 = S mod 5 (step t has phase t mod
+// 5): whole blocks of five in a loop with a single exit, then the 0..4
+// remaining steps.  (Breaking out of the loop after any step makes flow
+// blocks with edges back to the loop header; the memory-wait analysis merges
+// their state into the header and waits there for every row in flight.)
+template <int S, class Step>
+__device__ __forceinline__ void run_steps(int t0, int t1, Step &step)
 {
-    const int nfull = T - T % 5;
-    for (int t = 0; t < nfull; t += 5) {
-        step(t, Ph<0>{});
-        step(t + 1, Ph<1>{});
-        step(t + 2, Ph<2>{});
-        step(t + 3, Ph<3>{});
-        step(t + 4, Ph<4>{});
+    int t = t0;
+    for (; t + 5 <= t1; t += 5) {
+        step(t, Ph<S % 5>{});
+        step(t + 1, Ph<(S + 1) % 5>{});
+        step(t + 2, Ph<(S + 2) % 5>{});
+        step(t + 3, Ph<(S + 3) % 5>{});
+        step(t + 4, Ph<(S + 4) % 5>{});
     }
-    if (nfull < T) {
-        step(nfull, Ph<0>{});
-        if (nfull + 1 < T) {
-            step(nfull + 1, Ph<1>{});
-            if (nfull + 2 < T) {
-                step(nfull + 2, Ph<2>{});
-                if (nfull + 3 < T) step(nfull + 3, Ph<3>{});
+    if (t < t1) {
+        step(t, Ph<S % 5>{});
+        if (t + 1 < t1) {
+            step(t + 1, Ph<(S + 1) % 5>{});
+            if (t + 2 < t1) {
+                step(t + 2, Ph<(S + 2) % 5>{});
+                if (t + 3 < t1) step(t + 3, Ph<(S + 3) % 5>{});
             }
         }
     }
 }
 
-// Steps t0 .. t1-1 (t0 a multiple of five, so the ring phase of step t is
-// t % 5), in blocks of five with a single exit, then the rest.
-template <class Step>
-__device__ __forceinline__ void run_steps_from(int t0, int t1, Step &step)
-{
-    const int nfull = t0 + (t1 - t0) / 5 * 5;
-    for (int t = t0; t < nfull; t += 5) {
-        step(t, Ph<0>{});
-        step(t + 1, Ph<1>{});
-        step(t + 2, Ph<2>{});
-        step(t + 3, Ph<3>{});
-        step(t + 4, Ph<4>{});
+// Rows r, r + 1, ... of an image as the border rule maps them, in scalar
+// registers; after `count` rows the last one repeats.
+template <int BM>
+struct RowWalk {
+    gin base, p;
+    int64_t pitch;
+    int r, last, H;      // p advances from rows [0, last); kRefl: the last row
+    __device__ __forceinline__ RowWalk(gin img, int64_t row_pitch, int row, int height, int count)
+        : base(img), pitch(row_pitch), r(row), last(row + count - 1), H(height)
+    {
+        if (BM != kRefl) last = max(min(last, H - 1), 0);
+        p = base + (int64_t)edge_index<BM>(r, H) * pitch;
     }
-    if (nfull < t1) {
-        step(nfull, Ph<0>{});
-        if (nfull + 1 < t1) {
-            step(nfull + 1, Ph<1>{});
-            if (nfull + 2 < t1) {
-                step(nfull + 2, Ph<2>{});
-                if (nfull + 3 < t1) step(nfull + 3, Ph<3>{});
-            }
+    __device__ __forceinline__ void next()
+    {
+        if constexpr (BM == kRefl) {
+            r = min(r + 1, last);
+            p = base + (int64_t)edge_index<BM>(r, H) * pitch;
+        } else {
+            p += (uint32_t)r < (uint32_t)last ? pitch : 0;
+            ++r;
         }
+        // kept as a scalar base: as a pointer of each lane it would be
+        // advanced by a vector instruction a load
+        asm volatile("" : "+s"(p));
+    }
+};
+
+// A lane's column pair of a row: one load where the columns are neighbours
+// (IN), else two.  The offsets stay 32-bit values of the block that loads, so
+// that they are added to the scalar base by the load itself.
+template <bool IN>
+__device__ __forceinline__ F2 load_pair(gin row, uint32_t &oa, uint32_t &ob)
+{
+    asm volatile("" : "+v"(oa));
+    if constexpr (!IN) asm volatile("" : "+v"(ob));
+    if constexpr (IN) {
+        const f2v p = *reinterpret_cast<const GF f2v_a4 *>(row + oa);
+        return F2{p.x, p.y};
+    } else {
+        return F2{*reinterpret_cast<const GF float *>(row + oa), *reinterpret_cast<const GF float *>(row + ob)};
+    }
+}
+
+// Stores past the L2: nothing here reads the outputs again.
+__device__ __forceinline__ void store_pair(gout p, F2 v, bool keep_a, bool keep_b)
+{
+    if (keep_a && keep_b) {
+        __builtin_nontemporal_store(f2v{v.a, v.b}, reinterpret_cast<GF f2v_a4 *>(p));
+    } else {
+        if (keep_a) *reinterpret_cast<GF float *>(p) = v.a;
+        if (keep_b) *reinterpret_cast<GF float *>(p + 4) = v.b;
     }
 }
 
@@ -223,6 +288,70 @@ __device__ __forceinline__ void run_steps_from(int t0, int t1, Step &step)
 // output rows [o0, o1).  Lane l holds output columns s*124 - 2 + 2l + {0, 1}
 // (centre columns + OFF).  Step t loads input row o0 + OFF - 2 + t and, from
 // t = 4 on, finishes output row o0 + t - 4.  BM is the border rule.
+// IN: every column the wave loads lies inside the image.
+template <int OFF, int BM, bool IN>
+__device__ __forceinline__ void fwd_sweep(const F32Args &a, int b, int s, int o0, int o1)
+{
+    const int lane = threadIdx.x & 63;
+    const int ox = s * kOwnF - kHaloF + 2 * lane;            // output column of element a
+    const bool in_lane = lane >= kHaloF / 2 && lane < (kHaloF + kOwnF) / 2;
+    const bool keep_a = in_lane && (IN || ox < a.Wo), keep_b = IN ? keep_a : in_lane && ox + 1 < a.Wo;
+    uint32_t xa = (uint32_t)edge_index<BM>(ox + OFF, a.W) * 4u, xb = (uint32_t)edge_index<BM>(ox + 1 + OFF, a.W) * 4u;
+    // ZERO: does the lane's column lie inside the image?
+    const bool ina = IN || (ox + OFF >= 0 && ox + OFF < a.W), inb = IN || (ox + 1 + OFF >= 0 && ox + 1 + OFF < a.W);
+    const int r0 = o0 + OFF - 2, T = o1 - o0 + 4;
+    RowWalk<BM> src((gin)a.src + (int64_t)b * a.src_bstride, a.src_pitch, r0, a.H, T);
+    gout dst = (gout)a.out + (int64_t)b * a.out_bstride + (int64_t)o0 * a.out_pitch;
+    uint32_t oa = (uint32_t)max(ox, 0) * 4u;
+
+    F2 X[5], HR[5], HS[5], pf[5];
+    constexpr int PD = 3;   // rows loaded ahead
+    auto load = [&](F2 &v) __attribute__((always_inline)) {
+        v = load_pair<IN>(src.p, xa, xb);
+        src.next();
+    };
+    // prologue loads in row order (the first steps consume them)
+#pragma unroll
+    for (int t = 0; t < PD; ++t) {
+        load(pf[t]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    auto enter = [&](int t, auto phase) __attribute__((always_inline)) {
+        constexpr int p = decltype(phase)::value;
+        load(pf[(p + PD) % 5]);
+        F2 x = pf[p];
+        if constexpr (BM == kZero) {
+            const bool rin = r0 + t >= 0 && r0 + t < a.H;
+            x = F2{rin && ina ? x.a : 0.f, rin && inb ? x.b : 0.f};
+        }
+        X[p] = x;
+        hfilters(x, HR[p], HS[p]);
+    };
+    auto step = [&](int t, auto phase) __attribute__((always_inline)) {
+        constexpr int p = decltype(phase)::value;
+        constexpr int s0 = (p + 1) % 5, s1 = (p + 2) % 5, s2 = (p + 3) % 5, s3 = (p + 4) % 5, s4 = p;
+        enter(t, phase);
+        const F2 Gx = comb_c(HR[s0], HR[s1], HR[s2], HR[s3], HR[s4]);
+        const F2 Hm = comb_cd(HR[s0], HR[s1], HR[s2], HR[s3], HR[s4], HS[s0], HS[s2], HS[s4]);
+        const F2 vs = X[s3] - X[s1];
+        const F2 vr = (X[s4] - X[s0]) + 2.0f * vs;
+        F2 Gy, Hp;
+        hcombine(vr, vs, Gy, Hp);
+        F2 m{mag_of(Gx.a, Gy.a, Hp.a, Hm.a), mag_of(Gx.b, Gy.b, Hp.b, Hm.b)};
+        // every lane finishes its sums: inside the store's branch the lane
+        // shifts could not be part of the additions
+        asm volatile("" : "+v"(m.a), "+v"(m.b), "+v"(oa));
+        store_pair(dst + oa, m, keep_a, keep_b);
+        dst += a.out_pitch;
+        asm volatile("" : "+s"(dst));
+    };
+    enter(0, Ph<0>{});
+    enter(1, Ph<1>{});
+    enter(2, Ph<2>{});
+    enter(3, Ph<3>{});
+    run_steps<4>(4, T, step);
+}
+
 template <int OFF, int BM>
 __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_fwd(F32Args a, int nstrip, int nchunk)
 {
@@ -233,68 +362,11 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_fwd(F32Args a, int 
     const int s = rem % nstrip, k = rem / nstrip;
     const int o0 = (int)((int64_t)k * a.Ho / nchunk), o1 = (int)((int64_t)(k + 1) * a.Ho / nchunk);
     if (o1 <= o0) return;
-    const int lane = threadIdx.x & 63;
-    const int ox = s * kOwnF - kHaloF + 2 * lane;            // output column of element a
-    const bool in_lane = lane >= kHaloF / 2 && lane < (kHaloF + kOwnF) / 2;
-    const bool keep_a = in_lane && ox < a.Wo, keep_b = in_lane && ox + 1 < a.Wo;
-    const char *src = reinterpret_cast<const char *>(a.src) + (int64_t)b * a.src_bstride;
-    const int64_t xa = (int64_t)edge_index<BM>(ox + OFF, a.W) * 4, xb = (int64_t)edge_index<BM>(ox + 1 + OFF, a.W) * 4;
-    // ZERO: does the lane's column lie inside the image?
-    const bool ina = ox + OFF >= 0 && ox + OFF < a.W, inb = ox + 1 + OFF >= 0 && ox + 1 + OFF < a.W;
-    char *dst = reinterpret_cast<char *>(a.out) + (int64_t)b * a.out_bstride;
-    const int64_t oa = (int64_t)(ox < 0 ? 0 : ox) * 4;
-    const int r0 = o0 + OFF - 2;
-    // both kept columns stored with one 8-byte store
-    const bool vst = keep_a && keep_b && ((reinterpret_cast<uintptr_t>(dst) | (uintptr_t)a.out_pitch) & 7u) == 0;
-    // a pair is two 4-byte loads at the lane's border-mapped columns (see
-    // the adjoint's loads)
-    auto ld = [&](int t) {
-        const int r = r0 + t;
-        const char *row = src + (int64_t)edge_index<BM>(r, a.H) * a.src_pitch;
-        F2 v{*reinterpret_cast<const float *>(row + xa), *reinterpret_cast<const float *>(row + xb)};
-        if constexpr (BM == kZero) {
-            const bool rin = r >= 0 && r < a.H;
-            v = F2{rin && ina ? v.a : 0.f, rin && inb ? v.b : 0.f};
-        }
-        return v;
-    };
-    const int T = o1 - o0 + 4;
-
-    F2 X[5], HR[5], HS[5], pf[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) X[i] = HR[i] = HS[i] = pf[i] = F2{0.f, 0.f};
-    constexpr int PD = 3;   // rows loaded ahead
-    // prologue loads in row order (the loop's first steps consume them)
-#pragma unroll
-    for (int t = 0; t < PD; ++t) {
-        pf[t] = ld(t);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-
-    auto step = [&](int t, auto phase) {
-        constexpr int p = decltype(phase)::value;
-        constexpr int s0 = (p + 1) % 5, s1 = (p + 2) % 5, s2 = (p + 3) % 5, s3 = (p + 4) % 5, s4 = p;
-        pf[(p + PD) % 5] = ld(min(t + PD, T - 1));
-        const F2 x = pf[p];
-        X[s4] = x;
-        hfilters(x, HR[s4], HS[s4]);
-        if (t < 4) return;
-        const F2 Gx = comb_c(HR[s0], HR[s1], HR[s2], HR[s3], HR[s4]);
-        const F2 Gm = comb_cd(HR[s0], HR[s1], HR[s2], HR[s3], HR[s4], HS[s0], HS[s2], HS[s4]);
-        const F2 vs = X[s3] - X[s1];
-        const F2 vr = (X[s4] - X[s0]) + 2.0f * vs;
-        F2 Gy, Gp;
-        hcombine(vr, vs, Gy, Gp);
-        float *row = reinterpret_cast<float *>(dst + (int64_t)(o0 + t - 4) * a.out_pitch + oa);
-        const float ma = mag_of(Gx.a, Gy.a, Gp.a, Gm.a), mb = mag_of(Gx.b, Gy.b, Gp.b, Gm.b);
-        if (vst) {
-            *reinterpret_cast<float2 *>(row) = float2{ma, mb};
-        } else {
-            if (keep_a) row[0] = ma;
-            if (keep_b) row[1] = mb;
-        }
-    };
-    run_steps(T, step);
+    const int x0 = s * kOwnF - kHaloF + OFF;
+    if (x0 >= 0 && x0 + 128 <= a.W && s * kOwnF + kOwnF <= a.Wo)
+        fwd_sweep<OFF, BM, true>(a, b, s, o0, o1);
+    else
+        fwd_sweep<OFF, BM, false>(a, b, s, o0, o1);
 }
 
 // ---------------------------------------------------------------- adjoint
@@ -305,16 +377,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_fwd(F32Args a, int 
 // stored.  BM is the border rule: under REPLICATE and REFLECT101 the padded
 // rows and columns -2, -1, H, H+1 (W, W+1) fold back onto the pixels that
 // stood in for them; under ZERO and VALID they are dropped.
-template <int OFF, int BM>
-__global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_bwd(F32Args a, int nstrip, int nchunk)
+template <int OFF, int BM, bool IN>
+__device__ __forceinline__ void bwd_sweep(const F32Args &a, int b, int s, int X0, int X1)
 {
-    const int wave = blockIdx.x * kWavesPerGroup + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int per_img = nstrip * nchunk;
-    if (wave >= a.B * per_img) return;
-    const int b = wave / per_img, rem = wave % per_img;
-    const int s = rem % nstrip, k = rem / nstrip;
-    const int X0 = (int)((int64_t)k * a.H / nchunk), X1 = (int)((int64_t)(k + 1) * a.H / nchunk);
-    if (X1 <= X0) return;
     const int lane = threadIdx.x & 63;
     const int c = s * kOwnB - kHaloB + 2 * lane;             // input column of element a
     // replicate: fold the padded columns -2, -1 onto 0 and W, W+1 onto W-1;
@@ -337,66 +402,41 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_bwd(F32Args a, int 
         else
             khi = min(khi, max(0, a.W - 3));
     }
-    const bool keep_a = c >= klo && c < khi, keep_b = c + 1 >= klo && c + 1 < khi;
+    const bool keep_a = c >= klo && c < khi, keep_b = IN ? keep_a : c + 1 >= klo && c + 1 < khi;
     // an output pixel is centred on the column
-    const bool oc_a = c - OFF >= 0 && c - OFF < a.Wo, oc_b = c + 1 - OFF >= 0 && c + 1 - OFF < a.Wo;
-    const int64_t xa = (int64_t)edge_index<BM>(c, a.W) * 4, xb = (int64_t)edge_index<BM>(c + 1, a.W) * 4;
-    const bool ina = c >= 0 && c < a.W, inb = c + 1 >= 0 && c + 1 < a.W;   // (ZERO)
-    const int64_t ga = (int64_t)clampi(c - OFF, 0, a.Wo - 1) * 4, gb = (int64_t)clampi(c + 1 - OFF, 0, a.Wo - 1) * 4;
-    const char *src = reinterpret_cast<const char *>(a.src) + (int64_t)b * a.src_bstride;
-    const char *gr = reinterpret_cast<const char *>(a.grad) + (int64_t)b * a.g_bstride;
-    char *dst = reinterpret_cast<char *>(a.out) + (int64_t)b * a.out_bstride + (int64_t)(c < 0 ? 0 : c) * 4;
+    const bool oc_a = IN || (c - OFF >= 0 && c - OFF < a.Wo), oc_b = IN || (c + 1 - OFF >= 0 && c + 1 - OFF < a.Wo);
+    uint32_t xa = (uint32_t)edge_index<BM>(c, a.W) * 4u, xb = (uint32_t)edge_index<BM>(c + 1, a.W) * 4u;
+    const bool ina = IN || (c >= 0 && c < a.W), inb = IN || (c + 1 >= 0 && c + 1 < a.W);   // (ZERO)
+    uint32_t ga = (uint32_t)clampi(c - OFF, 0, a.Wo - 1) * 4u, gb = (uint32_t)clampi(c + 1 - OFF, 0, a.Wo - 1) * 4u;
+    const gout dst = (gout)a.out + (int64_t)b * a.out_bstride;
+    uint32_t oa = (uint32_t)max(c, 0) * 4u;
     const int c0 = s * kOwnB - kHaloB;                        // column of lane 0's element a
-    // both kept columns stored with one 8-byte store (c is even)
-    const bool vst = keep_a && keep_b && c >= 0 &&
-                     ((reinterpret_cast<uintptr_t>(a.out) | (uintptr_t)a.out_pitch | (uintptr_t)a.out_bstride) & 7u) == 0;
     // input rows X0-4 .. X1+3 give the adjoint rows [X0, X1); at the top and
     // bottom of the image, where padded rows fold back, two more rows on
     // that side give the padded rows -2, -1 and H, H+1
     const int r0 = X0 - ((kFold && X0 == 0) ? 6 : 4);
     const int T = X1 + ((kFold && X1 == a.H) ? 6 : 4) - r0;
 
-    auto ldx = [&](int t) {
-        const int r = r0 + t;
-        const char *row = src + (int64_t)edge_index<BM>(r, a.H) * a.src_pitch;
-        // two 4-byte loads at the lane's border-mapped columns (inside the
-        // image xb = xa + 4).  An 8-byte load for waves whose pairs all lie
-        // inside took the same VALU count or more: behind the wave-uniform
-        // choice the compiler computed both addresses and selected between
-        // them on every row (adjoint interior loop: 1074 against 946 VALU
-        // instructions per 5 rows).
-        F2 v{*reinterpret_cast<const float *>(row + xa), *reinterpret_cast<const float *>(row + xb)};
-        if constexpr (BM == kZero) {
-            const bool rin = r >= 0 && r < a.H;
-            v = F2{rin && ina ? v.a : 0.f, rin && inb ? v.b : 0.f};
-        }
-        return v;
-    };
-    // grad of the output row whose centre is input row r0 + t - 2 (0 outside;
-    // ga, gb are clamped columns, masked where no output pixel is centred)
-    auto ldg = [&](int t) {
-        const int o = r0 + t - 2 - OFF;
-        F2 v{0.f, 0.f};
-        if (o >= 0 && o < a.Ho) {
-            const char *row = gr + (int64_t)o * a.g_pitch;
-            v = F2{*reinterpret_cast<const float *>(row + ga), *reinterpret_cast<const float *>(row + gb)};
-        }
-        return F2{oc_a ? v.a : 0.f, oc_b ? v.b : 0.f};
-    };
+    // input rows, and the gradient rows centred two rows above them (a row
+    // outside the gradient is read as the nearest one and masked below)
+    RowWalk<BM> src((gin)a.src + (int64_t)b * a.src_bstride, a.src_pitch, r0, a.H, T);
+    RowWalk<kClamp> gr((gin)a.grad + (int64_t)b * a.g_bstride, a.g_pitch, r0 - 2 - OFF, a.Ho, T);
 
     // rings (slot = step mod 5): input rows, their row filters, and the
     // centre-row planes -w_x, -w_m, -w_y, -w_p
     F2 X[5], HR[5], HS[5], WX[5], WM[5], WY[5], WP[5];
     F2 pfx[5], pfg[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i)
-        X[i] = HR[i] = HS[i] = WX[i] = WM[i] = WY[i] = WP[i] = pfx[i] = pfg[i] = F2{0.f, 0.f};
     constexpr int PD = 3;   // rows loaded ahead (measured: 2 is 9% slower, 4 no faster)
-    // prologue loads in row order (the loop's first steps consume them)
+    auto load = [&](int slot) __attribute__((always_inline)) {
+        pfx[slot] = load_pair<IN>(src.p, xa, xb);
+        src.next();
+        pfg[slot] = load_pair<IN>(gr.p, ga, gb);
+        gr.next();
+    };
+    // prologue loads in row order (the first steps consume them)
 #pragma unroll
     for (int t = 0; t < PD; ++t) {
-        pfx[t] = ldx(t);
-        pfg[t] = ldg(t);
+        load(t);
         __builtin_amdgcn_sched_barrier(0);
     }
     // replicate: sums of the padded rows above row 0 / from row H-1 down;
@@ -442,43 +482,62 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_bwd(F32Args a, int 
                 }
             }
         }
-        float *p = reinterpret_cast<float *>(dst + (int64_t)row * a.out_pitch);
-        if (vst) {
-            *reinterpret_cast<float2 *>(p) = float2{v.a, v.b};
-        } else {
-            if (keep_a) p[0] = v.a;
-            if (keep_b) p[1] = v.b;
-        }
+        asm volatile("" : "+v"(v.a), "+v"(v.b), "+v"(oa));   // (as in the forward)
+        gout p = dst + (int64_t)row * a.out_pitch;
+        asm volatile("" : "+s"(p));
+        store_pair(p + oa, v, keep_a, keep_b);
     };
 
-    // INTERIOR: a row of P that is one of the wave's own rows and no padded
-    // row folds onto (rows 3 .. H-4 under a folding rule): stored as is.
-    auto step = [&](int t, auto phase, auto interior) __attribute__((always_inline)) {
+    // Step t: the row's filters (all steps), the weighted planes of centre row
+    // t - 2 (from step 4 on, when five rows are there), the row of P (from
+    // step 8 on, when five rows of planes are).  INTERIOR: a row of P that is
+    // one of the wave's own rows, that no padded row folds onto (rows 3 ..
+    // H-4 under a folding rule), and whose centre row is inside the gradient:
+    // stored as is.
+    auto enter = [&](int t, auto phase) __attribute__((always_inline)) {
         constexpr int p = decltype(phase)::value;
-        constexpr bool INTERIOR = decltype(interior)::value;
+        load((p + PD) % 5);
+        F2 x = pfx[p];
+        if constexpr (BM == kZero) {
+            const bool rin = r0 + t >= 0 && r0 + t < a.H;
+            x = F2{rin && ina ? x.a : 0.f, rin && inb ? x.b : 0.f};
+        }
+        X[p] = x;
+        hfilters(x, HR[p], HS[p]);
+    };
+    auto planes = [&](int t, auto phase, auto interior) __attribute__((always_inline)) {
+        constexpr int p = decltype(phase)::value;
         // input rows t-4 .. t live in slots (p+1)%5 .. p
         constexpr int s0 = (p + 1) % 5, s1 = (p + 2) % 5, s2 = (p + 3) % 5, s3 = (p + 4) % 5, s4 = p;
-        pfx[(p + PD) % 5] = ldx(min(t + PD, T - 1));
-        pfg[(p + PD) % 5] = ldg(min(t + PD, T - 1));
-        const F2 x = pfx[p];
-        X[s4] = x;
-        hfilters(x, HR[s4], HS[s4]);
+        enter(t, phase);
         // centre row q = r - 2 (slot s2 of the input rings)
         const F2 Gx = comb_c(HR[s0], HR[s1], HR[s2], HR[s3], HR[s4]);
-        const F2 Gm = comb_cd(HR[s0], HR[s1], HR[s2], HR[s3], HR[s4], HS[s0], HS[s2], HS[s4]);
+        const F2 Hm = comb_cd(HR[s0], HR[s1], HR[s2], HR[s3], HR[s4], HS[s0], HS[s2], HS[s4]);
         const F2 vs = X[s3] - X[s1];
         const F2 vr = (X[s4] - X[s0]) + 2.0f * vs;
-        F2 Gy, Gp;
-        hcombine(vr, vs, Gy, Gp);
-        const F2 gq = pfg[p];                    // grad of the output row centred on q
+        F2 Gy, Hp;
+        hcombine(vr, vs, Gy, Hp);
+        F2 gq = pfg[p];                    // grad of the output row centred on q
+        if constexpr (!decltype(interior)::value) {
+            const int o = r0 + t - 2 - OFF;
+            const bool oin = o >= 0 && o < a.Ho;
+            gq = F2{oin && oc_a ? gq.a : 0.f, oin && oc_b ? gq.b : 0.f};
+        } else if constexpr (!IN) {
+            gq = F2{oc_a ? gq.a : 0.f, oc_b ? gq.b : 0.f};
+        }
         // the planes enter negated, so the sums below are P itself
-        const F2 sc{-scale_of(gq.a, sum_sq(Gx.a, Gy.a, Gp.a, Gm.a)), -scale_of(gq.b, sum_sq(Gx.b, Gy.b, Gp.b, Gm.b))};
-        const F2 hsc = 0.5f * sc;
+        const F2 sc = scale_of(F2{-gq.a, -gq.b}, F2{sum_sq(Gx.a, Gy.a, Hp.a, Hm.a), sum_sq(Gx.b, Gy.b, Hp.b, Hm.b)});
         // w rings hold centre rows q-4 .. q in slots (p+1)%5 .. p as well
         WX[s4] = F2{sc.a * Gx.a, sc.b * Gx.b};
         WY[s4] = F2{sc.a * Gy.a, sc.b * Gy.b};
-        WP[s4] = F2{hsc.a * Gp.a, hsc.b * Gp.b};
-        WM[s4] = F2{hsc.a * Gm.a, hsc.b * Gm.b};
+        WP[s4] = F2{sc.a * Hp.a, sc.b * Hp.b};   // dM/dGd+- = Gd+- / (2 M)
+        WM[s4] = F2{sc.a * Hm.a, sc.b * Hm.b};
+    };
+    auto step = [&](int t, auto phase, auto interior) __attribute__((always_inline)) {
+        constexpr int p = decltype(phase)::value;
+        constexpr bool INTERIOR = decltype(interior)::value;
+        constexpr int s0 = (p + 1) % 5, s1 = (p + 2) % 5, s2 = (p + 3) % 5, s3 = (p + 4) % 5, s4 = p;
+        planes(t, phase, interior);
         // padded adjoint row p_ = q - 2 (slot s2 of the w rings).  Each term
         // K = u_v (x) u_h is applied down the columns first:
         //   V1 = c_v(w_x) + c'_v(w_m)  (row filter r),   V2 = d_v(w_m)  (-s),
@@ -488,21 +547,22 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_bwd(F32Args a, int 
         // Q_dx = r[dx] V1 - s[dx] V2 + c[dx] V3 + c'[dx] V4 - d[dx] V5.
         const F2 e04m = WM[s0] + WM[s4];
         const F2 V1 = comb_c(WX[s0], WX[s1], WX[s2], WX[s3], WX[s4]) +
-                      (6.0f * (e04m + (WM[s1] + WM[s3])) + 2.0f * WM[s2]);
+                      2.0f * (3.0f * (e04m + (WM[s1] + WM[s3])) + WM[s2]);
         const F2 V2 = 10.0f * e04m - 12.0f * WM[s2];
         const F2 V3 = (WY[s4] - WY[s0]) + 2.0f * (WY[s3] - WY[s1]);
         const F2 V5 = WP[s3] - WP[s1];
         const F2 V4 = (WP[s4] - WP[s0]) + 2.0f * V5;
         // Q_+-2 = E +- V1, Q_+-1 = F +- O, Q_0
-        const F2 E = V3 + 6.0f * V4 - 10.0f * V5;
-        const F2 Fq = 4.0f * V3 + 6.0f * V4;
+        const F2 V46 = 6.0f * V4;
+        const F2 E = V3 + V46 - 10.0f * V5;
+        const F2 Fq = 4.0f * V3 + V46;
         const F2 O = 2.0f * V1 - V2;
         const F2 Qm2 = E - V1, Qp2 = E + V1, Qm1 = Fq - O, Qp1 = Fq + O;
-        const F2 Q0 = 6.0f * V3 + 2.0f * V4 + 12.0f * V5;
+        const F2 Q0h = 3.0f * V3 + V4 + 6.0f * V5;   // Q_0 / 2
         // column a takes Q_-2, Q_-1 from the left lane's a, b, Q_+1 from its
         // own b and Q_+2 from the right lane's a; column b likewise
-        const F2 P{(Q0.a + Qp1.b) + from_left(Qm2.a + Qm1.b) + from_right(Qp2.a),
-                   (Qm1.a + Q0.b) + from_left(Qm2.b) + from_right(Qp1.a + Qp2.b)};
+        const F2 P{(2.0f * Q0h.a + Qp1.b) + from_left(Qm2.a + Qm1.b) + from_right(Qp2.a),
+                   (2.0f * Q0h.b + Qm1.a) + from_left(Qm2.b) + from_right(Qp1.a + Qp2.b)};
         const int pr = r0 + t - 4;               // padded row of P
         if constexpr (INTERIOR) {
             store(pr, P);
@@ -567,20 +627,27 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_bwd(F32Args a, int 
                 store(pr, v);
         }
     };
-    // steps whose P row is interior, [ta, tb) with ta a multiple of five
-    // (the ring phase stays t % 5), run without the row checks; the others
-    // take the general step
-    const int plo = kFold ? max(X0, 3) : X0, phi = kFold ? min(X1, a.H - 3) : X1;
-    int ta = min(T, (plo - r0 + 4 + 4) / 5 * 5);
-    const int tb = max(ta, phi - r0 + 4);
     using Gen = std::false_type;
     using Int = std::true_type;
     auto gen = [&](int t, auto ph) __attribute__((always_inline)) { step(t, ph, Gen{}); };
     auto mid = [&](int t, auto ph) __attribute__((always_inline)) { step(t, ph, Int{}); };
-    run_steps_from(0, ta, gen);
-    const int tm = ta + (tb - ta) / 5 * 5;
-    run_steps_from(ta, tm, mid);
-    run_steps_from(tm, T, gen);
+    enter(0, Ph<0>{});
+    enter(1, Ph<1>{});
+    enter(2, Ph<2>{});
+    enter(3, Ph<3>{});
+    planes(4, Ph<4>{}, Gen{});
+    planes(5, Ph<0>{}, Gen{});
+    planes(6, Ph<1>{}, Gen{});
+    planes(7, Ph<2>{}, Gen{});
+    // steps whose P row is interior, [ta, tb) with ta = 3 mod 5 as step 8, run
+    // without the row checks; the others take the general step.  (Step t
+    // finishes P of row r0 + t - 4.)
+    const int plo = kFold ? max(X0, 3) : X0, phi = kFold ? min(X1, a.H - 3) : min(X1, a.Ho + OFF - 2);
+    const int ta = min(T, 8 + max(0, (plo - r0 + 4 - 8 + 4) / 5 * 5));
+    const int tm = ta + max(0, phi - r0 + 4 - ta) / 5 * 5;
+    run_steps<3>(8, ta, gen);
+    run_steps<3>(ta, tm, mid);
+    run_steps<3>(tm, T, gen);
     if constexpr (kFold && BM == kRefl) {
         if (X1 == a.H) {                           // the held rows, with H and H+1 added
             if (a.H - 3 >= X0) store(a.H - 3, hold0);
@@ -588,6 +655,25 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_bwd(F32Args a, int 
             store(a.H - 1, hold2);
         }
     }
+}
+
+// IN: every column the wave loads, of the input and of the gradient, lies
+// inside, and no padded column folds onto its own.
+template <int OFF, int BM>
+__global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_bwd(F32Args a, int nstrip, int nchunk)
+{
+    const int wave = blockIdx.x * kWavesPerGroup + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int per_img = nstrip * nchunk;
+    if (wave >= a.B * per_img) return;
+    const int b = wave / per_img, rem = wave % per_img;
+    const int s = rem % nstrip, k = rem / nstrip;
+    const int X0 = (int)((int64_t)k * a.H / nchunk), X1 = (int)((int64_t)(k + 1) * a.H / nchunk);
+    if (X1 <= X0) return;
+    const int c0 = s * kOwnB - kHaloB;
+    if (c0 >= OFF && c0 + 128 <= a.Wo + OFF && c0 + 128 <= a.W - 3)
+        bwd_sweep<OFF, BM, true>(a, b, s, X0, X1);
+    else
+        bwd_sweep<OFF, BM, false>(a, b, s, X0, X1);
 }
 
 // Resident waves of a kernel (cached per kernel).
@@ -608,16 +694,21 @@ int resident_f32(const void *fn)
     return w;
 }
 
-// Row chunks per strip so that the grid fills at most one round of resident
-// waves (rounding up would leave a few waves to run as a second, nearly
-// empty round), with at least 32 rows per chunk: the pipeline costs 4
-// (forward) or 12 (adjoint) extra row steps per chunk.
-int chunks_for(const void *fn, int64_t strips, int rows)
+// Row chunks per strip: as many as fill one round of resident waves (rounding
+// up would leave a few waves to run as a second, nearly empty round), of at
+// least 4 rows, though a chunk costs 4 (forward) or 8 (adjoint) warm-up rows:
+// small batches are bound by the serial steps of a wave (forward + adjoint of
+// 1 x 256^2: 10.5 us at 4 rows, 31.5 at 32; 8 x 512^2 23.7 and 33.7).  `most`
+// rows at most: the forward of a large batch, which is bound by memory, runs
+// several rounds that follow each other through the image (32 x 1024^2: 59.5
+// us at 16 rows, 67.0 in one round of 36); the adjoint, bound by its
+// arithmetic, does not (one round of 73 rows 105 us, 32 rows 107, 16 rows 113).
+int chunks_for(const void *fn, int64_t strips, int rows, int most)
 {
     int slots = resident_f32(fn);
     if (slots <= 0) slots = 4096;
-    int64_t n = slots / strips;
-    n = std::max<int64_t>(1, std::min<int64_t>(n, rows / 32));
+    int64_t n = std::max<int64_t>(slots / strips, rows / most);
+    n = std::max<int64_t>(1, std::min<int64_t>(n, rows / 4));
     return (int)n;
 }
 
@@ -631,7 +722,7 @@ hipError_t launch_f32_fwd(const F32Args &a, hipStream_t st)
                    : a.bmode == 2 ? reinterpret_cast<const void *>(&k_f32_fwd<0, kRefl>)
                                   : reinterpret_cast<const void *>(&k_f32_fwd<0, kClamp>);
     int nstrip = (a.Wo + kOwnF - 1) / kOwnF;
-    int nchunk = chunks_for(fn, (int64_t)a.B * nstrip, a.Ho);
+    int nchunk = chunks_for(fn, (int64_t)a.B * nstrip, a.Ho, 16);
     const int64_t waves = (int64_t)a.B * nstrip * nchunk;
     const int grid = (int)((waves + kWavesPerGroup - 1) / kWavesPerGroup);
     F32Args aa = a;
@@ -647,7 +738,7 @@ hipError_t launch_f32_bwd(const F32Args &a, hipStream_t st)
                    : a.bmode == 2 ? reinterpret_cast<const void *>(&k_f32_bwd<0, kRefl>)
                                   : reinterpret_cast<const void *>(&k_f32_bwd<0, kClamp>);
     int nstrip = (a.W + kOwnB - 1) / kOwnB;
-    int nchunk = chunks_for(fn, (int64_t)a.B * nstrip, a.H);
+    int nchunk = chunks_for(fn, (int64_t)a.B * nstrip, a.H, 1 << 30);
     const int64_t waves = (int64_t)a.B * nstrip * nchunk;
     const int grid = (int)((waves + kWavesPerGroup - 1) / kWavesPerGroup);
     F32Args aa = a;
