@@ -252,11 +252,12 @@ int sobel4x5_debug_plan_claims(sobel4x5_plan plan, uint32_t *claims, int64_t cap
  * make sure no launch of it is still running. */
 int sobel4x5_plan_destroy(sobel4x5_plan plan);
 
-/* One-shot batched call: builds (or reuses a cached) plan for these images
- * and launches it on `stream`.  Equivalent to plan_create + plan_launch.
- * The cache (8 plans, least recently used first out) is keyed by every
- * descriptor field, the border, the device and the stream; evicting a plan
- * waits for its stream. */
+/* One-shot batched call on `stream`, with the results of plan_create +
+ * plan_launch.  Up to 48 images travel in the kernel's arguments: the call
+ * allocates, uploads and keeps nothing, and works under graph capture.  A
+ * larger batch builds a plan or reuses a cached one; the cache (8 plans,
+ * least recently used first out) is keyed by every descriptor field, the
+ * border, the device and the stream; evicting a plan waits for its stream. */
 int sobel4x5_batched(const sobel4x5_image *imgs, int32_t count, int32_t border, void *stream);
 
 /* Host-only argument check of a batch (never touches the GPU). */

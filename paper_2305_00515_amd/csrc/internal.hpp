@@ -94,6 +94,10 @@ hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, 
 // job asks for directional planes.  `claims` (device, `total` counters, or
 // null): each wave-tile's counter gains one for every wave that takes it.
 // `past`: outputs are stored past the L2 (OutputStores).
+// tiles == nullptr: `jobs` is a HOST array of `total` <= kBatchArgs images,
+// magnitudes only, tiled for bands of s.th rows; they go into the kernel's
+// arguments (`queue`, `grid` and `claims` are not looked at).
+constexpr int32_t kBatchArgs = 48;
 hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border,
                              bool past, bool dir, const U8Shape &s, int grid, hipStream_t stream,
                              uint32_t *claims = nullptr);

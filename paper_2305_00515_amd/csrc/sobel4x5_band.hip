@@ -149,9 +149,27 @@ void batched_tiles(const U8Job &j, int32_t img, int th, int, std::vector<int4> &
 }
 
 hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border, bool past,
-                             bool dir, const U8Shape &, int grid, hipStream_t st, uint32_t *claims)
+                             bool dir, const U8Shape &s, int grid, hipStream_t st, uint32_t *claims)
 {
     int off = border == 1 ? 2 : 0, bm = border_mode(border);
+    if (!tiles) {
+        BandImages b;
+        int64_t waves = 0;
+        for (int32_t i = 0; i < 64; ++i) {
+            b.first[i] = i < total ? (u32)waves : 0xffffffffu;
+            if (i >= total) continue;
+            const U8Job &j = jobs[i];
+            b.img[i] = BandImage{j.src, j.mag, j.src_pitch, j.mag_pitch, j.W, j.H, j.nt, j.inv_nt,
+                                 (u32)(j.nt * batched_bands(j, s.th))};
+            waves += batched_count(j, s.th);
+        }
+        u32 w = (u32)waves;
+        int bq = s.th / 4;
+        void *args[] = {(void *)&b, const_cast<BandTaps *>(&kTaps4x5), (void *)&w, (void *)&bq, (void *)&off, (void *)&bm};
+        const void *fn = past ? reinterpret_cast<const void *>(&k_band_args<true>)
+                              : reinterpret_cast<const void *>(&k_band_args<false>);
+        return hipLaunchKernel(fn, dim3((w + kBandWaves - 1) / kBandWaves), dim3(64 * kBandWaves), args, 0, st);
+    }
     void *args[] = {(void *)&jobs, (void *)&tiles, (void *)&total, (void *)&queue, (void *)&claims,
                     const_cast<BandTaps *>(&kTaps4x5), (void *)&off, (void *)&bm};
     return hipLaunchKernel(batched_fn(dir, past), dim3(grid), dim3(64 * kBandWaves), args, 0, st);

@@ -613,5 +613,44 @@ __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu
     }
 }
 
+// A small batch of magnitudes in the kernel's arguments: no table to upload, to
+// keep or to wait for.  Wave w of the grid belongs to the last image whose
+// first wave is not beyond it.
+struct BandImage {
+    const uint8_t *src;
+    uint8_t *mag;
+    int64_t src_pitch, mag_pitch;
+    int32_t W, H;
+    u32 nt, inv_nt, tiles;
+};
+struct BandImages {
+    BandImage img[kBatchArgs];
+    u32 first[64];      // first wave of each image, ~0 beyond the last one
+};
+
+template <bool PAST>
+__global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_band_args(
+    const BandImages B, const BandTaps T, u32 waves, int bq, int off, int bm)
+{
+    const u32 w = band_workgroup(blockIdx.x, gridDim.x) * kBandWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u64 at = __builtin_amdgcn_ballot_w64(B.first[threadIdx.x & 63] <= w);
+    const int i = __builtin_popcountll(at) - 1;   // first[0] is 0
+    const BandImage &I = B.img[i];
+    U8Job J{};
+    J.src = I.src;
+    J.mag = I.mag;
+    J.src_pitch = I.src_pitch;
+    J.mag_pitch = I.mag_pitch;
+    J.W = I.W;
+    J.H = I.H;
+    J.Wo = I.W - 2 * off;
+    J.Ho = I.H - 2 * off;
+    J.nt = I.nt;
+    J.inv_nt = I.inv_nt;
+    const BandTile t = band_tile<4>(J, min(16 * (w - B.first[i]) + (threadIdx.x & 15), I.tiles - 1), bq);
+    if (w >= waves) return;
+    band_run<4, 4, false, 0, PAST>(J, t, off, bm, T);
+}
+
 }  // namespace
 }  // namespace s4x5

@@ -146,3 +146,31 @@ def test_batches(oracle_mod, sobel_lib, gpu, sizes, planes):
                 ref = om if plane == 0 else od[plane - 1]
                 assert np.array_equal(t.cpu().numpy(), ref), (sizes[i], border, k)
         plan.close()
+
+
+@pytest.mark.parametrize("count", [1, 2, 47, 48, 49, 63])
+def test_one_shot_batches_of_any_count(oracle_mod, sobel_lib, gpu, count):
+    """Up to 48 images travel in the kernel's arguments, more through a plan:
+    the same results on both sides of the line, call after call with other
+    buffers, also captured into a graph (up to 48)."""
+    rng = np.random.default_rng(count)
+    sizes = [(int(h), int(w)) for h, w in rng.integers(1, 90, (count, 2))]
+    for rep in range(2):
+        imgs = [synth.rect_image(h, w, 100 * rep + h + w) % 6 for h, w in sizes]
+        srcs = [torch.from_numpy(m).to(gpu) for m in imgs]
+        border = 3 * rep
+        mags = sobel_lib.sobel4x5_batched(srcs, border=border)
+        torch.cuda.synchronize()
+        for m, t in zip(imgs, mags):
+            assert np.array_equal(t.cpu().numpy(), oracle_mod.sobel_u8(m, border, want_dir=False)[0]), m.shape
+    if count <= 48:
+        out = [torch.empty_like(s) for s in srcs]
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            sobel_lib.sobel4x5_batched(srcs, out, border=border)
+        for _ in range(3):
+            for t in out:
+                t.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(out, mags))
