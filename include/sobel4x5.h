@@ -184,8 +184,7 @@ int sobel4x5_family_weights(int32_t a, int32_t ab, int32_t an, int32_t am, int32
                             int32_t *weights_out);
 
 /*
- * Batched uint8 magnitudes: many images of uneven sizes in ONE launch of a
- * persistent work-queue kernel (not in the paper; it applies the same integer
+ * Batched uint8 magnitudes: many images of uneven sizes in ONE launch (not in the paper; it applies the same integer
  * arithmetic per image).
  *   sobel4x5_image : host descriptor; src/mag device pointers, pitches in bytes.
  */
@@ -202,7 +201,8 @@ typedef struct sobel4x5_plan_s *sobel4x5_plan;
 
 #define SOBEL4X5_PLAN_AUTOTUNE 1u  /* time candidate tile shapes, keep the fastest
                                       that is bit-exact against the default   */
-#define SOBEL4X5_PLAN_NO_GRAPH 2u  /* launch the kernel directly, no hipGraph */
+#define SOBEL4X5_PLAN_NO_GRAPH 2u  /* no hipGraph for a plan with a work queue
+                                      (one with a static grid never has one)  */
 
 /*
  * sobel4x5_plan_create -- build a reusable plan for a fixed set of images.
@@ -213,14 +213,17 @@ typedef struct sobel4x5_plan_s *sobel4x5_plan;
  * Allocates device memory for the tile table and queue counters (ENOMEM on
  * failure), uploads them, selects the tile shape (autotuned with
  * SOBEL4X5_PLAN_AUTOTUNE, which runs and synchronises the device), and
- * captures the launch in a hipGraph.  The images' contents are not read here
- * except during autotuning, which writes the mag buffers.
+ * captures the launch in a hipGraph if that shape takes its tiles from a work
+ * queue (only autotuning can choose such a one).  The images' contents are
+ * not read here except during autotuning, which writes the mag buffers.
  */
 int sobel4x5_plan_create(const sobel4x5_image *imgs, int32_t count, int32_t border,
                          uint32_t flags, sobel4x5_plan *out);
 
-/* Enqueue the plan's work on `stream` (graph launch).  The queue counters
- * reset themselves at the end of every launch, so launches can repeat. */
+/* Enqueue the plan's work on `stream`: its kernel, or the graph of a plan with
+ * a work queue.  A plan without a graph can be launched under graph capture;
+ * it must then outlive the captured graph.  The queue counters reset
+ * themselves at the end of every launch, so launches can repeat. */
 int sobel4x5_plan_launch(sobel4x5_plan plan, void *stream);
 
 /* Tile shape the plan uses: pixels per lane, rows per tile, waves per

@@ -365,11 +365,16 @@ int plan_setup(sobel4x5_plan_s *p, const U8Shape &shape)
     return ok();
 }
 
-int plan_direct_launch(sobel4x5_plan_s *p, hipStream_t st, uint32_t *claims = nullptr)
+hipError_t plan_kernel(sobel4x5_plan_s *p, hipStream_t st, uint32_t *claims)
 {
     uint32_t *queue = p->shape.waves == kStaticGrid ? nullptr : p->d_queue;
-    hipError_t e = launch_u8_batched(p->d_jobs, p->d_tiles, p->total, queue, p->border, p->stores.past_l2(), p->dir,
-                                     p->shape, p->grid, st, claims);
+    return launch_u8_batched(p->d_jobs, p->d_tiles, p->total, queue, p->border, p->stores.past_l2(), p->dir, p->shape,
+                             p->grid, st, claims);
+}
+
+int plan_direct_launch(sobel4x5_plan_s *p, hipStream_t st, uint32_t *claims = nullptr)
+{
+    hipError_t e = plan_kernel(p, st, claims);
     return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
 }
 
@@ -854,6 +859,12 @@ int sobel4x5_plan_create_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *
     }
     hipGetDevice(&p->device);
     int rc = (flags & SOBEL4X5_PLAN_AUTOTUNE) ? plan_autotune(p) : plan_setup(p, batch_default_shape(p->stores));
+    // A static grid is one kernel without state, and the plan launches it as
+    // such: 16 images of 64..640 cost the caller 5.5 us a launch, 18.6 when
+    // waited for, where a captured graph of it cost 13.2 and 35.9, and 140 us
+    // more to build.  A plan with a work queue keeps the graph: its launches
+    // share the queue words.
+    p->use_graph = p->use_graph && p->shape.waves != kStaticGrid;
     if (rc == SOBEL4X5_OK && p->use_graph) rc = plan_capture(p);
     if (rc != SOBEL4X5_OK) {
         plan_free_device(p);
@@ -879,7 +890,14 @@ int sobel4x5_plan_launch(sobel4x5_plan plan, void *stream)
         hipError_t e = guard(hipGraphLaunch(plan->exec, st));
         return e == hipSuccess ? ok() : hip_fail(e, "hipGraphLaunch");
     }
-    return plan_direct_launch(plan, st);
+    // The stream may belong to the plan's device while another is current.
+    int dev = plan->device;
+    hipGetDevice(&dev);
+    const bool other = st && dev != plan->device;
+    if (other) hipSetDevice(plan->device);
+    hipError_t e = guard(plan_kernel(plan, st, nullptr));
+    if (other) hipSetDevice(dev);
+    return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
 }
 
 int sobel4x5_debug_plan_claims(sobel4x5_plan plan, uint32_t *claims, int64_t capacity, int64_t *ntiles, void *stream)
@@ -924,7 +942,7 @@ int sobel4x5_batched_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *outs
     hipStream_t st = static_cast<hipStream_t>(stream);
     // A few images' magnitudes: the images go into the kernel's arguments, and
     // the call keeps nothing.  (16 images of 64..640: 5 us a launch, where a
-    // plan's graph launch takes 14 and a new plan 250.)
+    // a plan's look-up and launch take 9 and a new plan 100.)
     if (!outs && count <= kBatchArgs) {
         U8Job jobs[kBatchArgs];
         OutputStores stores;

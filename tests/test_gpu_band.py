@@ -174,3 +174,21 @@ def test_one_shot_batches_of_any_count(oracle_mod, sobel_lib, gpu, count):
             g.replay()
             torch.cuda.synchronize()
             assert all(torch.equal(a, b) for a, b in zip(out, mags))
+
+
+def test_plan_launches_under_capture(oracle_mod, sobel_lib, gpu):
+    """A plan launches its kernel as such, so its launches can be captured."""
+    imgs = [synth.rect_image(h, w, h + w) for h, w in ((5, 9), (64, 300), (131, 77))]
+    srcs = [torch.from_numpy(m).to(gpu) for m in imgs]
+    mags = [torch.empty_like(s) for s in srcs]
+    plan = sobel_lib.Plan(srcs, mags)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.launch()
+    for _ in range(3):
+        for t in mags:
+            t.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for m, t in zip(imgs, mags):
+            assert np.array_equal(t.cpu().numpy(), oracle_mod.sobel_u8(m, 0, want_dir=False)[0]), m.shape
