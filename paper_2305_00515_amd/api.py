@@ -4,12 +4,17 @@ Argument marshalling only: every function checks tensor devices/dtypes,
 converts them to raw device pointers and byte pitches, and calls the library
 on torch's current HIP stream.  All arithmetic happens in the HIP kernels.
 The library is required: importing this module on a machine where it cannot
-be loaded raises, and there is no CPU fallback.
+be loaded raises, and there is no CPU fallback.  The calls that are shorter on
+the GPU than in the interpreter are marshalled by the compiled binding _bind
+where it is built; what it does not take, the code here handles and refuses.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import threading
+import weakref
+from collections import deque
 from pathlib import Path
 
 import numpy as np
@@ -106,13 +111,39 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+def _load_bind():
+    """(u8, batched) of the compiled binding, or two functions that take no
+    call where it has not been built."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not (_PKG / "_bind.so").exists():
+        return (lambda *a: None,) * 2
+    from . import _bind
+    fns = (lib.sobel4x5_u8, lib.sobel4x5_u8_op, lib.sobel4x5_u8_weighted, lib.sobel4x5_batched)
+    _bind.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in fns), raw)
+    return _bind.u8, _bind.batched
+
+
+# Each returns the call's result in a tuple, the library's status, or None for
+# a call that is not in the plain form that it takes: 512x512 magnitudes cost
+# their caller 10.7 us through ctypes and 4.6 through it, 16 crops 94 and 19.
+_bind_u8, _bind_batched = _load_bind()
+
+
 def _check(rc: int, where: str) -> None:
     if rc != OK:
         raise SobelError(rc, where, lib.sobel4x5_last_error().decode())
 
 
+def _raw_stream(index: int) -> int:
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# torch's own query without the Stream object around it (0.1 us for 2.0)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _raw_stream)
+
+
 def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return ctypes.c_void_p(_raw_stream(t.device.index))
 
 
 def _need_cuda(t: torch.Tensor, dtype, name: str) -> None:
@@ -178,6 +209,11 @@ def sobel4x5_u8(src: torch.Tensor, border: int = BORDER_REPLICATE, *, mag: torch
     Planes are 0 deg Gx, 45 deg Gd, 90 deg Gy, 135 deg Gdt as int16 (DIR_S16)
     or int32 (DIR_S32).  Output tensors may be passed in (any row pitch).
     """
+    r = _bind_u8(src, None, border, mag, want_mag, dir_type, dirs, None)
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        _check(r, "sobel4x5_u8")
     out, (h, w, pitch), res = _u8_outputs(src, border, mag, want_mag, dir_type, dirs)
     _check(lib.sobel4x5_u8(src.data_ptr(), w, h, pitch, border, ctypes.byref(out), _stream(src)),
            "sobel4x5_u8")
@@ -189,6 +225,11 @@ def sobel4x5_u8_op(src: torch.Tensor, op: int, border: int = BORDER_REPLICATE, *
                    dirs: list | None = None):
     """sobel4x5_u8 for operator `op` (OP_*): the two-directional operators
     return two planes [Gx, Gy]; the 3x3 pair's VALID output is (H-2, W-2)."""
+    r = _bind_u8(src, op, border, mag, want_mag, dir_type, dirs, None)
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        _check(r, "sobel4x5_u8_op")
     out, (h, w, pitch), res = _u8_outputs(src, border, mag, want_mag, dir_type, dirs, op)
     _check(lib.sobel4x5_u8_op(src.data_ptr(), w, h, pitch, op, border, ctypes.byref(out), _stream(src)),
            "sobel4x5_u8_op")
@@ -207,6 +248,11 @@ def sobel4x5_u8_weighted(src: torch.Tensor, weights, border: int = BORDER_REPLIC
                          dirs: list | None = None):
     """sobel4x5_u8 with run-time integer kernels (4, 5, 5), plane order as the
     default operator; each kernel antisymmetric under a half turn."""
+    r = _bind_u8(src, None, border, mag, want_mag, dir_type, dirs, weights)
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        _check(r, "sobel4x5_u8_weighted")
     wb = _weights_buf(weights)
     out, (h, w, pitch), res = _u8_outputs(src, border, mag, want_mag, dir_type, dirs)
     _check(lib.sobel4x5_u8_weighted(src.data_ptr(), w, h, pitch, border, wb.ctypes.data, ctypes.byref(out),
@@ -252,24 +298,75 @@ def _host_rows(a, name):
     return a.shape[0], a.shape[1], a.strides[0], a.ctypes.data
 
 
+class _PinnedOutputs:
+    """Page-locked output arrays of one Pipe.  The device copies straight into
+    them, where a new pageable array of 2 MB costs its page faults and a second
+    copy (8 images of 1080x1920: 1.85 ms a run into pageable arrays, 1.04 into
+    these).  A block comes back when its array, with every view of it, is
+    gone; blocks in use and idle together stay within LIMIT bytes, and beyond
+    that the arrays are ordinary ones.  The blocks go back to torch's pinned
+    allocator with the pool."""
+
+    LIMIT = 256 << 20
+
+    def __init__(self):
+        self._lock = threading.Lock()
+        self._idle = {}      # block size -> deque of idle blocks
+        self._bytes = 0      # of all blocks, in use and idle
+
+    def array(self, h, w):
+        block = self._take(h * w) if h > 0 and w > 0 else None
+        if block is None:
+            return np.empty((max(h, 0), max(w, 0)), np.uint8)
+        # Its base is the tensor, so numpy takes the array itself, and not the
+        # block, as the owner of every view made of it.
+        a = block[:h * w].view(h, w).numpy()
+        # A finalizer may run inside _take, on any thread: it takes no lock.
+        weakref.finalize(a, self._idle[block.numel()].append, block).atexit = False
+        return a
+
+    def _take(self, nbytes):
+        size = 1 << max(16, (nbytes - 1).bit_length())
+        with self._lock:
+            idle = self._idle.setdefault(size, deque())
+            try:
+                return idle.pop()
+            except IndexError:
+                pass
+            for other, blocks in self._idle.items():
+                while self._bytes + size > self.LIMIT and blocks:
+                    blocks.pop()
+                    self._bytes -= other
+            if self._bytes + size > self.LIMIT:
+                return None
+            try:
+                block = torch.empty(size, dtype=torch.uint8, pin_memory=True)
+            except RuntimeError:
+                return None
+            self._bytes += size
+            return block
+
+
 class Pipe:
     """Host-memory images -> host-memory magnitudes, with the copies to and
     from the device overlapped with the kernels across `depth` slots."""
 
     def __init__(self, max_width: int, max_height: int, depth: int = 3):
         self._h = ctypes.c_void_p()
+        self._outputs = _PinnedOutputs()
         _check(lib.sobel4x5_pipe_create(max_width, max_height, depth, ctypes.byref(self._h)), "sobel4x5_pipe_create")
 
     def run(self, srcs, mags=None, border: int = BORDER_REPLICATE):
         """srcs: uint8 host images (numpy arrays or CPU tensors, pinned or
-        not); mags: matching outputs or None (numpy arrays are allocated)."""
+        not); mags: matching outputs or None (numpy arrays are allocated, in
+        page-locked memory up to 256 MiB a Pipe)."""
         n = len(srcs)
         if mags is None:
             mags = []
             for m in srcs:
                 h, w = (m.shape[0], m.shape[1])
                 ho, wo = out_shape(h, w, border)
-                mags.append(np.empty((max(ho, 0), max(wo, 0)), np.uint8))
+                mags.append(self._outputs.array(ho, wo))
         if len(mags) != n:
             raise ValueError("srcs and mags differ in length")
         arr = (Image * max(n, 1))()
@@ -287,6 +384,7 @@ class Pipe:
         if self._h:
             lib.sobel4x5_pipe_destroy(self._h)
             self._h = ctypes.c_void_p()
+            self._outputs = _PinnedOutputs()
 
     def __del__(self):
         try:
@@ -413,6 +511,11 @@ def sobel4x5_batched(srcs, mags=None, border: int = BORDER_REPLICATE, *, want_ma
         imgs, outs, res = _images_ex(list(srcs), mags, border, want_mag, dir_type, dirs)
         _check(lib.sobel4x5_batched_ex(imgs, outs, len(imgs), border, _stream(srcs[0])), "sobel4x5_batched_ex")
         return res
+    r = _bind_batched(srcs, mags, border)
+    if r.__class__ is tuple:
+        return r[0]
+    if r is not None:
+        _check(r, "sobel4x5_batched")
     if mags is None:
         mags = []
         for s in srcs:

@@ -1,4 +1,5 @@
-"""Build the HIP library libsobel4x5.so in-tree for gfx950 (hipcc).
+"""Build the HIP library libsobel4x5.so in-tree for gfx950 (hipcc), and its
+CPython binding (host compiler).
 
 Usage: python -m paper_2305_00515_amd.build [--verbose]
 """
@@ -16,6 +17,7 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libsobel4x5.so"
+BIND = PKG / "_bind.so"      # CPython binding of the library's smallest calls
 ARCH = os.environ.get("SOBEL4X5_ARCH", "gfx950")
 
 SOURCES = ["sobel4x5_api.cpp", "sobel4x5_u8.hip", "sobel4x5_f32.hip",
@@ -60,8 +62,24 @@ def _run(cmd, verbose):
     return res.returncode
 
 
+def bind_command(out: Path):
+    """The host compiler's line for the CPython binding (torch's headers, no
+    GPU code; it reaches the library through addresses that api.py hands it)."""
+    import sysconfig
+    import torch
+    t = Path(torch.__file__).resolve().parent
+    cxx = os.environ.get("CXX") or shutil.which("g++") or hipcc()
+    return [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            "-isystem", str(t / "include"), "-isystem", str(t / "include" / "torch" / "csrc" / "api" / "include"),
+            "-I" + sysconfig.get_paths()["include"], "-I" + str(ROOT / "include"),
+            "-o", str(out), str(CSRC / "bind.cpp"),
+            "-L" + str(t / "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = False, out: Path | None = None, defines=()) -> Path:
-    """Compile every source into libsobel4x5.so (always recompiles).
+    """Compile every source into libsobel4x5.so, and the binding beside it
+    (always recompiles).
 
     The translation units compile in parallel into a scratch folder, then
     link.  ``out`` and ``defines`` (NAME=VALUE strings) build a variant
@@ -77,16 +95,24 @@ def build(verbose: bool = False, out: Path | None = None, defines=()) -> Path:
         for src in SOURCES:
             obj = objdir / (Path(src).stem + ".o")
             jobs.append((obj, [hipcc()] + compile_flags + dflags + ["-c", "-o", str(obj), str(CSRC / src)]))
+        objs = [str(o) for o, _ in jobs]
+        bind = objdir / BIND.name
+        if out == LIB:
+            jobs.append((bind, bind_command(bind)))
         workers = max(1, min(len(jobs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
         with ThreadPoolExecutor(max_workers=workers) as ex:
             codes = list(ex.map(lambda j: _run(j[1], verbose), jobs))
         if any(codes):
             raise RuntimeError("hipcc failed building libsobel4x5.so")
         tmp = out.with_suffix(".so.tmp%d" % os.getpid())
-        link = [hipcc(), "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", str(tmp)] + [str(o) for o, _ in jobs]
+        link = [hipcc(), "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", str(tmp)] + objs
         if _run(link, verbose):
             raise RuntimeError("linking libsobel4x5.so failed")
         os.replace(tmp, out)
+        if out == LIB:
+            tmp = BIND.with_suffix(".so.tmp%d" % os.getpid())
+            shutil.copyfile(bind, tmp)
+            os.replace(tmp, BIND)
     finally:
         shutil.rmtree(objdir, ignore_errors=True)
     return out

@@ -1,0 +1,135 @@
+"""The compiled binding against the general path, over the forms that both
+accept and those that neither does, and the pipe's page-locked outputs."""
+import gc
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2305_00515_amd import synth
+
+
+def general(api, monkeypatch):
+    monkeypatch.setattr(api, "_bind_u8", lambda *a: None)
+    monkeypatch.setattr(api, "_bind_batched", lambda *a: None)
+
+
+def outcome(fn):
+    """The call's result as plain arrays, or its error's type and words."""
+    try:
+        r = fn()
+    except Exception as e:
+        return type(e), str(e)
+    torch.cuda.synchronize()
+    flat = lambda v: [flat(x) for x in v] if isinstance(v, (list, tuple)) else None if v is None else v.cpu().numpy()
+    return flat(r)
+
+
+def same(a, b):
+    if isinstance(a, list):
+        return isinstance(b, list) and len(a) == len(b) and all(same(x, y) for x, y in zip(a, b))
+    if isinstance(a, np.ndarray):
+        return isinstance(b, np.ndarray) and a.dtype == b.dtype and np.array_equal(a, b)
+    return a == b
+
+
+def test_binding_leaves_other_forms_to_the_general_path(sobel_lib):
+    """Without a GPU tensor in the plain form it takes nothing and raises nothing."""
+    img = torch.zeros(8, 8, dtype=torch.uint8)
+    for src in (img, img.numpy(), 3, None, img.to_sparse(), img.float()):
+        assert sobel_lib._bind_u8(src, None, 0, None, True, 0, None, None) is None
+        assert sobel_lib._bind_batched([src], None, 0) is None
+    assert sobel_lib._bind_batched([], None, 0) is None
+
+
+@pytest.mark.gpu
+def test_binding_is_built_and_used(sobel_lib, gpu):
+    src = torch.zeros(8, 8, dtype=torch.uint8, device=gpu)
+    mag, dirs = sobel_lib._bind_u8(src, None, 0, None, True, 0, None, None)
+    assert mag.shape == (8, 8) and dirs is None
+    assert len(sobel_lib._bind_batched([src], None, 0)[0]) == 1
+    with torch.overrides.TorchFunctionMode():
+        assert sobel_lib._bind_u8(src, None, 0, None, True, 0, None, None) is None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", ["u8", "op1", "op2", "weighted"])
+def test_binding_matches_the_general_path(sobel_lib, gpu, monkeypatch, call):
+    api = sobel_lib
+    w64 = api.family_weights(1, 3, 5, 10, 15, 30).astype(np.int64)
+    big = w64.copy()
+    big[0, 0, 0] = 2 ** 31
+    img = torch.from_numpy(synth.rect_image(40, 72, 3)).to(gpu)
+    one = img[:1, :1]
+    srcs = [img, img[3:, 5:], img[:, ::2], img.t(), img[::2], img[None], img.to(torch.int16), img.cpu(), one, img[:3],
+            img[:0], img[:, :1], torch.nn.Parameter(img, requires_grad=False)]
+    kinds = [dict(), dict(border=1), dict(border=2), dict(border=3), dict(border=7), dict(border=True),
+             dict(want_mag=False), dict(dir_type=1), dict(dir_type=2, want_mag=False), dict(dir_type=3),
+             dict(dir_type=2, border=1), dict(border=0.0)]
+    planes = 2 if call.startswith("op") else 4
+    new = lambda h, w, t: torch.empty(h, w, dtype=t, device=gpu)
+    outs = [lambda h, w: dict(mag=new(h, w, torch.uint8)), lambda h, w: dict(mag=new(h, w + 3, torch.uint8)[:, 3:]),
+            lambda h, w: dict(mag=new(h, w + 1, torch.uint8)), lambda h, w: dict(mag=new(h, w, torch.int16)),
+            lambda h, w: dict(mag=new(h, w, torch.uint8), want_mag=False),
+            lambda h, w: dict(dir_type=1, dirs=[new(h, w, torch.int16) for _ in range(planes)]),
+            lambda h, w: dict(dir_type=1, dirs=tuple(new(h, w + 8, torch.int16)[:, 4:-4] for _ in range(planes))),
+            lambda h, w: dict(dir_type=1, dirs=[new(h, w + k, torch.int16)[:, k:] for k in range(planes)]),
+            lambda h, w: dict(dir_type=2, dirs=[new(h, w, torch.int16) for _ in range(planes)]),
+            lambda h, w: dict(dir_type=1, dirs=[new(h, w, torch.int16)])]
+
+    def run(src, weights, **kw):
+        if call == "u8":
+            return api.sobel4x5_u8(src, **kw)
+        if call == "weighted":
+            return api.sobel4x5_u8_weighted(src, weights, **kw)
+        return api.sobel4x5_u8_op(src, int(call[2]), **kw)
+
+    todo = [(s, w64, (lambda kw=kw: dict(kw))) for s in srcs for kw in kinds]
+    todo += [(s, w64, (lambda o=o, s=s: o(*s.shape))) for s in srcs[:2] for o in outs]
+    if call == "weighted":
+        todo += [(img, w, dict) for w in (w64.astype(np.int32), w64.reshape(100), w64.tolist(), big, w64[:3], -w64,
+                                          w64.astype(np.float64), np.asfortranarray(w64), w64.astype(">i4"),
+                                          w64.astype(np.uint32), w64.astype(np.int16))]
+    took = [outcome(lambda: run(s, w, **kw())) for s, w, kw in todo]
+    general(api, monkeypatch)
+    for (s, w, kw), got in zip(todo, took):
+        want = outcome(lambda: run(s, w, **kw()))
+        assert same(got, want), (tuple(s.shape), kw(), got, want)
+
+
+@pytest.mark.gpu
+def test_batched_binding_matches_the_general_path(sobel_lib, gpu, monkeypatch):
+    api = sobel_lib
+    imgs = [torch.from_numpy(synth.rect_image(h, w, h)).to(gpu) for h, w in ((9, 5), (40, 72), (17, 130))]
+    pad = [m[1:, 2:] for m in imgs]
+    todo = [(s, m, b) for s in (imgs, tuple(imgs), pad, iter(()), [], [imgs[0][:3]], [imgs[0].cpu()], [imgs[1][:, ::2]])
+            for b in (0, 1, 3, 9) for m in (None, [], [torch.empty_like(i) for i in imgs],
+                                            tuple(torch.empty_like(i) for i in imgs))]
+    run = lambda s, m, b: api.sobel4x5_batched(s, m, border=b)
+    took = [outcome(lambda: run(*t)) for t in todo]
+    general(api, monkeypatch)
+    for t, got in zip(todo, took):
+        assert same(got, outcome(lambda: run(*t))), (t[2], got)
+
+
+@pytest.mark.gpu
+def test_pipe_outputs_are_not_reused_while_viewed(oracle_mod, sobel_lib, gpu):
+    """A view keeps its block out of the pool; a dropped array gives it back;
+    beyond the limit the outputs are ordinary arrays."""
+    a, b = synth.rect_image(100, 333, 1), synth.rect_image(100, 333, 2)
+    want = oracle_mod.sobel_u8(a, 0, want_dir=False)[0]
+    pipe = sobel_lib.Pipe(333, 100)
+    pool = pipe._outputs
+    view = pipe.run([a])[0][10:, 3:].T
+    for _ in range(3):
+        pipe.run([b, b])
+    gc.collect()
+    assert np.array_equal(view, want[10:, 3:].T)
+    assert pool._bytes == 3 * (1 << 16)      # one viewed, two idle
+    pool.LIMIT = pool._bytes
+    mags = pipe.run([a] * 5)
+    assert all(np.array_equal(m, want) for m in mags) and pool._bytes <= pool.LIMIT
+    pipe.close()
+    gc.collect()
+    assert np.array_equal(view, want[10:, 3:].T) and all(np.array_equal(m, want) for m in mags)
