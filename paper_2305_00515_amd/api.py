@@ -308,6 +308,7 @@ class _PinnedOutputs:
     allocator with the pool."""
 
     LIMIT = 256 << 20
+    SMALLEST = 64 << 10     # below, an ordinary array costs less than the block's upkeep
 
     def __init__(self):
         self._lock = threading.Lock()
@@ -315,18 +316,18 @@ class _PinnedOutputs:
         self._bytes = 0      # of all blocks, in use and idle
 
     def array(self, h, w):
-        block = self._take(h * w) if h > 0 and w > 0 else None
+        block = self._take(h * w) if h > 0 and w > 0 and h * w >= self.SMALLEST else None
         if block is None:
             return np.empty((max(h, 0), max(w, 0)), np.uint8)
-        # Its base is the tensor, so numpy takes the array itself, and not the
+        # Its base is a tensor, so numpy takes the array itself, and not the
         # block, as the owner of every view made of it.
-        a = block[:h * w].view(h, w).numpy()
+        a = block.as_strided((h, w), (w, 1)).numpy()
         # A finalizer may run inside _take, on any thread: it takes no lock.
         weakref.finalize(a, self._idle[block.numel()].append, block).atexit = False
         return a
 
     def _take(self, nbytes):
-        size = 1 << max(16, (nbytes - 1).bit_length())
+        size = 1 << (nbytes - 1).bit_length()
         with self._lock:
             idle = self._idle.setdefault(size, deque())
             try:
