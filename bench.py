@@ -4,7 +4,7 @@ Headline: uint8 8192x8192, magnitude only, replicate border -- Gpixel/s and
 the achieved fraction of HBM peak, with inputs resident in HBM.  Launches
 rotate over >= 1 GiB of distinct (src, mag) buffer sets so that the 256 MB
 Infinity Cache cannot serve them.  Secondary results (mixed-size batch in one
-persistent launch vs per-image launches, fp32 forward+backward, the size /
+launch vs per-image launches, fp32 forward+backward, the size /
 output-type sweep) are reported in extra keys of the same JSON line.
 
 python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -276,7 +276,7 @@ def bench_batched(torch, api, synth, dev, steps, warmup):
         mags.append(torch.empty((h, w), dtype=torch.uint8, device=dev))
     px = sum(h * w for h, w in sizes)
     # one launch of the batched kernel (autotuned tile shape and grid form:
-    # one wave per tile, or a persistent grid on a work queue) in a hipGraph
+    # one wave per tile, or a persistent grid on a work queue)
     plan = api.Plan(srcs, mags, autotune=True)
     k = max(5, steps // 10)
     ms_plan = time_launches(torch, lambda i: plan.launch(), k, 20)
@@ -307,7 +307,7 @@ def bench_batched(torch, api, synth, dev, steps, warmup):
 def bench_borders(torch, api, synth, dev, steps, warmup):
     """Border rules on the 8192^2 magnitude (replicate, zero, reflect-101),
     and the 256-image batch with int16 directional planes as well as
-    magnitudes (2 + 8 = 10 B/px) in one persistent launch, per border."""
+    magnitudes (2 + 8 = 10 B/px) in one launch, per border."""
     out = {}
     img = synth.rect_image(N, N, 3)
     nsets = max(2, ROTATE_BYTES // (2 * N * N))
@@ -433,16 +433,18 @@ def bench_copy(torch, api, dev, steps):
 #   traffic: HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE and
 #            WRITE_SIZE (KiB per dispatch), each scaled by what the same
 #            counter reads for the plain copy kernel (sobel4x5_debug_copy) of
-#            known size (profiles/k_u8_single_8192x8192_mag_u8.md);
-#   valu:    VALU instructions per output pixel (SQ_INSTS_VALU x 64 / pixels
-#            from the same profile; the kernel has no transcendental
-#            instruction, so each is one issue slot).
-U8_PROFILE = {"src_sha256": "5c30fa8417524d3a", "traffic_bytes": 145362304, "valu_slots_per_px": 21434880 * 64 / 8192.0 ** 2}
+#            known size (profiles/k_band_single_8192x8192_mag_u8.md);
+#   valu:    vector instructions per output pixel without the matrix
+#            products, which issue beside them ((SQ_INSTS_VALU -
+#            SQ_INSTS_MFMA) x 64 / pixels from the same profile); one of them,
+#            the square root, issues at a lower rate.
+U8_PROFILE = {"src_sha256": "74f2b287e172847d", "traffic_bytes": 136018432,
+              "valu_slots_per_px": (10749052 - 1048576) * 64 / 8192.0 ** 2}
 
 
-# Sources k_u8_single is compiled from (the hash covers them in this order);
-# its launch code lives elsewhere (u8_launch.hpp, sobel4x5_u8.hip).
-U8_KERNEL_SOURCES = ("u8_sweep.hpp", "load_columns.hpp", "internal.hpp")
+# Sources k_band_single is compiled from (the hash covers them in this order);
+# its launch code lives elsewhere (sobel4x5_band.hip).
+U8_KERNEL_SOURCES = ("u8_band.hpp", "band_cols.hpp", "internal.hpp")
 
 
 def u8_source_hash():
@@ -546,7 +548,7 @@ def main():
                        "hot_same_buffer_ms": round(r["hot_ms"], 5), "per_launch_us": r["per_launch_us"]},
             "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": u8_profile("traffic_bytes"),
-                         "kernel": "k_u8_single<8,replicate,aligned,mag-only>",
+                         "kernel": "k_band_single",
                          "alg_bytes_per_launch": r["alg_bytes"], "valu": valu},
         })
     if want("copy"):

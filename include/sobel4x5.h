@@ -14,10 +14,9 @@
  *     caller.  Nothing here frees them.  Descriptor arrays and the outputs
  *     struct are HOST memory, read during the call only.
  *   - Pitches and strides are in BYTES.  A row pitch must be at least the
- *     row's width in bytes; any larger value is accepted.  Input images
- *     with 16-byte aligned rows (base and pitch) take the fast path; any
- *     other input takes a slower path with identical results.  Output rows
- *     need no alignment.
+ *     row's width in bytes; any larger value is accepted.  uint8 rows need
+ *     no alignment, in or out; output rows of whole 64-byte lines (base and
+ *     pitch) are the fastest to write.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *     Work is enqueued asynchronously on it; device faults surface at the
  *     caller's next synchronisation.
@@ -241,7 +240,7 @@ int sobel4x5_plan_info(sobel4x5_plan plan, int32_t *px_per_lane, int32_t *rows_p
  *   ntiles   : receives the plan's tile count (always, also with claims NULL).
  *   stream   : HIP stream.
  * Clears claims[0 .. ntiles) and launches the plan's kernel once, directly
- * (not through its graph), on `stream`; the outputs are written as by
+ * (never through a graph), on `stream`; the outputs are written as by
  * sobel4x5_plan_launch.  In a correct launch every counter ends at 1 (none
  * skipped, none taken twice), in the persistent and in the static grid form.
  * Must not overlap another launch of the same plan.  For tests and
@@ -251,7 +250,7 @@ int sobel4x5_plan_info(sobel4x5_plan plan, int32_t *px_per_lane, int32_t *rows_p
 int sobel4x5_debug_plan_claims(sobel4x5_plan plan, uint32_t *claims, int64_t capacity, int64_t *ntiles,
                                void *stream);
 
-/* Free the plan (device memory, graph).  Waits for nothing: the caller must
+/* Free the plan (device memory, and the graph if it has one).  Waits for nothing: the caller must
  * make sure no launch of it is still running. */
 int sobel4x5_plan_destroy(sobel4x5_plan plan);
 
@@ -317,9 +316,10 @@ int sobel4x5_validate_batch_ex(const sobel4x5_image *imgs, const sobel4x5_output
  *   max_width x max_height (device: 2 * depth * round_up(max_width, 256) *
  *   max_height bytes; pinned host: the same).  depth in [1, 16].
  * sobel4x5_pipe_run -- process `count` images (sobel4x5_image descriptors
- *   whose src and mag point to HOST memory, pageable or pinned; pinned
- *   buffers are copied directly, pageable ones through the staging
- *   buffers) with the given border; magnitude only.  Synchronous: returns
+ *   whose src and mag point to HOST memory, pageable or pinned; pinned rows
+ *   that lie back to back or whose pitch is a multiple of 4 are copied
+ *   directly, others through the staging buffers) with the given border;
+ *   magnitude only.  Synchronous: returns
  *   when every magnitude is in host memory.  A pipeline must not be run by
  *   two threads at once.  On an EHIP return every copy and kernel the call
  *   queued has finished (nothing writes a caller buffer afterwards), the
@@ -377,23 +377,19 @@ int sobel4x5_validate_f32(const float *src, int32_t batch, int32_t width, int32_
 int sobel4x5_debug_round_mag(const int32_t *S, uint8_t *out, int64_t n, void *stream);
 
 /*
- * The same with a choice of the two implementations of that rounding in
- * the two-directional operators' kernels: method 0 converts S to fp32 and
- * rounds its square root (kernels that run three waves per SIMD); method 1
- * reads a table of the rounded value of every S below 2^16, held in LDS, at
- * min(S, 65535) (kernels that run two waves per SIMD).  Both must give the
- * same byte for every S.  EINVAL for another method.
+ * The same with a choice of two implementations: method 0 converts S to
+ * fp32 and rounds its square root, as every kernel does; method 1 finds the
+ * root by integer arithmetic alone.  Both must give the same byte for every
+ * S.  EINVAL for another method.
  */
 int sobel4x5_debug_round_mag_ex(const int32_t *S, uint8_t *out, int64_t n, int32_t method, void *stream);
 
 /*
- * Diagnostic: the rounding of the four-directional kernels, step for step.
- * They never form S; they form E1 = (Gx + Gy)/2, E2 = (Gx - Gy)/2,
- * Hp = (Gd + Gdt)/2 and Hm = (Gd - Gdt)/2 (all int16), for which
- * S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2) (Eq. (sobel5_2)), sum the four squares
- * on int16 lanes saturating at 32767, and read min(255, round(sqrt(2 T)))
- * from a table in LDS.  q: n quadruples (E1, E2, Hp, Hm) of int16 (device,
- * 8 bytes each); out[i] (device) receives the byte of quadruple i, which
+ * Diagnostic: the four-directional magnitude's rounding from the half sums
+ * and differences that its kernel multiplies out, E1 = (Gx + Gy)/2,
+ * E2 = (Gx - Gy)/2, Hp = (Gd + Gdt)/2 and Hm = (Gd - Gdt)/2, for which
+ * S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2) (Eq. (sobel5_2)).  q: n quadruples
+ * (E1, E2, Hp, Hm) of int16 (device, 8 bytes each); out[i] (device) receives the byte of quadruple i, which
  * must equal min(255, round(sqrt(S))) for every int16 quadruple.
  * EINVAL for n < 0 or NULL pointers with n > 0.
  */

@@ -503,7 +503,7 @@ class Plan:
 
 def sobel4x5_batched(srcs, mags=None, border: int = BORDER_REPLICATE, *, want_mag: bool = True,
                      dir_type: int = DIR_NONE, dirs=None):
-    """Magnitudes of many uint8 images of uneven sizes in one persistent launch.
+    """Magnitudes of many uint8 images of uneven sizes in one launch.
 
     With dir_type (DIR_S16 / DIR_S32) every image also gets its four
     directional planes, and the result is a list of (mag or None, [planes]).
@@ -587,7 +587,7 @@ def sobel4x5_f32_bwd(x: torch.Tensor, grad_mag: torch.Tensor, border: int = BORD
 
 def debug_round_mag(S: torch.Tensor, method: int = 0) -> torch.Tensor:
     """The library's uint8 rounding min(255, round(sqrt(S))) of int32 values
-    S: method 0 by the fp32 square root, 1 by the LDS table."""
+    S: method 0 by the fp32 square root, 1 by integer arithmetic."""
     _need_cuda(S, torch.int32, "S")
     S = S.contiguous()
     out = torch.empty(S.shape, dtype=torch.uint8, device=S.device)
@@ -597,10 +597,9 @@ def debug_round_mag(S: torch.Tensor, method: int = 0) -> torch.Tensor:
 
 
 def debug_round_quad(q: torch.Tensor) -> torch.Tensor:
-    """The four-directional kernels' rounding of int16 quadruples
+    """The four-directional magnitude's rounding of int16 quadruples
     (E1, E2, Hp, Hm), shape [n, 4]: min(255, round(sqrt(S))) with
-    S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2), through the saturated int16 sum and
-    the LDS table."""
+    S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2)."""
     _need_cuda(q, torch.int16, "q")
     if q.dim() != 2 or q.shape[1] != 4:
         raise ValueError("q must have shape [n, 4]")

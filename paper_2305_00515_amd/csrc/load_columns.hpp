@@ -1,7 +1,8 @@
-// Byte columns a lane of the uint8 kernels loads from every row it reads
-// (aligned-row path), and the reflect-101 index map.  Plain integer code,
-// shared by the kernels and by host-side checks that enumerate every lane of
-// every launch geometry and every index the map can be asked for.
+// The reflect-101 index map of the kernels, and the byte columns of lanes that
+// load aligned blocks of rows (a layout that no kernel uses now: the banded
+// products load windows at any address, band_cols.hpp).  Plain integer code,
+// shared with host-side checks that enumerate every lane of every geometry
+// and every index the map can be asked for.
 //
 // A lane owns ppl (8 or 16) consecutive pixels starting at column xo (a
 // multiple of ppl); it loads the aligned ppl-byte block at `ldx`, and the

@@ -19,9 +19,9 @@
 // loads one window of 4 NB + 8 bytes of a row (NB words and one on each
 // side), and after 4 NB products holds all responses of 4 NB consecutive
 // pixels of one row.  The first two columns of a word take the windows of
-// that word and the one before, the last two of that word and the next.  An image quad enters
-// once and serves two steps (its operand registers keep their place, and the
-// weight operands come in two orders instead).
+// that word and the one before, the last two of that word and the next.  An
+// image quad enters once and serves two steps (its operand registers keep
+// their place, and the weight operands come in two orders instead).
 //
 // The tiles of a wave are 16 consecutive ones of the image's tile grid, row
 // band by row band; each lane addresses its own, so narrow images and the
@@ -33,9 +33,9 @@
 // is antisymmetric under a half turn, so its weights sum to zero and the
 // shift leaves the response unchanged.  Responses are exact in int32.
 //
-// What bounds it: memory.  A four-directional magnitude takes 8.7 vector
-// instructions and one product a pixel (8192^2: 10.1 M wave instructions,
-// 1.05 M of them products; 18 us of issue), and HBM moves 1.07 times the
+// What bounds it: memory.  A four-directional magnitude takes 9.3 vector
+// instructions and one product a pixel (8192^2: 10.7 M wave instructions,
+// 1.05 M of them products; 18 us of issue), and HBM moves 1.03 times the
 // input and 1.00 times the output.  8192^2 takes 25.8 us, 5.2 TB/s, where a
 // plain copy of the same bytes takes 27.0 us; the packed int16 sweep that
 // ran here before took 20.4 instructions a pixel and 45.1 us.  What counted:
