@@ -308,7 +308,9 @@ class _PinnedOutputs:
     allocator with the pool."""
 
     LIMIT = 256 << 20
-    SMALLEST = 64 << 10     # below, an ordinary array costs less than the block's upkeep
+    # below, an ordinary array costs less than the block's upkeep (a run of 3
+    # images of 256x256: 63 us against 69; of 4 of 400x701: 150 against 115)
+    SMALLEST = 256 << 10
 
     def __init__(self):
         self._lock = threading.Lock()

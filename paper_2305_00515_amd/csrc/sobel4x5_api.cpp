@@ -750,27 +750,33 @@ void pipe_free(sobel4x5_pipe_s *p)
     }
 }
 
+// Rows that lie back to back are copied as rows of whole words: one, two or
+// four of them at a time.
+int rows_per_word_row(int64_t w) { return w % 4 == 0 ? 1 : w % 2 == 0 ? 2 : 4; }
+
 // Rows in page-locked memory are copied from where they lie if their pitch is
 // of whole words or they lie back to back.  (A pitched copy of whole words is
 // one fast transfer; of any other pitch it goes row by row.  4 images of 896
 // rows out: 154 us a run for 733 bytes at a pitch of 736, 23.6 ms at 733 or
 // 734, 265 through the staging buffer.  A plain copy is slower than a pitched
-// one: 239 against 154 for 736 bytes back to back.)
-bool pipe_direct(const void *p, int64_t pitch, int32_t w)
+// one: 239 against 154 for 736 bytes back to back.)  Rows left over take a
+// second transfer, which a small image does not win back (3 of 301x301: 89 us
+// against 69 staged; 4 of 401x701: 137 against 150).
+bool pipe_direct(const void *p, int64_t pitch, int32_t w, int32_t h)
 {
-    return (pitch % 4 == 0 || pitch == w) && is_pinned(p);
+    if (pitch % 4 != 0 && (pitch != w || (h % rows_per_word_row(w) != 0 && (int64_t)w * h < 256 << 10))) return false;
+    return is_pinned(p);
 }
 
 // The device's pitch for such rows: its own, or back to back as they are.
 int64_t pipe_pitch(const PipeSlot &s, int64_t pitch, int32_t w) { return pitch % 4 ? w : s.pitch; }
 
-// Back to back rows of another pitch than whole words go as rows of four, and
-// what is left as one.
 hipError_t pipe_copy(uint8_t *dst, int64_t dpitch, const uint8_t *src, int64_t spitch, int32_t w, int32_t h,
                      hipMemcpyKind kind, hipStream_t st)
 {
     if (spitch % 4 == 0 && dpitch % 4 == 0) return hipMemcpy2DAsync(dst, dpitch, src, spitch, w, h, kind, st);
-    const size_t row = 4 * (size_t)w, rows = h / 4, rest = (h % 4) * (size_t)w;
+    const int k = rows_per_word_row(w);
+    const size_t row = k * (size_t)w, rows = h / k, rest = (h % k) * (size_t)w;
     hipError_t e = hipSuccess;
     if (rows) e = hipMemcpy2DAsync(dst, row, src, row, row, rows, kind, st);
     if (rest && e == hipSuccess)
@@ -1388,7 +1394,7 @@ int sobel4x5_pipe_run(sobel4x5_pipe p, const sobel4x5_image *imgs, int32_t count
         // staging buffer, so that the copy itself is asynchronous)
         const uint8_t *hs = m.src;
         int64_t hp = m.src_pitch;
-        if (!pipe_direct(m.src, m.src_pitch, m.width)) {
+        if (!pipe_direct(m.src, m.src_pitch, m.width, m.height)) {
             for (int32_t r = 0; r < m.height; ++r)
                 std::memcpy(sl.h_src + r * sl.pitch, m.src + r * m.src_pitch, (size_t)m.width);
             hs = sl.h_src;
@@ -1400,7 +1406,7 @@ int sobel4x5_pipe_run(sobel4x5_pipe p, const sobel4x5_image *imgs, int32_t count
         const int64_t sp = pipe_pitch(sl, hp, m.width);
         hipError_t e = guard(pipe_copy(sl.d_src, sp, hs, hp, m.width, m.height, hipMemcpyHostToDevice, sl.st));
         if (e != hipSuccess) return abandon(hip_fail(e, "pipeline host-to-device copy"));
-        sl.staged_out = !pipe_direct(m.mag, m.mag_pitch, Wo);
+        sl.staged_out = !pipe_direct(m.mag, m.mag_pitch, Wo, Ho);
         uint8_t *hm = sl.staged_out ? sl.h_mag : m.mag;
         const int64_t op = sl.staged_out ? sl.pitch : m.mag_pitch, dp = pipe_pitch(sl, op, Wo);
         U8Job j = make_job(sl.d_src, m.width, m.height, sp, Wo, Ho, sl.d_mag, dp, nullptr, 0, 0);

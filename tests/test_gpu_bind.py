@@ -117,16 +117,16 @@ def test_batched_binding_matches_the_general_path(sobel_lib, gpu, monkeypatch):
 def test_pipe_outputs_are_not_reused_while_viewed(oracle_mod, sobel_lib, gpu):
     """A view keeps its block out of the pool; a dropped array gives it back;
     beyond the limit the outputs are ordinary arrays."""
-    a, b = synth.rect_image(200, 333, 1), synth.rect_image(200, 333, 2)
+    a, b = synth.rect_image(500, 601, 1), synth.rect_image(500, 601, 2)
     want = oracle_mod.sobel_u8(a, 0, want_dir=False)[0]
-    pipe = sobel_lib.Pipe(333, 200)
+    pipe = sobel_lib.Pipe(601, 500)
     pool = pipe._outputs
     view = pipe.run([a])[0][10:, 3:].T
     for _ in range(3):
         pipe.run([b, b])
     gc.collect()
     assert np.array_equal(view, want[10:, 3:].T)
-    assert pool._bytes == 3 * (1 << 17)      # one viewed, two idle
+    assert pool._bytes == 3 * (1 << 19)      # one viewed, two idle
     pool.LIMIT = pool._bytes
     mags = pipe.run([a] * 5)
     assert all(np.array_equal(m, want) for m in mags) and pool._bytes <= pool.LIMIT
@@ -136,8 +136,8 @@ def test_pipe_outputs_are_not_reused_while_viewed(oracle_mod, sobel_lib, gpu):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("h", [1, 3, 4, 5, 260])
-@pytest.mark.parametrize("w,pad", [(300, 0), (301, 0), (301, 3), (301, 2), (333, 4)])
+@pytest.mark.parametrize("h", [1, 3, 4, 6, 899])
+@pytest.mark.parametrize("w,pad", [(300, 0), (301, 0), (302, 0), (301, 3), (301, 2), (333, 4)])
 def test_pipe_pinned_rows_of_any_pitch(oracle_mod, sobel_lib, gpu, h, w, pad):
     """Page-locked rows of whole words, back to back, and of other pitches,
     both ways; nothing outside the rows is written."""
@@ -145,7 +145,7 @@ def test_pipe_pinned_rows_of_any_pitch(oracle_mod, sobel_lib, gpu, h, w, pad):
     src = torch.empty((h, w + pad), dtype=torch.uint8, pin_memory=True)[:, :w]
     src.copy_(torch.from_numpy(img))
     whole = torch.full((h + 1, w + pad), 0x5A, dtype=torch.uint8, pin_memory=True)
-    pipe = sobel_lib.Pipe(400, 300)
+    pipe = sobel_lib.Pipe(400, 900)
     pipe.run([src], [whole[:h, :w]])
     want = oracle_mod.sobel_u8(img, 0, want_dir=False)[0]
     assert np.array_equal(whole[:h, :w].numpy(), want)
