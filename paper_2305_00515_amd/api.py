@@ -318,9 +318,9 @@ class _PinnedOutputs:
         self._bytes = 0      # of all blocks, in use and idle
 
     def array(self, h, w):
-        block = self._take(h * w) if h > 0 and w > 0 and h * w >= self.SMALLEST else None
+        block = self._take(h * w)
         if block is None:
-            return np.empty((max(h, 0), max(w, 0)), np.uint8)
+            return np.empty((h, w), np.uint8)
         # Its base is a tensor, so numpy takes the array itself, and not the
         # block, as the owner of every view made of it.
         a = block.as_strided((h, w), (w, 1)).numpy()
@@ -369,7 +369,10 @@ class Pipe:
             for m in srcs:
                 h, w = (m.shape[0], m.shape[1])
                 ho, wo = out_shape(h, w, border)
-                mags.append(self._outputs.array(ho, wo))
+                if ho * wo >= _PinnedOutputs.SMALLEST and ho > 0:
+                    mags.append(self._outputs.array(ho, wo))
+                else:
+                    mags.append(np.empty((max(ho, 0), max(wo, 0)), np.uint8))
         if len(mags) != n:
             raise ValueError("srcs and mags differ in length")
         arr = (Image * max(n, 1))()
