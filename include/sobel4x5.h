@@ -317,11 +317,11 @@ int sobel4x5_validate_batch_ex(const sobel4x5_image *imgs, const sobel4x5_output
  *   max_height bytes; pinned host: the same).  depth in [1, 16].
  * sobel4x5_pipe_run -- process `count` images (sobel4x5_image descriptors
  *   whose src and mag point to HOST memory, pageable or pinned; pinned rows
- *   that lie back to back or whose pitch is a multiple of 4 are mostly copied
- *   directly, others through the staging buffers) with the given border;
- *   magnitude only.  Synchronous: returns
- *   when every magnitude is in host memory.  A pipeline must not be run by
- *   two threads at once.  On an EHIP return every copy and kernel the call
+ *   that lie back to back or whose pitch is a multiple of 4 are copied
+ *   directly, others, and small images of odd width that leave rows over,
+ *   through the staging buffers) with the given border; magnitude only.
+ *   Synchronous: returns when every magnitude is in host memory.  A pipeline
+ *   must not be run by two threads at once.  On an EHIP return every copy and kernel the call
  *   queued has finished (nothing writes a caller buffer afterwards), the
  *   magnitudes of this call's images are unspecified, and the pipeline is
  *   idle and reusable with any other image array.
