@@ -54,6 +54,12 @@
 #include <type_traits>
 
 namespace s4x5 {
+
+// `v` with lane `lane` replaced by the scalar `s`: the compiler's intrinsic,
+// which keeps the two wait states between a vector instruction that writes `s`
+// (the reload of a spilled argument) and this one; asm would not.
+__device__ unsigned int write_lane(unsigned int s, unsigned int lane, unsigned int v) __asm("llvm.amdgcn.writelane.i32");
+
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -136,8 +142,8 @@ __device__ __forceinline__ void band_weights(const BandTaps &T, BandA<NR> &A)
     u32 lo = 0, hi = 0;
 #pragma unroll
     for (int i = 0; i < 5 * NR; ++i) {
-        asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((u32)T.row[i]), "n"(i));
-        asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((u32)(T.row[i] >> 32)), "n"(i));
+        lo = write_lane((u32)T.row[i], i, lo);
+        hi = write_lane((u32)(T.row[i] >> 32), i, hi);
     }
     const u64 near = band_tap(lo, hi, f, g - j), far = band_tap(lo, hi, f, g + 4 - j);
 #pragma unroll
@@ -149,7 +155,9 @@ __device__ __forceinline__ void band_weights(const BandTaps &T, BandA<NR> &A)
     }
 }
 
-// a * a + acc on the 24-bit multiplier (|a| < 2^23), one instruction.
+// a * a + acc on the 24-bit multiplier (|a| < 2^23), one instruction.  `a` may
+// come from a matrix product only if a compiled instruction has read that
+// product before: the wait for it stands there, and none before asm.
 __device__ __forceinline__ int sq24(int a, int acc)
 {
     int r;
@@ -324,7 +332,7 @@ __device__ __forceinline__ int sum_squares(const int (&G)[NR])
 #pragma unroll
     for (int f = 0; f < NR; ++f) {
         const int v = CLAMP ? band_clamp(G[f], -256, 256) : G[f];
-        S = f == 0 ? __mul24(v, v) : sq24(v, S);
+        S = f == 0 ? __mul24(v, v) : sq24(v, S);   // the compiled product comes first (see sq24)
     }
     return S;
 }
