@@ -259,7 +259,10 @@ int sobel4x5_plan_destroy(sobel4x5_plan plan);
  * allocates, uploads and keeps nothing, and works under graph capture.  A
  * larger batch builds a plan or reuses a cached one; the cache (8 plans,
  * least recently used first out) is keyed by every descriptor field, the
- * border, the device and the stream; evicting a plan waits for its stream. */
+ * border, the device and the stream; evicting a plan waits for its stream.
+ * Such a batch is SOBEL4X5_EUNSUPPORTED under graph capture, with nothing
+ * enqueued: the graph would outlive the cached plan.  Capture the launch of a
+ * plan of your own, or sobel4x5_batched_noalloc. */
 int sobel4x5_batched(const sobel4x5_image *imgs, int32_t count, int32_t border, void *stream);
 
 /* Host-only argument check of a batch (never touches the GPU). */
@@ -295,6 +298,8 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
  * planes, as for sobel4x5_u8).  imgs[i].mag and mag_pitch are ignored.
  * outs == NULL is the plain call.  Outputs of all images must not overlap
  * each other or any input.  The autotuner checks every output plane.
+ * sobel4x5_batched_ex with `outs` always uses a cached plan, and so is
+ * SOBEL4X5_EUNSUPPORTED under graph capture.
  */
 int sobel4x5_plan_create_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *outs, int32_t count,
                             int32_t border, uint32_t flags, sobel4x5_plan *out);

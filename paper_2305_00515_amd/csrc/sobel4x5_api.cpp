@@ -665,6 +665,15 @@ PlanCache &plan_cache()
     return *c;
 }
 
+// Whether `st` is being captured into a graph (the null stream cannot be).
+hipError_t is_captured(hipStream_t st, bool *captured)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    const hipError_t e = st ? hipStreamIsCapturing(st, &s) : hipSuccess;
+    *captured = s != hipStreamCaptureStatusNone;
+    return e;
+}
+
 // Key of a one-shot batched call, from the descriptor fields one by one (not
 // the structs' raw bytes, whose padding a C caller may leave uninitialised),
 // the border, the device and the stream.  A plan's work queue admits one
@@ -1000,6 +1009,14 @@ int sobel4x5_batched_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *outs
             return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
         }
     }
+    // A graph would replay the launch with the cached plan's tables, which the
+    // cache frees at its own time: only a plan that the caller holds may be
+    // captured.
+    bool captured;
+    if (hipError_t e = is_captured(st, &captured); e != hipSuccess) return hip_fail(e, "batched launch");
+    if (captured)
+        return fail(SOBEL4X5_EUNSUPPORTED, "a stream capture takes batches of up to %d magnitudes; others need a plan "
+                    "(sobel4x5_plan_create) that outlives the graph", kBatchArgs);
     int dev = 0;
     hipGetDevice(&dev);
     const std::string key = batch_key(imgs, outs, count, border, dev, st);
