@@ -282,8 +282,11 @@ int sobel4x5_validate_batch(const sobel4x5_image *imgs, int32_t count, int32_t b
  *   Limits: count <= SOBEL4X5_NOALLOC_MAX_IMAGES and at most
  *   SOBEL4X5_NOALLOC_MAX_TILES wave-tiles (about 150 per 2048x2048 image);
  *   a batch beyond either is SOBEL4X5_EINVAL, with nothing enqueued.
- *   Every call on one device uses that device's one buffer, which keeps the
- *   last call's tables: calls on one stream are ordered and safe, but calls
+ *   Under graph capture nothing is copied: the images travel in the arguments
+ *   of one kernel per 48 images, so the graph holds all that it reads and no
+ *   other call disturbs a replay.
+ *   Otherwise every call on one device uses that device's one buffer, which
+ *   keeps the last call's tables: calls on one stream are ordered and safe, but calls
  *   that overlap in time on one device (different streams not joined by
  *   events, or different threads) race and give wrong results.
  */

@@ -1063,7 +1063,7 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     // Tables built on the host in fixed static buffers (no allocation, host
     // or device), then copied into the fixed device buffer on `stream`.  The
     // lock covers the building and both copies: a copy from pageable memory
-    // has read its source when hipMemcpyAsync returns.
+    // has read its source when hipMemcpyAsync returns (outside a capture).
     static std::mutex mu;
     static unsigned char stage[kNoallocBytes];     // queue words, jobs, tiles: the device layout
     std::lock_guard<std::mutex> lk(mu);
@@ -1084,6 +1084,19 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     if (budget > kNoallocMaxTiles)
         return fail(SOBEL4X5_EINVAL, "the batch needs more than %d wave-tiles, the allocation-free call's limit",
                     kNoallocMaxTiles);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    // Under capture the copies below would read `stage` again at every replay,
+    // and the device buffer would hold whatever call came last: the images go
+    // into kernel arguments instead, which the graph keeps.
+    bool captured;
+    hipError_t e = is_captured(st, &captured);
+    if (e != hipSuccess) return hip_fail(e, "batched launch");
+    for (int32_t i = 0; captured && i < count; i += kBatchArgs) {
+        e = guard(launch_u8_batched(jobs + i, nullptr, std::min(kBatchArgs, count - i), nullptr, border,
+                                    stores.past_l2(), false, shape, 0, st));
+        if (e != hipSuccess) return hip_fail(e, "batched launch");
+    }
+    if (captured) return ok();
     // bands high enough for the table: a batch within the budget fits with
     // one band an image at the latest
     int64_t total = 0;
@@ -1100,10 +1113,8 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     int4 *t = reinterpret_cast<int4 *>(stage + kNoallocTilesOff);
     for (int32_t i = 0; i < count; ++i) batched_tiles_each(jobs[i], i, shape.th, [&](int4 e) { *t++ = e; });
     void *scr = nullptr;
-    hipError_t e = guard(noalloc_scratch(&scr));
-    if (e != hipSuccess) return hip_fail(e, "looking up the fixed device buffer");
+    if ((e = guard(noalloc_scratch(&scr))) != hipSuccess) return hip_fail(e, "looking up the fixed device buffer");
     unsigned char *base = static_cast<unsigned char *>(scr);
-    hipStream_t st = static_cast<hipStream_t>(stream);
     // queue words and the count jobs, then the total tiles
     if ((e = guard(hipMemcpyAsync(base, stage, kNoallocJobsOff + sizeof(U8Job) * count, hipMemcpyHostToDevice,
                                   st))) != hipSuccess ||

@@ -139,6 +139,28 @@ int main()
         CHECK(sobel4x5_batched(imgs.data(), 49, 0, st) == SOBEL4X5_OK);
         CHECK(sobel4x5_batched_ex(imgs.data(), outs.data(), 3, 0, st) == SOBEL4X5_OK);
         CHECK(launches.size() == 3 && !launches[1].in_arguments && !launches[2].in_arguments);
+        allocations = 0;
+    }
+
+    // The allocation-free call: a graph must hold all that its launches read, so
+    // that another batch in between changes nothing for a replay.
+    for (int32_t count : {1, 48, 49, 130}) {
+        capturing = true;
+        launches.clear();
+        copies = 0;
+        CHECK(sobel4x5_batched_noalloc(imgs.data(), count, 0, st) == SOBEL4X5_OK);
+        std::vector<const uint8_t *> seen;
+        for (const Launch &l : launches) {
+            CHECK(l.in_arguments && (int)l.srcs.size() <= s4x5::kBatchArgs);
+            seen.insert(seen.end(), l.srcs.begin(), l.srcs.end());
+        }
+        CHECK(copies == 0 && allocations == 0);
+        CHECK((int)seen.size() == count);
+        for (int i = 0; i < (int)seen.size() && i < count; ++i) CHECK(seen[i] == imgs[i].src);
+        capturing = false;
+        launches.clear();
+        CHECK(sobel4x5_batched_noalloc(imgs.data(), count, 0, st) == SOBEL4X5_OK);
+        CHECK(launches.size() == 1 && !launches[0].in_arguments && allocations == 0);
     }
 
     if (bad) return 1;

@@ -57,3 +57,27 @@ def test_batches_of_a_cached_plan_are_refused_under_capture(oracle_mod, sobel_li
     want = [oracle_mod.sobel_u8(m, want_dir=False)[0] for m in imgs]
     assert np.array_equal(one.cpu().numpy(), want[0])
     assert all(np.array_equal(t.cpu().numpy(), w) for t, w in zip(mags, want))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("count", [3, 49, 100])
+def test_captured_noalloc_call_is_its_own(oracle_mod, sobel_lib, gpu, count):
+    """Batch A captured through the allocation-free call, batch B run eagerly
+    through it, A replayed: A's outputs, call after call."""
+    def batch(n, seed):
+        imgs = [synth.rect_image(17 + (7 * i + seed) % 40, 21 + (11 * i) % 60, seed + i) % 6 for i in range(n)]
+        srcs = [torch.from_numpy(m).to(gpu) for m in imgs]
+        return imgs, srcs, [torch.zeros_like(s) for s in srcs]
+    a, b = batch(count, 1), batch(count + 5, 500)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        sobel_lib.sobel4x5_batched_noalloc(a[1], a[2])
+    for _ in range(3):
+        for t in a[2] + b[2]:
+            t.zero_()
+        sobel_lib.sobel4x5_batched_noalloc(b[1], b[2])
+        g.replay()
+        torch.cuda.synchronize()
+        for imgs, _, mags in (a, b):
+            for m, t in zip(imgs, mags):
+                assert np.array_equal(t.cpu().numpy(), oracle_mod.sobel_u8(m, want_dir=False)[0]), m.shape
