@@ -225,7 +225,8 @@ def sobel4x5_u8_op(src: torch.Tensor, op: int, border: int = BORDER_REPLICATE, *
                    dirs: list | None = None):
     """sobel4x5_u8 for operator `op` (OP_*): the two-directional operators
     return two planes [Gx, Gy]; the 3x3 pair's VALID output is (H-2, W-2)."""
-    r = _bind_u8(src, op, border, mag, want_mag, dir_type, dirs, None)
+    # (None is the binding's own word for the default operator)
+    r = None if op is None else _bind_u8(src, op, border, mag, want_mag, dir_type, dirs, None)
     if r.__class__ is tuple:
         return r
     if r is not None:
@@ -248,7 +249,7 @@ def sobel4x5_u8_weighted(src: torch.Tensor, weights, border: int = BORDER_REPLIC
                          dirs: list | None = None):
     """sobel4x5_u8 with run-time integer kernels (4, 5, 5), plane order as the
     default operator; each kernel antisymmetric under a half turn."""
-    r = _bind_u8(src, None, border, mag, want_mag, dir_type, dirs, weights)
+    r = None if weights is None else _bind_u8(src, None, border, mag, want_mag, dir_type, dirs, weights)
     if r.__class__ is tuple:
         return r
     if r is not None:
