@@ -11,8 +11,11 @@ where it is built; what it does not take, the code here handles and refuses.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import sys
 import threading
+import warnings
 import weakref
 from collections import deque
 from pathlib import Path
@@ -112,21 +115,31 @@ lib = _load()
 
 
 def _load_bind():
-    """(u8, batched) of the compiled binding, or two functions that take no
-    call where it has not been built."""
+    """The compiled binding, or None where it has not been built or does not
+    fit this torch and interpreter (whose C++ interface it is tied to)."""
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if raw is None or not (_PKG / "_bind.so").exists():
-        return (lambda *a: None,) * 2
-    from . import _bind
+        return None
+    here = "torch %s, Python %d.%d" % ((torch.__version__,) + sys.version_info[:2])
+    try:
+        bind = importlib.import_module("._bind", __package__)
+        why = None if bind.built_for == here else "it was built for %s" % bind.built_for
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    if why:
+        warnings.warn("%s: the compiled binding is not used, and calls cost more on the host (%s; this is %s). "
+                      "Build again." % (_PKG.name, why, here), RuntimeWarning)
+        return None
     fns = (lib.sobel4x5_u8, lib.sobel4x5_u8_op, lib.sobel4x5_u8_weighted, lib.sobel4x5_batched)
-    _bind.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in fns), raw)
-    return _bind.u8, _bind.batched
+    bind.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in fns), raw)
+    return bind
 
 
 # Each returns the call's result in a tuple, the library's status, or None for
 # a call that is not in the plain form that it takes: 512x512 magnitudes cost
 # their caller 10.7 us through ctypes and 4.6 through it, 16 crops 94 and 19.
-_bind_u8, _bind_batched = _load_bind()
+_bind = _load_bind()
+_bind_u8, _bind_batched = (_bind.u8, _bind.batched) if _bind else (lambda *a: None,) * 2
 
 
 def _check(rc: int, where: str) -> None:

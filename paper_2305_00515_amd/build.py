@@ -54,7 +54,11 @@ def hipcc() -> str:
 def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    try:
+        res = subprocess.run(cmd, capture_output=True, text=True)
+    except OSError as e:
+        sys.stderr.write("%s: %s\n" % (cmd[0], e))
+        return 1
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
     elif verbose and res.stderr.strip():
@@ -71,6 +75,7 @@ def bind_command(out: Path):
     cxx = os.environ.get("CXX") or shutil.which("g++") or hipcc()
     return [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            '-DSOBEL4X5_TORCH="%s"' % torch.__version__,
             "-isystem", str(t / "include"), "-isystem", str(t / "include" / "torch" / "csrc" / "api" / "include"),
             "-I" + sysconfig.get_paths()["include"], "-I" + str(ROOT / "include"),
             "-o", str(out), str(CSRC / "bind.cpp"),
@@ -79,7 +84,9 @@ def bind_command(out: Path):
 
 def build(verbose: bool = False, out: Path | None = None, defines=()) -> Path:
     """Compile every source into libsobel4x5.so, and the binding beside it
-    (always recompiles).
+    (always recompiles).  The library works without the binding, so a machine
+    that cannot build it (no torch headers, no host compiler) gets the library
+    alone, with a word on stderr.
 
     The translation units compile in parallel into a scratch folder, then
     link.  ``out`` and ``defines`` (NAME=VALUE strings) build a variant
@@ -98,21 +105,27 @@ def build(verbose: bool = False, out: Path | None = None, defines=()) -> Path:
         objs = [str(o) for o, _ in jobs]
         bind = objdir / BIND.name
         if out == LIB:
-            jobs.append((bind, bind_command(bind)))
+            try:
+                jobs.append((bind, bind_command(bind)))
+            except (ImportError, RuntimeError) as e:
+                sys.stderr.write("no command to build the binding: %s\n" % e)
         workers = max(1, min(len(jobs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
         with ThreadPoolExecutor(max_workers=workers) as ex:
             codes = list(ex.map(lambda j: _run(j[1], verbose), jobs))
-        if any(codes):
+        if any(codes[:len(objs)]):
             raise RuntimeError("hipcc failed building libsobel4x5.so")
         tmp = out.with_suffix(".so.tmp%d" % os.getpid())
         link = [hipcc(), "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", str(tmp)] + objs
         if _run(link, verbose):
             raise RuntimeError("linking libsobel4x5.so failed")
         os.replace(tmp, out)
-        if out == LIB:
+        if out == LIB and len(codes) > len(objs) and codes[-1] == 0:
             tmp = BIND.with_suffix(".so.tmp%d" % os.getpid())
             shutil.copyfile(bind, tmp)
             os.replace(tmp, BIND)
+        elif out == LIB:
+            BIND.unlink(missing_ok=True)    # none rather than one of another build
+            sys.stderr.write("the binding was not built: calls will take the general path\n")
     finally:
         shutil.rmtree(objdir, ignore_errors=True)
     return out

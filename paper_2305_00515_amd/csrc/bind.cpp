@@ -22,6 +22,11 @@
 
 #include "../../include/sobel4x5.h"
 
+// The torch that this is built against: another one's C++ interface may differ.
+#ifndef SOBEL4X5_TORCH
+#define SOBEL4X5_TORCH "unknown"
+#endif
+
 namespace {
 
 using U8 = int (*)(const uint8_t *, int32_t, int32_t, int64_t, int32_t, const sobel4x5_outputs *, void *);
@@ -323,4 +328,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bind", nullptr, -1, methods, null
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__bind() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__bind()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddObject(m, "built_for",
+                                PyUnicode_FromFormat("torch %s, Python %d.%d", SOBEL4X5_TORCH, PY_MAJOR_VERSION,
+                                                     PY_MINOR_VERSION)) < 0)
+        Py_CLEAR(m);
+    return m;
+}
