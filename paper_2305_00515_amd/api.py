@@ -14,10 +14,7 @@ import ctypes
 import importlib
 import os
 import sys
-import threading
 import warnings
-import weakref
-from collections import deque
 from pathlib import Path
 
 import numpy as np
@@ -312,56 +309,31 @@ def _host_rows(a, name):
     return a.shape[0], a.shape[1], a.strides[0], a.ctypes.data
 
 
-class _PinnedOutputs:
-    """Page-locked output arrays of one Pipe.  The device copies straight into
-    them, where a new pageable array of 2 MB costs its page faults and a second
-    copy (8 images of 1080x1920: 1.85 ms a run into pageable arrays, 1.04 into
-    these).  A block comes back when its array, with every view of it, is
-    gone; blocks in use and idle together stay within LIMIT bytes, and beyond
-    that the arrays are ordinary ones.  The blocks go back to torch's pinned
-    allocator with the pool."""
+class _Outputs:
+    """Output arrays of one Pipe, in ordinary memory whose blocks are kept for
+    the next arrays: a new array of 2 MB costs its page faults.  An array owns
+    its block, which comes back when the array, with every view of it, is gone;
+    blocks in use and idle together stay within LIMIT bytes, and beyond that,
+    or without the compiled binding, the arrays are numpy's own."""
 
     LIMIT = 256 << 20
-    # below, an ordinary array costs less than the block's upkeep (a run of 3
-    # images of 256x256: 63 us against 69; of 4 of 400x701: 150 against 115)
-    SMALLEST = 256 << 10
+    SMALLEST = 256 << 10     # below, the C library keeps the block itself
 
     def __init__(self):
-        self._lock = threading.Lock()
-        self._idle = {}      # block size -> deque of idle blocks
-        self._bytes = 0      # of all blocks, in use and idle
+        self._pool = _bind.host_pool() if _bind else None
 
     def array(self, h, w):
-        block = self._take(h * w)
-        if block is None:
-            return np.empty((h, w), np.uint8)
-        # Its base is a tensor, so numpy takes the array itself, and not the
-        # block, as the owner of every view made of it.
-        a = block.as_strided((h, w), (w, 1)).numpy()
-        # A finalizer may run inside _take, on any thread: it takes no lock.
-        weakref.finalize(a, self._idle[block.numel()].append, block).atexit = False
-        return a
+        if self._pool is None or h * w < self.SMALLEST or h < 1:
+            return np.empty((max(h, 0), max(w, 0)), np.uint8)
+        return _bind.host_array(self._pool, h, w, self.LIMIT)
 
-    def _take(self, nbytes):
-        size = 1 << (nbytes - 1).bit_length()
-        with self._lock:
-            idle = self._idle.setdefault(size, deque())
-            try:
-                return idle.pop()
-            except IndexError:
-                pass
-            for other, blocks in self._idle.items():
-                while self._bytes + size > self.LIMIT and blocks:
-                    blocks.pop()
-                    self._bytes -= other
-            if self._bytes + size > self.LIMIT:
-                return None
-            try:
-                block = torch.empty(size, dtype=torch.uint8, pin_memory=True)
-            except RuntimeError:
-                return None
-            self._bytes += size
-            return block
+    @property
+    def _bytes(self):
+        return _bind.host_bytes(self._pool) if self._pool else 0
+
+    def close(self):
+        if self._pool is not None:
+            _bind.host_close(self._pool)
 
 
 class Pipe:
@@ -370,23 +342,19 @@ class Pipe:
 
     def __init__(self, max_width: int, max_height: int, depth: int = 3):
         self._h = ctypes.c_void_p()
-        self._outputs = _PinnedOutputs()
+        self._outputs = _Outputs()
         _check(lib.sobel4x5_pipe_create(max_width, max_height, depth, ctypes.byref(self._h)), "sobel4x5_pipe_create")
 
     def run(self, srcs, mags=None, border: int = BORDER_REPLICATE):
         """srcs: uint8 host images (numpy arrays or CPU tensors, pinned or
-        not); mags: matching outputs or None (numpy arrays are allocated, in
-        page-locked memory up to 256 MiB a Pipe)."""
+        not); mags: matching outputs or None (numpy arrays are allocated; the
+        Pipe keeps the memory of up to 256 MiB of them for its next runs)."""
         n = len(srcs)
         if mags is None:
             mags = []
             for m in srcs:
                 h, w = (m.shape[0], m.shape[1])
-                ho, wo = out_shape(h, w, border)
-                if ho * wo >= _PinnedOutputs.SMALLEST and ho > 0:
-                    mags.append(self._outputs.array(ho, wo))
-                else:
-                    mags.append(np.empty((max(ho, 0), max(wo, 0)), np.uint8))
+                mags.append(self._outputs.array(*out_shape(h, w, border)))
         if len(mags) != n:
             raise ValueError("srcs and mags differ in length")
         arr = (Image * max(n, 1))()
@@ -404,7 +372,7 @@ class Pipe:
         if self._h:
             lib.sobel4x5_pipe_destroy(self._h)
             self._h = ctypes.c_void_p()
-            self._outputs = _PinnedOutputs()
+            self._outputs.close()
 
     def __del__(self):
         try:

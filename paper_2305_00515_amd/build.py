@@ -17,7 +17,7 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libsobel4x5.so"
-BIND = PKG / "_bind.so"      # CPython binding of the library's smallest calls
+BIND = PKG / "_bind.so"      # CPython binding of the library's smallest calls, and the pipe's arrays
 ARCH = os.environ.get("SOBEL4X5_ARCH", "gfx950")
 
 SOURCES = ["sobel4x5_api.cpp", "sobel4x5_u8.hip", "sobel4x5_f32.hip",
@@ -67,9 +67,10 @@ def _run(cmd, verbose):
 
 
 def bind_command(out: Path):
-    """The host compiler's line for the CPython binding (torch's headers, no
+    """The host compiler's line for the CPython binding (torch's and numpy's headers, no
     GPU code; it reaches the library through addresses that api.py hands it)."""
     import sysconfig
+    import numpy
     import torch
     t = Path(torch.__file__).resolve().parent
     cxx = os.environ.get("CXX") or shutil.which("g++") or hipcc()
@@ -77,7 +78,7 @@ def bind_command(out: Path):
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
             '-DSOBEL4X5_TORCH="%s"' % torch.__version__,
             "-isystem", str(t / "include"), "-isystem", str(t / "include" / "torch" / "csrc" / "api" / "include"),
-            "-I" + sysconfig.get_paths()["include"], "-I" + str(ROOT / "include"),
+            "-isystem", numpy.get_include(), "-I" + sysconfig.get_paths()["include"], "-I" + str(ROOT / "include"),
             "-o", str(out), str(CSRC / "bind.cpp"),
             "-L" + str(t / "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
 

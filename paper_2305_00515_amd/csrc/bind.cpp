@@ -7,11 +7,11 @@
 // 2160x3840: 10.6 -> 5.0; run-time kernels: 12.9 -> 5.7; 16 crops of 64..640 in
 // one batch: 94 -> 19.)
 //
-// Each function here handles exact torch tensors in exactly the forms that the
+// Each function of a call handles exact torch tensors in exactly the forms that the
 // C entry points take.  For everything else -- another type, a wrong shape, a
 // tensor subclass, a function mode, an allocation that fails -- it returns None
 // before anything is launched and the caller takes its general path, which
-// decides and words the error.  Nothing is kept between calls.
+// decides and words the error.  Nothing is kept between these calls.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/Functions.h>
@@ -20,7 +20,10 @@
 #include <cstdint>
 #include <vector>
 
+#define NPY_NO_DEPRECATED_API NPY_1_22_API_VERSION
+#define NPY_TARGET_VERSION NPY_1_22_API_VERSION
 #include "../../include/sobel4x5.h"
+#include "host_arrays.hpp"
 
 // The torch that this is built against: another one's C++ interface may differ.
 #ifndef SOBEL4X5_TORCH
@@ -321,6 +324,10 @@ PyMethodDef methods[] = {
     {"init", fast(init), METH_FASTCALL, nullptr},
     {"u8", fast(entry<8, u8_call>), METH_FASTCALL, nullptr},
     {"batched", fast(entry<3, batched_call>), METH_FASTCALL, nullptr},
+    {"host_pool", host_pool, METH_NOARGS, nullptr},
+    {"host_array", fast(host_array), METH_FASTCALL, nullptr},
+    {"host_bytes", host_bytes, METH_O, nullptr},
+    {"host_close", host_close, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 
@@ -330,6 +337,7 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bind", nullptr, -1, methods, null
 
 PyMODINIT_FUNC PyInit__bind()
 {
+    if (PyArray_ImportNumPyAPI() < 0) return nullptr;
     PyObject *m = PyModule_Create(&module);
     if (m && PyModule_AddObject(m, "built_for",
                                 PyUnicode_FromFormat("torch %s, Python %d.%d", SOBEL4X5_TORCH, PY_MAJOR_VERSION,
