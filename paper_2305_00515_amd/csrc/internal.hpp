@@ -7,6 +7,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "launch_rules.hpp"
+
 namespace s4x5 {
 
 // One uint8 image as the kernels see it.  Output pixel (yo, xo) is the

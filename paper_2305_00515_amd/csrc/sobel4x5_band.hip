@@ -23,26 +23,6 @@ int64_t band_slots()
     return (int64_t)n * kBandResident;
 }
 
-// Bands of an image of nt tile columns and nq quads of rows.
-// - The fewest steps with which all waves are resident at once, as a wave that
-//   waits for a slot starts with a trip to memory (4096^2 at 4 steps 10.7 us,
-//   at 2 12.1; 3840x2160 at 2 steps 6.9 us, at 1 8.5).  Above one step an
-//   even number (the steps come in pairs: 4001x2999 9.1 us at 4 steps, 10.0
-//   at 3).  At most 8 steps: larger images run several rounds, which hide
-//   each other's first loads and end more evenly (16384^2: 103.6 us at 8
-//   steps, 114.8 at 64; 8192^2: 25.8 at 8 and 25.7 at 16).
-// - With planes one step: the stores bound it, and many short waves store in
-//   the order of memory (4096^2 with int16 planes 24.6 us at 1 step, 27.8 at
-//   2, 31.5 at 8; int32 52.5, 53.3, 55.0).
-int band_steps(int64_t nt, int64_t nq, int64_t slots, bool planes)
-{
-    const int64_t bands = std::max<int64_t>(1, slots * 16 / nt);
-    int64_t bq = planes ? 1 : (nq + bands - 1) / bands;
-    if (bq > 1) bq = std::min<int64_t>((bq + 1) / 2 * 2, 8);
-    while (nt * ((nq + bq - 1) / bq) > INT32_MAX) bq *= 2;   // tiles are numbered in 32 bits
-    return (int)bq;
-}
-
 const void *batched_fn(bool dir, bool past)
 {
     if (dir)

@@ -46,7 +46,7 @@
 //     sums, and the scaling of tiny S only in rows that hold one: 86 -> 72
 //     instructions (adjoint 105 -> 97 us);
 //   - short row ranges where a batch is small or memory is the bound
-//     (chunks_for: forward 67 -> 59 us; 1 x 256^2 38.6 -> 9.8 us).
+//     (f32_ranges: forward 67 -> 59 us; 1 x 256^2 38.6 -> 9.8 us).
 // Five waves a SIMD (96 registers) spill and take 156 us; each XCD on one
 // stretch of the batch takes the forward to 72 us.
 
@@ -694,22 +694,10 @@ int resident_f32(const void *fn)
     return w;
 }
 
-// Row chunks per strip: as many as fill one round of resident waves (rounding
-// up would leave a few waves to run as a second, nearly empty round), of at
-// least 4 rows, though a chunk costs 4 (forward) or 8 (adjoint) warm-up rows:
-// small batches are bound by the serial steps of a wave (forward + adjoint of
-// 1 x 256^2: 10.5 us at 4 rows, 31.5 at 32; 8 x 512^2 23.7 and 33.7).  `most`
-// rows at most: the forward of a large batch, which is bound by memory, runs
-// several rounds that follow each other through the image (32 x 1024^2: 59.5
-// us at 16 rows, 67.0 in one round of 36); the adjoint, bound by its
-// arithmetic, does not (one round of 73 rows 105 us, 32 rows 107, 16 rows 113).
 int chunks_for(const void *fn, int64_t strips, int rows, int most)
 {
-    int slots = resident_f32(fn);
-    if (slots <= 0) slots = 4096;
-    int64_t n = std::max<int64_t>(slots / strips, rows / most);
-    n = std::max<int64_t>(1, std::min<int64_t>(n, rows / 4));
-    return (int)n;
+    const int slots = resident_f32(fn);
+    return f32_ranges(slots > 0 ? slots : 4096, strips, rows, most);
 }
 
 }  // namespace
