@@ -37,10 +37,7 @@ struct U8Shape {
     int waves = 0;  // single image: waves to launch (0 = by size); batched: kStaticGrid or a persistent grid
 };
 
-// Fills the tile columns of `j` for tiles of s.ppl pixels.  Rows of tiles
-// start at multiples of 8 tiles (128 bytes of magnitudes) where that adds at
-// most a sixteenth of the tiles, so that a wave's bytes of a row are whole
-// lines.
+// Fills the tile columns of `j` for tiles of s.ppl pixels (tile_columns).
 void u8_tile(U8Job &j, const U8Shape &s);
 
 // Whether a launch's outputs are stored past the L2 (nontemporal).  Measured on
@@ -107,39 +104,17 @@ hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total
 // Wave-tiles of image `img` (tiled by u8_tile): 16 consecutive tiles of its
 // tile grid each, in bands of `th` rows, as {image, first tile, steps of four
 // rows, tiles of the image}.
-inline int64_t batched_bands(const U8Job &j, int th) { return ((int64_t)j.Ho + th - 1) / th; }
-inline int64_t batched_count(const U8Job &j, int th) { return (j.nt * batched_bands(j, th) + 15) / 16; }
 template <class Push>
 void batched_tiles_each(const U8Job &j, int32_t img, int th, Push &&push)
 {
-    const int64_t tiles = j.nt * batched_bands(j, th);
+    const int64_t tiles = batched_image_tiles(j, th);
     for (int64_t t = 0; t < tiles; t += 16) push(make_int4(img, (int)t, th / 4, (int)tiles));
-}
-
-// The unit in which the allocation-free call's public limit is counted: per
-// image, strips of 512 columns in chunks of `tallx` * 32 rows, the last
-// 1 / `shortq` of the rows in chunks of 32; the 128-column tiles that no whole
-// strip holds in chunks of 128 rows.
-struct BatchSplit {
-    int tallx;
-    int shortq;
-};
-inline int64_t budget_tiles(int32_t Wo, int32_t Ho, const BatchSplit &sp = BatchSplit{2, 4})
-{
-    const int64_t ntx = ((int64_t)Wo + 127) / 128, strips = ntx / 4, tall = 32 * sp.tallx;
-    const int64_t rows = (Ho - Ho / sp.shortq) / tall * tall;
-    return strips * (rows / tall + (Ho - rows + 31) / 32) + (ntx - 4 * strips) * (((int64_t)Ho + 127) / 128);
 }
 
 // Allocation-free batched call (sobel4x5_batched_noalloc): the queue
 // words, the job table and the tile table of one batch live in a fixed
 // device buffer of kNoallocBytes per device, laid out as below.  The limits
-// are the public SOBEL4X5_NOALLOC_MAX_*.
-constexpr int32_t kNoallocMaxImages = 1024;
-constexpr int32_t kNoallocMaxTiles = 65536;
-// entries of the tile table: a wave-tile is half as wide as the budget's
-// strip, and rows of tiles are rounded up by at most a sixteenth
-constexpr int32_t kNoallocTable = 2 * kNoallocMaxTiles + kNoallocMaxTiles / 4 + kNoallocMaxImages;
+// are the public SOBEL4X5_NOALLOC_MAX_* (launch_rules.hpp).
 constexpr size_t kNoallocJobsOff = 256;   // bytes [0, 8): queue[0], queue[1]
 constexpr size_t kNoallocTilesOff = (kNoallocJobsOff + sizeof(U8Job) * kNoallocMaxImages + 255) / 256 * 256;
 constexpr size_t kNoallocBytes = kNoallocTilesOff + sizeof(int4) * kNoallocTable;

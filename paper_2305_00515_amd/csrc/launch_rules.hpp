@@ -51,4 +51,70 @@ inline int band_steps(int64_t nt, int64_t nq, int64_t slots, bool planes)
     return (int)bq;
 }
 
+// Tile columns of an image of Wo columns, for tiles of ppl pixels.  Rows of
+// tiles start at multiples of 8 tiles (128 bytes of magnitudes) where that adds
+// at most a sixteenth of the tiles, so that a wave's bytes of a row are whole
+// lines.
+inline uint32_t tile_columns(int32_t Wo, int ppl)
+{
+    const int64_t nt = ((int64_t)Wo + ppl - 1) / ppl, whole = (nt + 7) / 8 * 8;
+    return (uint32_t)((whole - nt) * 16 <= nt ? whole : nt);
+}
+
+// Batches: tiles of an image of j.nt tile columns and j.Ho rows in bands of th
+// rows, and the wave-tiles (16 tiles) that hold them.
+template <class Job>
+int64_t batched_image_tiles(const Job &j, int th)
+{
+    return (int64_t)j.nt * (((int64_t)j.Ho + th - 1) / th);
+}
+template <class Job>
+int64_t batched_count(const Job &j, int th)
+{
+    return (batched_image_tiles(j, th) + 15) / 16;
+}
+
+// The height of a batch's bands: `th`, doubled until the batch has at most
+// `limit` wave-tiles and every image's tiles are numbered in 31 bits; 0 if that
+// is not so even with one band an image.
+template <class Job>
+int batched_fit(const Job *jobs, int32_t count, int th, int64_t limit, int64_t *total)
+{
+    for (;; th *= 2) {
+        int64_t most = 0;
+        int32_t rows = 0;
+        *total = 0;
+        for (int32_t i = 0; i < count; ++i) {
+            *total += batched_count(jobs[i], th);
+            most = std::max(most, batched_image_tiles(jobs[i], th));
+            rows = std::max(rows, jobs[i].Ho);
+        }
+        if (*total <= limit && most <= INT32_MAX) return th;
+        if (th >= rows) return 0;
+    }
+}
+
+// The unit in which the allocation-free call's public limit is counted: per
+// image, strips of 512 columns in chunks of `tallx` * 32 rows, the last
+// 1 / `shortq` of the rows in chunks of 32; the 128-column tiles that no whole
+// strip holds in chunks of 128 rows.
+struct BatchSplit {
+    int tallx;
+    int shortq;
+};
+inline int64_t budget_tiles(int32_t Wo, int32_t Ho, const BatchSplit &sp = BatchSplit{2, 4})
+{
+    const int64_t ntx = ((int64_t)Wo + 127) / 128, strips = ntx / 4, tall = 32 * sp.tallx;
+    const int64_t rows = (Ho - Ho / sp.shortq) / tall * tall;
+    return strips * (rows / tall + (Ho - rows + 31) / 32) + (ntx - 4 * strips) * (((int64_t)Ho + 127) / 128);
+}
+
+// Limits of the allocation-free batched call: images, tiles in that unit, and
+// entries of the tile table (a wave-tile is half as wide as the budget's strip,
+// and rows of tiles are rounded up by at most a sixteenth: a batch within the
+// budget fits with one band an image at the latest).
+constexpr int32_t kNoallocMaxImages = 1024;
+constexpr int32_t kNoallocMaxTiles = 65536;
+constexpr int32_t kNoallocTable = 2 * kNoallocMaxTiles + kNoallocMaxTiles / 4 + kNoallocMaxImages;
+
 }  // namespace s4x5

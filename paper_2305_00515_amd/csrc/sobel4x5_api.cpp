@@ -325,20 +325,20 @@ int plan_setup(sobel4x5_plan_s *p, const U8Shape &shape)
     plan_free_device(p);
     p->shape = shape;
     std::vector<U8Job> jobs(p->count);
-    int64_t total = 0, most = 0;
     for (int32_t i = 0; i < p->count; ++i) {
         jobs[i] = plan_job(p, i);
         u8_tile(jobs[i], shape);
-        total += batched_count(jobs[i], shape.th);
-        most = std::max(most, jobs[i].nt * batched_bands(jobs[i], shape.th));
     }
-    if (total > INT32_MAX || most > INT32_MAX) return fail(SOBEL4X5_EINVAL, "batch too large for one plan");
+    int64_t total = 0;
+    p->shape.th = batched_fit(jobs.data(), p->count, shape.th, shape.waves == kStaticGrid ? kLaunchWaves : INT32_MAX,
+                              &total);
+    if (!p->shape.th) return fail(SOBEL4X5_EINVAL, "batch too large for one plan");
     p->total = (int32_t)total;
     const size_t tiles_off = kNoallocJobsOff + (sizeof(U8Job) * p->count + 255) / 256 * 256;
     std::vector<unsigned char> host(tiles_off + sizeof(int4) * (size_t)total);
     std::memcpy(host.data() + kNoallocJobsOff, jobs.data(), sizeof(U8Job) * p->count);
     int4 *t = reinterpret_cast<int4 *>(host.data() + tiles_off);
-    for (int32_t i = 0; i < p->count; ++i) batched_tiles_each(jobs[i], i, shape.th, [&](int4 e) { *t++ = e; });
+    for (int32_t i = 0; i < p->count; ++i) batched_tiles_each(jobs[i], i, p->shape.th, [&](int4 e) { *t++ = e; });
     hipError_t e;
     if ((e = hipMalloc(&p->d_base, host.size())) != hipSuccess) {
         p->d_base = nullptr;
@@ -996,14 +996,11 @@ int sobel4x5_batched_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *outs
             jobs[i] = make_job(m.src, m.width, m.height, m.src_pitch, Wo, Ho, m.mag, m.mag_pitch, nullptr, 0, 0);
             stores.add(jobs[i]);
         }
-        const U8Shape shape = batch_default_shape(stores);
-        int64_t total = 0, most = 0;
-        for (int32_t i = 0; i < count; ++i) {
-            u8_tile(jobs[i], shape);
-            total += batched_count(jobs[i], shape.th);
-            most = std::max(most, jobs[i].nt * batched_bands(jobs[i], shape.th));
-        }
-        if (shape.waves == kStaticGrid && total <= INT32_MAX && most <= INT32_MAX) {
+        U8Shape shape = batch_default_shape(stores);
+        for (int32_t i = 0; i < count; ++i) u8_tile(jobs[i], shape);
+        int64_t total = 0;
+        shape.th = batched_fit(jobs, count, shape.th, kLaunchWaves, &total);
+        if (shape.waves == kStaticGrid && shape.th) {
             hipError_t e = guard(launch_u8_batched(jobs, nullptr, count, nullptr, border, stores.past_l2(), false, shape,
                                                    0, st));
             return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
@@ -1097,19 +1094,10 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
         if (e != hipSuccess) return hip_fail(e, "batched launch");
     }
     if (captured) return ok();
-    // bands high enough for the table: a batch within the budget fits with
-    // one band an image at the latest
+    // bands high enough for the table
     int64_t total = 0;
-    for (;; shape.th *= 2) {
-        total = 0;
-        int32_t rows = 0;
-        for (int32_t i = 0; i < count; ++i) {
-            total += batched_count(jobs[i], shape.th);
-            rows = std::max(rows, jobs[i].Ho);
-        }
-        if (total <= kNoallocTable) break;
-        if (shape.th >= rows) return fail(SOBEL4X5_EINVAL, "the batch does not fit the allocation-free call's table");
-    }
+    shape.th = batched_fit(jobs, count, shape.th, kNoallocTable, &total);
+    if (!shape.th) return fail(SOBEL4X5_EINVAL, "the batch does not fit the allocation-free call's table");
     int4 *t = reinterpret_cast<int4 *>(stage + kNoallocTilesOff);
     for (int32_t i = 0; i < count; ++i) batched_tiles_each(jobs[i], i, shape.th, [&](int4 e) { *t++ = e; });
     void *scr = nullptr;

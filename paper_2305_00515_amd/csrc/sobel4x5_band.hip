@@ -62,8 +62,7 @@ hipError_t launch_any(const U8Job &j, const BandTaps &taps, int off, int border,
 
 void u8_tile(U8Job &j, const U8Shape &s)
 {
-    const int64_t nt = ((int64_t)j.Wo + s.ppl - 1) / s.ppl, whole = (nt + 7) / 8 * 8;
-    j.nt = (u32)((whole - nt) * 16 <= nt ? whole : nt);
+    j.nt = tile_columns(j.Wo, s.ppl);
     j.inv_nt = (u32)std::min<uint64_t>((1ull << 32) / std::max<u32>(1, j.nt), 0xffffffffull);
 }
 
@@ -140,7 +139,7 @@ hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total
             if (i >= total) continue;
             const U8Job &j = jobs[i];
             b.img[i] = BandImage{j.src, j.mag, j.src_pitch, j.mag_pitch, j.W, j.H, j.nt, j.inv_nt,
-                                 (u32)(j.nt * batched_bands(j, s.th))};
+                                 (u32)batched_image_tiles(j, s.th)};
             waves += batched_count(j, s.th);
         }
         u32 w = (u32)waves;

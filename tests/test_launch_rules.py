@@ -63,6 +63,70 @@ int main() {
 }
 """
 
+BATCH = HEAD + r"""
+#include <random>
+struct Job { uint32_t nt; int32_t Ho; };
+static int doubled = 0;
+static void noalloc(const std::vector<std::pair<int, int>> &sizes, int th) {      // (Wo, Ho) within the budget
+    std::vector<Job> jobs;
+    int64_t budget = 0, total = 0, again = 0;
+    for (auto &s : sizes) {
+        jobs.push_back({tile_columns(s.first, 16), s.second});
+        budget += budget_tiles(s.first, s.second);
+    }
+    if (budget > kNoallocMaxTiles || jobs.size() > (size_t)kNoallocMaxImages) return;
+    const int fit = batched_fit(jobs.data(), (int)jobs.size(), th, kNoallocTable, &total);
+    for (auto &j : jobs) again += batched_count(j, fit ? fit : th);
+    CHECK(fit >= th && total == again && total <= kNoallocTable, "%zu of %d x %d: th %d, %lld entries", jobs.size(),
+          sizes[0].first, sizes[0].second, fit, (long long)total);
+    doubled += fit > th;
+    // no higher than needed
+    if (fit > th) {
+        int64_t less = 0;
+        for (auto &j : jobs) less += batched_count(j, fit / 2);
+        CHECK(less > kNoallocTable, "%zu of %d x %d: th %d", jobs.size(), sizes[0].first, sizes[0].second, fit);
+    }
+}
+int main() {
+    std::mt19937 rng(7);
+    for (int th : {4, 16, 32}) {
+        // as many as the budget takes of one size
+        for (int64_t W : sides())
+            for (int64_t H : sides()) {
+                const int64_t one = budget_tiles((int)W, (int)H);
+                if (one > kNoallocMaxTiles) continue;
+                noalloc(std::vector<std::pair<int, int>>(std::min<int64_t>(kNoallocMaxImages, kNoallocMaxTiles / one), {(int)W, (int)H}), th);
+            }
+        // mixed sizes, filled up to the budget
+        for (int rep = 0; rep < 300; ++rep) {
+            std::vector<std::pair<int, int>> v;
+            const double top = 6 + rng() % 10;
+            int64_t budget = 0;
+            while (v.size() < (size_t)kNoallocMaxImages) {
+                auto side = [&] { return 1 + (int)(rng() % (uint64_t)(1 << (1 + rng() % (int)top))); };
+                const int w = side(), h = side();
+                if ((budget += budget_tiles(w, h)) > kNoallocMaxTiles) break;
+                v.push_back({w, h});
+            }
+            if (!v.empty()) noalloc(v, th);
+        }
+    }
+    CHECK(doubled > 100, "%d batches took higher bands", doubled);
+    // plans: what a launch holds, and an image whose tiles need 32 bits
+    int64_t total = 0;
+    for (int ppl : {8, 16}) {
+        std::vector<Job> tall(12, {tile_columns(1, ppl), 1 << 30});
+        CHECK(batched_fit(tall.data(), 12, 4, kLaunchWaves, &total) > 4 && total <= kLaunchWaves && (total + 3) / 4 * 256 <= kItems, "tall");
+    }
+    Job wide{tile_columns(1 << 30, 8), 200};
+    CHECK(batched_fit(&wide, 1, 4, INT32_MAX, &total) == 16 && batched_image_tiles(wide, 16) <= INT32_MAX, "wide");
+    std::vector<Job> many(3000, {1u << 24, 8});
+    CHECK(batched_fit(many.data(), 3000, 4, INT32_MAX, &total) == 0, "too large");
+    if (!bad) std::puts("ok");
+    return bad != 0;
+}
+"""
+
 
 def run(tmp_path, program):
     cxx = shutil.which("g++") or shutil.which("clang++")
@@ -77,3 +141,21 @@ def run(tmp_path, program):
 
 def test_single_images_and_fp32_batches(tmp_path):
     run(tmp_path, SINGLE)
+
+
+def test_bands_of_batches(tmp_path):
+    run(tmp_path, BATCH)
+
+
+@pytest.mark.gpu
+def test_bands_that_the_table_makes_higher(sobel_lib, gpu, monkeypatch):
+    """80 images of 2048 x 1024 in bands of 4 rows are more wave-tiles than the
+    allocation-free call's table holds: it takes bands of 8, same bytes."""
+    torch = pytest.importorskip("torch")
+    from paper_2305_00515_amd import synth
+    monkeypatch.setenv("SOBEL4X5_BATCH_TH", "4")
+    srcs = [torch.from_numpy(synth.rect_image(2048, 1024, 7 + i)).to(gpu) for i in range(2)] * 40
+    want = [sobel_lib.sobel4x5_u8(s)[0] for s in srcs[:2]]
+    mags = sobel_lib.sobel4x5_batched_noalloc(srcs)
+    torch.cuda.synchronize()
+    assert all(torch.equal(m, want[i % 2]) for i, m in enumerate(mags))
