@@ -506,7 +506,8 @@ std::string tune_key(const sobel4x5_plan_s *p)
     hipDeviceProp_t prop;
     std::memset(&prop, 0, sizeof prop);
     hipGetDeviceProperties(&prop, p->device);
-    // the key describes the workload shape, not the pointers
+    // the key describes the workload shape, not the pointers: sizes, outputs
+    // asked for, and what selects the kernel and the default shape
     uint64_t h = 1469598103934665603ull;
     auto mix = [&](uint64_t v) { h = (h ^ v) * 1099511628211ull; };
     int64_t px = 0;
@@ -515,10 +516,11 @@ std::string tune_key(const sobel4x5_plan_s *p)
         mix((uint64_t)m.height);
         px += (int64_t)m.width * m.height;
     }
+    for (const auto &o : p->outs) mix(((uint64_t)(uint32_t)o.dir_type << 1) | (o.mag != nullptr));
     char buf[256];
-    std::snprintf(buf, sizeof buf, "v%d|k%016llx|%s|b%d|d%d|n%d|px%lld|h%016llx", SOBEL4X5_VERSION,
-                  (unsigned long long)(SOBEL4X5_KERNEL_HASH), prop.gcnArchName, p->border, (int)p->dir, p->count,
-                  (long long)px, (unsigned long long)h);
+    std::snprintf(buf, sizeof buf, "v%d|k%016llx|%s|b%d|d%d|s%d%d|n%d|px%lld|h%016llx", SOBEL4X5_VERSION,
+                  (unsigned long long)(SOBEL4X5_KERNEL_HASH), prop.gcnArchName, p->border, (int)p->dir,
+                  (int)p->stores.past_l2(), (int)p->stores.whole, p->count, (long long)px, (unsigned long long)h);
     std::string key = buf;
     for (char &c : key)
         if (c == ' ' || c == '\n') c = '_';
