@@ -572,7 +572,7 @@ void tune_store(const std::string &key, const U8Shape &s)
 // SOBEL4X5_BATCH_TH (4..256) and SOBEL4X5_BATCH_STATIC (0 or 1) override it.
 U8Shape batch_default_shape(const OutputStores &o)
 {
-    U8Shape s{o.planes ? 8 : 16, o.planes ? (o.whole ? 4 : 8) : o.large() ? 32 : 16, 4};
+    U8Shape s{o.ppl(), o.planes ? (o.whole ? 4 : 8) : o.large() ? 32 : 16, 4};
     s.waves = kStaticGrid;
     const int th = env_int("SOBEL4X5_BATCH_TH", 0);
     if (th >= 4 && th <= 256) s.th = th / 4 * 4;

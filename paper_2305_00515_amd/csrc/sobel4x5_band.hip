@@ -23,13 +23,15 @@ int64_t band_slots()
     return (int64_t)n * kBandResident;
 }
 
-const void *batched_fn(bool dir, bool past)
+template <int NB, int DIR>
+const void *batched_fn(bool past)
 {
-    if (dir)
-        return past ? reinterpret_cast<const void *>(&k_band_batched<2, kPlanesAny, true>)
-                    : reinterpret_cast<const void *>(&k_band_batched<2, kPlanesAny, false>);
-    return past ? reinterpret_cast<const void *>(&k_band_batched<4, 0, true>)
-                : reinterpret_cast<const void *>(&k_band_batched<4, 0, false>);
+    return past ? reinterpret_cast<const void *>(&k_band_batched<NB, DIR, true>)
+                : reinterpret_cast<const void *>(&k_band_batched<NB, DIR, false>);
+}
+const void *batched_fn(const U8Shape &s, bool past, bool dir)
+{
+    return !dir ? batched_fn<4, 0>(past) : s.ppl == 4 ? batched_fn<1, kPlanesAny>(past) : batched_fn<2, kPlanesAny>(past);
 }
 
 int border_mode(int border) { return border == 2 ? kBandZero : border == 3 ? kBandRefl : kBandRep; }
@@ -151,15 +153,15 @@ hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total
     }
     void *args[] = {(void *)&jobs, (void *)&tiles, (void *)&total, (void *)&queue, (void *)&claims,
                     const_cast<BandTaps *>(&kTaps4x5), (void *)&off, (void *)&bm};
-    return hipLaunchKernel(batched_fn(dir, past), dim3(grid), dim3(64 * kBandWaves), args, 0, st);
+    return hipLaunchKernel(batched_fn(s, past, dir), dim3(grid), dim3(64 * kBandWaves), args, 0, st);
 }
 
-int u8_persistent_grid(const U8Shape &, int, bool past, bool dir)
+int u8_persistent_grid(const U8Shape &s, int, bool past, bool dir)
 {
     int dev = 0, ncu = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_fn(dir, past), 64 * kBandWaves, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_fn(s, past, dir), 64 * kBandWaves, 0) != hipSuccess)
         return 0;
     if (per_cu < 1) per_cu = 1;
     return ncu * per_cu;
