@@ -33,7 +33,6 @@ struct U8Job {
 struct U8Shape {
     int ppl;        // batched: pixels per lane (OutputStores::ppl)
     int th;         // batched: rows of a wave's tiles, a multiple of 4
-    int wpg;        // waves per workgroup (4)
     int waves = 0;  // single image: waves to launch (0 = by size); batched: kStaticGrid or a persistent grid
 };
 
@@ -131,7 +130,7 @@ hipError_t noalloc_scratch(void **out);
 
 // Number of workgroups of the persistent kernel that fit on the device at
 // once for shape `s` (occupancy x CUs), or 0 on error.
-int u8_persistent_grid(const U8Shape &s, int border, bool past, bool dir);
+int u8_persistent_grid(const U8Shape &s, bool past, bool dir);
 
 // uint8 operator with run-time weights (four integer kernels that are
 // antisymmetric under a half turn), as coefficients of the 12 upper-half

@@ -8,9 +8,11 @@
 
 namespace s4x5 {
 
-// A launch has fewer than 2^32 work-items: workgroups of four waves, and waves.
-constexpr int64_t kLaunchGroups = 0xffffffffll / 256;
-constexpr int64_t kLaunchWaves = 4 * kLaunchGroups;
+// Every workgroup has four waves.  A launch has fewer than 2^32 work-items, in
+// workgroups and in waves:
+constexpr int kGroupWaves = 4;
+constexpr int64_t kLaunchGroups = 0xffffffffll / (64 * kGroupWaves);
+constexpr int64_t kLaunchWaves = kGroupWaves * kLaunchGroups;
 
 // fp32: row ranges per strip, for a kernel of which `slots` waves are resident
 // at once: as many as fill one round of them (rounding up would leave a few

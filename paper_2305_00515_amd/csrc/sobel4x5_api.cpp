@@ -351,12 +351,12 @@ int plan_setup(sobel4x5_plan_s *p, const U8Shape &shape)
     p->d_queue = reinterpret_cast<uint32_t *>(p->d_base);
     p->d_jobs = reinterpret_cast<U8Job *>(p->d_base + kNoallocJobsOff);
     p->d_tiles = reinterpret_cast<int4 *>(p->d_base + tiles_off);
-    const int need = (p->total + 3) / 4;   // never more workgroups than work (4 waves each)
+    const int need = (int)(((int64_t)p->total + 3) / 4);   // never more workgroups than work (4 waves each)
     if (shape.waves == kStaticGrid) {       // one wave per wave-tile, no queue
         p->grid = std::max(1, need);
         return ok();
     }
-    p->grid = u8_persistent_grid(shape, p->border, p->stores.past_l2(), p->dir);
+    p->grid = u8_persistent_grid(shape, p->stores.past_l2(), p->dir);
     if (p->grid <= 0) {
         plan_free_device(p);
         return fail(SOBEL4X5_EHIP, "could not query occupancy");
@@ -538,9 +538,9 @@ bool tune_lookup(const std::string &key, U8Shape &s)
     while (std::fgets(line, sizeof line, f)) {
         int ppl = 0, th = 0, wpg = 0, st = 0;
         const int n = std::sscanf(line, "%511s %d %d %d %d", k, &ppl, &th, &wpg, &st);
-        if (n >= 4 && key == k && ppl == s.ppl && th >= 4 && th <= 256 && th % 4 == 0 && wpg == 4 &&
+        if (n >= 4 && key == k && ppl == s.ppl && th >= 4 && th <= 256 && th % 4 == 0 && wpg == kGroupWaves &&
             (st == 0 || st == 1)) {
-            s = U8Shape{ppl, th, wpg};
+            s = U8Shape{ppl, th};
             if (n >= 5 && st == 1) s.waves = kStaticGrid;
             found = true;   // last entry wins
         }
@@ -556,7 +556,7 @@ void tune_store(const std::string &key, const U8Shape &s)
     if (slash != std::string::npos && slash > 0) mkdir(path.substr(0, slash).c_str(), 0755);   // best effort
     FILE *f = std::fopen(path.c_str(), "a");
     if (!f) return;
-    std::fprintf(f, "%s %d %d %d %d\n", key.c_str(), s.ppl, s.th, s.wpg, s.waves == kStaticGrid ? 1 : 0);
+    std::fprintf(f, "%s %d %d %d %d\n", key.c_str(), s.ppl, s.th, kGroupWaves, s.waves == kStaticGrid ? 1 : 0);
     std::fclose(f);
 }
 
@@ -572,7 +572,7 @@ void tune_store(const std::string &key, const U8Shape &s)
 // SOBEL4X5_BATCH_TH (4..256) and SOBEL4X5_BATCH_STATIC (0 or 1) override it.
 U8Shape batch_default_shape(const OutputStores &o)
 {
-    U8Shape s{o.ppl(), o.planes ? (o.whole ? 4 : 8) : o.large() ? 32 : 16, 4};
+    U8Shape s{o.ppl(), o.planes ? (o.whole ? 4 : 8) : o.large() ? 32 : 16};
     s.waves = kStaticGrid;
     const int th = env_int("SOBEL4X5_BATCH_TH", 0);
     if (th >= 4 && th <= 256) s.th = th / 4 * 4;
@@ -630,7 +630,7 @@ int plan_autotune(sobel4x5_plan_s *p)
     const int ths[] = {8, 16, 32, 64, 128};
     for (int grid_form = 0; grid_form < 2; ++grid_form)   // persistent, static
         for (int th : ths) {
-            U8Shape c{ref.ppl, th, 4};
+            U8Shape c{ref.ppl, th};
             if (grid_form == 1) c.waves = kStaticGrid;
             if (c.th == ref.th && c.waves == ref.waves) continue;
             int rc;
@@ -966,7 +966,7 @@ int sobel4x5_plan_info(sobel4x5_plan plan, int32_t *px_per_lane, int32_t *rows_p
     if (!plan || plan->magic != kPlanMagic) return fail(SOBEL4X5_EINVAL, "invalid plan handle");
     if (px_per_lane) *px_per_lane = plan->shape.ppl;
     if (rows_per_tile) *rows_per_tile = plan->shape.th;
-    if (waves_per_group) *waves_per_group = plan->shape.wpg;
+    if (waves_per_group) *waves_per_group = kGroupWaves;
     if (grid) *grid = plan->grid;
     return ok();
 }
@@ -1117,7 +1117,7 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     int grid = std::max(1, need);
     uint32_t *queue = nullptr;
     if (shape.waves != kStaticGrid) {
-        grid = u8_persistent_grid(shape, border, stores.past_l2(), false);
+        grid = u8_persistent_grid(shape, stores.past_l2(), false);
         if (grid <= 0) return fail(SOBEL4X5_EHIP, "could not query occupancy");
         grid = std::max(1, std::min(grid, need));
         queue = reinterpret_cast<uint32_t *>(base);

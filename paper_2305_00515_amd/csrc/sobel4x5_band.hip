@@ -41,7 +41,7 @@ hipError_t launch_band(const U8Job &j, const BandTaps &taps, int off, int border
 {
     if (j.Wo <= 0 || j.Ho <= 0) return hipSuccess;
     U8Job job = j;
-    u8_tile(job, U8Shape{4 * NB, 0, kBandWaves});
+    u8_tile(job, U8Shape{4 * NB, 0});
     const int64_t nq = ((int64_t)j.Ho + 3) / 4;
     const int bq = band_steps(job.nt, nq, waves > 0 ? waves : band_slots(), DIR != 0);
     const BandGrid g{(u32)(job.nt * ((nq + bq - 1) / bq)), bq, off, border_mode(border)};
@@ -124,11 +124,6 @@ hipError_t launch_u8_mfma_weighted(const U8Job &j, int border, const int32_t *we
                  : launch_any<4, 4, false, 0>(j, taps, off, border, waves, st);
 }
 
-void batched_tiles(const U8Job &j, int32_t img, int th, int, std::vector<int4> &first, std::vector<int4> &)
-{
-    batched_tiles_each(j, img, th, [&](int4 t) { first.push_back(t); });
-}
-
 hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border, bool past,
                              bool dir, const U8Shape &s, int grid, hipStream_t st, uint32_t *claims)
 {
@@ -156,7 +151,7 @@ hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total
     return hipLaunchKernel(batched_fn(s, past, dir), dim3(grid), dim3(64 * kBandWaves), args, 0, st);
 }
 
-int u8_persistent_grid(const U8Shape &s, int, bool past, bool dir)
+int u8_persistent_grid(const U8Shape &s, bool past, bool dir)
 {
     int dev = 0, ncu = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;

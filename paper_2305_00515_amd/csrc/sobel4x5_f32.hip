@@ -60,7 +60,7 @@
 namespace s4x5 {
 namespace {
 
-constexpr int kWavesPerGroup = 4;
+constexpr int kWavesPerGroup = kGroupWaves;
 typedef float f2v __attribute__((ext_vector_type(2)));
 typedef f2v f2v_a4 __attribute__((aligned(4)));      // a pair at any element
 #define GF __attribute__((address_space(1)))

@@ -80,7 +80,7 @@ typedef u32 u32_u1 __attribute__((aligned(1)));
 typedef const BAND_G uint8_t *gsrc;
 typedef BAND_G uint8_t *gdst;
 
-constexpr int kBandWaves = 4;     // waves per workgroup
+constexpr int kBandWaves = kGroupWaves;
 constexpr int kBandResident = 16; // waves a CU holds: 4 on each SIMD, at up to 128 VGPRs
 
 // Weights of an operator: bytes 0..4 of row[5 f + dy] are the int8 weights of
