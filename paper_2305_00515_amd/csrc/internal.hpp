@@ -39,19 +39,27 @@ struct U8Shape {
 // Fills the tile columns of `j` for tiles of s.ppl pixels (tile_columns).
 void u8_tile(U8Job &j, const U8Shape &s);
 
-// Whether a launch's outputs are stored past the L2 (nontemporal).  Measured on
-// one image, stores past the L2 against stores through it:
-// - rows of whole 64-byte pieces: past it (8192^2 magnitudes 25.1 against
-//   31.0 us, 16384^2 103 against 113; 4096^2 int16 planes 24.6 against 40.5);
-// - other rows, whose ends share lines with a neighbouring wave: planes
-//   through it (4096 x 4104 int16 51.0 against 39.7 us), magnitudes past it
-//   up to 128 MiB of outputs, half of what the Infinity Cache holds to put
-//   the pieces together (8193 x 8192 29.3 against 35.6 us; 11001 x 11000 49.6
-//   against 59.0; 12001 x 12000 74.5 against 70.9; 15001 x 15000 121 against
-//   104).
+// How a launch's outputs are stored: through the L2, past it into the Infinity
+// Cache (agent scope), or past both (nontemporal).  Measured on single images,
+// and with a torch kernel that reads the outputs next:
+// - Rows of whole 64-byte pieces: past the L2 (4096^2 int16 planes 24.6 us past
+//   both, 40.5 through it).  Up to 32 MiB, an eighth of the Infinity Cache, the
+//   outputs stay there for their reader (over many inputs, each converted to
+//   float next: 2160x3840 22.4 us an image, 29.0 past both; 4096^2 37.7 and
+//   50.0; 1080x1920 with int16 planes 37.3 and 39.8), which costs the call
+//   nothing where its output memory is used again (2160x3840 6.49 and 6.66;
+//   4096^2 9.98 and 10.2).  Larger ones are faster alone past both (a few
+//   images in turn: 8192^2 24.8 and 28.2 us, 4096^2 with int16 planes 25.0 and
+//   40.4), and a reader pays for it (8192^2 converted to float 193 and 159).
+// - Other rows, whose ends share lines with a neighbouring wave: planes
+//   through the L2 (4096 x 4104 int16 39.7 us, past both 51.0), magnitudes past
+//   it up to 128 MiB, half of what the Infinity Cache holds to put the pieces
+//   together (8193 x 8192 29.3 us, through the L2 35.6; 11001 x 11000 49.6 and
+//   59.0; 12001 x 12000 74.5 and 70.9; 15001 x 15000 121 and 104).
 struct OutputStores {
+    enum Kind { kThroughL2 = 0, kToCache = 1, kToMemory = 2 };
     bool planes = false, whole = true, s32 = true;
-    int64_t bytes = 0;
+    int64_t pixels = 0, bytes = 0;
     void add(const U8Job &j)
     {
         uint64_t low = 0;
@@ -63,15 +71,22 @@ struct OutputStores {
             for (const void *d : j.dir) low |= reinterpret_cast<uintptr_t>(d);
         }
         whole = whole && (low & 63) == 0;
-        bytes += (int64_t)j.Wo * j.Ho;
+        int64_t each = j.mag != nullptr;
+        for (const void *d : j.dir) each += j.dir_type && d ? 2 * j.dir_type : 0;
+        pixels += (int64_t)j.Wo * j.Ho;
+        bytes += (int64_t)j.Wo * j.Ho * each;
     }
     // Pixels of a batch's lane: 16 bytes of a magnitude row or of a plane's, so
     // that a wave's store covers whole pieces of lines (12 images of 1024^2 with
     // int32 planes 40.6 us, with two stores a lane and plane 90.8; 4 of 2048^2
     // 54.0 and 118.9).  int32 planes beside int16 ones take the int16 form.
     int ppl() const { return !planes ? 16 : s32 ? 4 : 8; }
-    bool large() const { return bytes > ((int64_t)128 << 20); }
-    bool past_l2() const { return whole || (!planes && !large()); }
+    bool large() const { return pixels > ((int64_t)128 << 20); }
+    Kind kind() const
+    {
+        if (!whole && (planes || large())) return kThroughL2;
+        return bytes <= (int64_t)32 << 20 ? kToCache : kToMemory;
+    }
 };
 
 // Single image: one launch of the banded matrix-core kernels (u8_band.hpp),
@@ -97,13 +112,13 @@ hipError_t launch_u8_2dir(const U8Job &j, int op, int border, const U8Shape &s, 
 // or null for one wave per wave-tile.  `border`: the public code; `dir`: some
 // job asks for directional planes, which s.ppl = 4 or 8 can write.  `claims` (device, `total` counters, or
 // null): each wave-tile's counter gains one for every wave that takes it.
-// `past`: outputs are stored past the L2 (OutputStores).
+// `kind`: how outputs are stored (OutputStores).
 // tiles == nullptr: `jobs` is a HOST array of `total` <= kBatchArgs images,
 // magnitudes only, tiled for bands of s.th rows; they go into the kernel's
 // arguments (`queue`, `grid` and `claims` are not looked at).
 constexpr int32_t kBatchArgs = 48;
 hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border,
-                             bool past, bool dir, const U8Shape &s, int grid, hipStream_t stream,
+                             int kind, bool dir, const U8Shape &s, int grid, hipStream_t stream,
                              uint32_t *claims = nullptr);
 
 // Wave-tiles of image `img` (tiled by u8_tile): 16 consecutive tiles of its
@@ -130,7 +145,7 @@ hipError_t noalloc_scratch(void **out);
 
 // Number of workgroups of the persistent kernel that fit on the device at
 // once for shape `s` (occupancy x CUs), or 0 on error.
-int u8_persistent_grid(const U8Shape &s, bool past, bool dir);
+int u8_persistent_grid(const U8Shape &s, int kind, bool dir);
 
 // uint8 operator with run-time weights (four integer kernels that are
 // antisymmetric under a half turn), as coefficients of the 12 upper-half

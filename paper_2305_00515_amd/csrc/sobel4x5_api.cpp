@@ -356,7 +356,7 @@ int plan_setup(sobel4x5_plan_s *p, const U8Shape &shape)
         p->grid = std::max(1, need);
         return ok();
     }
-    p->grid = u8_persistent_grid(shape, p->stores.past_l2(), p->dir);
+    p->grid = u8_persistent_grid(shape, p->stores.kind(), p->dir);
     if (p->grid <= 0) {
         plan_free_device(p);
         return fail(SOBEL4X5_EHIP, "could not query occupancy");
@@ -368,7 +368,7 @@ int plan_setup(sobel4x5_plan_s *p, const U8Shape &shape)
 hipError_t plan_kernel(sobel4x5_plan_s *p, hipStream_t st, uint32_t *claims)
 {
     uint32_t *queue = p->shape.waves == kStaticGrid ? nullptr : p->d_queue;
-    return launch_u8_batched(p->d_jobs, p->d_tiles, p->total, queue, p->border, p->stores.past_l2(), p->dir, p->shape,
+    return launch_u8_batched(p->d_jobs, p->d_tiles, p->total, queue, p->border, p->stores.kind(), p->dir, p->shape,
                              p->grid, st, claims);
 }
 
@@ -520,7 +520,7 @@ std::string tune_key(const sobel4x5_plan_s *p)
     char buf[256];
     std::snprintf(buf, sizeof buf, "v%d|k%016llx|%s|b%d|d%d|s%d%d|n%d|px%lld|h%016llx", SOBEL4X5_VERSION,
                   (unsigned long long)(SOBEL4X5_KERNEL_HASH), prop.gcnArchName, p->border, (int)p->dir,
-                  (int)p->stores.past_l2(), (int)p->stores.whole, p->count, (long long)px, (unsigned long long)h);
+                  (int)p->stores.kind(), (int)p->stores.whole, p->count, (long long)px, (unsigned long long)h);
     std::string key = buf;
     for (char &c : key)
         if (c == ' ' || c == '\n') c = '_';
@@ -1003,7 +1003,7 @@ int sobel4x5_batched_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *outs
         int64_t total = 0;
         shape.th = batched_fit(jobs, count, shape.th, kLaunchWaves, &total);
         if (shape.waves == kStaticGrid && shape.th) {
-            hipError_t e = guard(launch_u8_batched(jobs, nullptr, count, nullptr, border, stores.past_l2(), false, shape,
+            hipError_t e = guard(launch_u8_batched(jobs, nullptr, count, nullptr, border, stores.kind(), false, shape,
                                                    0, st));
             return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
         }
@@ -1092,7 +1092,7 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     if (e != hipSuccess) return hip_fail(e, "batched launch");
     for (int32_t i = 0; captured && i < count; i += kBatchArgs) {
         e = guard(launch_u8_batched(jobs + i, nullptr, std::min(kBatchArgs, count - i), nullptr, border,
-                                    stores.past_l2(), false, shape, 0, st));
+                                    stores.kind(), false, shape, 0, st));
         if (e != hipSuccess) return hip_fail(e, "batched launch");
     }
     if (captured) return ok();
@@ -1117,14 +1117,14 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     int grid = std::max(1, need);
     uint32_t *queue = nullptr;
     if (shape.waves != kStaticGrid) {
-        grid = u8_persistent_grid(shape, stores.past_l2(), false);
+        grid = u8_persistent_grid(shape, stores.kind(), false);
         if (grid <= 0) return fail(SOBEL4X5_EHIP, "could not query occupancy");
         grid = std::max(1, std::min(grid, need));
         queue = reinterpret_cast<uint32_t *>(base);
     }
     e = guard(launch_u8_batched(reinterpret_cast<const U8Job *>(base + kNoallocJobsOff),
                                 reinterpret_cast<const int4 *>(base + kNoallocTilesOff), (int32_t)total, queue,
-                                border, stores.past_l2(), false, shape, grid, st));
+                                border, stores.kind(), false, shape, grid, st));
     return e == hipSuccess ? ok() : hip_fail(e, "batched launch");
 }
 

@@ -24,19 +24,20 @@ int64_t band_slots()
 }
 
 template <int NB, int DIR>
-const void *batched_fn(bool past)
+const void *batched_fn(int kind)
 {
-    return past ? reinterpret_cast<const void *>(&k_band_batched<NB, DIR, true>)
-                : reinterpret_cast<const void *>(&k_band_batched<NB, DIR, false>);
+    return kind == OutputStores::kToCache    ? reinterpret_cast<const void *>(&k_band_batched<NB, DIR, 1>)
+           : kind == OutputStores::kToMemory ? reinterpret_cast<const void *>(&k_band_batched<NB, DIR, 2>)
+                                             : reinterpret_cast<const void *>(&k_band_batched<NB, DIR, 0>);
 }
-const void *batched_fn(const U8Shape &s, bool past, bool dir)
+const void *batched_fn(const U8Shape &s, int kind, bool dir)
 {
-    return !dir ? batched_fn<4, 0>(past) : s.ppl == 4 ? batched_fn<1, kPlanesAny>(past) : batched_fn<2, kPlanesAny>(past);
+    return !dir ? batched_fn<4, 0>(kind) : s.ppl == 4 ? batched_fn<1, kPlanesAny>(kind) : batched_fn<2, kPlanesAny>(kind);
 }
 
 int border_mode(int border) { return border == 2 ? kBandZero : border == 3 ? kBandRefl : kBandRep; }
 
-template <int NB, int NR, bool CLAMP, int DIR, bool PAST>
+template <int NB, int NR, bool CLAMP, int DIR, int TO>
 hipError_t launch_band(const U8Job &j, const BandTaps &taps, int off, int border, int waves, hipStream_t st)
 {
     if (j.Wo <= 0 || j.Ho <= 0) return hipSuccess;
@@ -47,7 +48,7 @@ hipError_t launch_band(const U8Job &j, const BandTaps &taps, int off, int border
     const BandGrid g{(u32)(job.nt * ((nq + bq - 1) / bq)), bq, off, border_mode(border)};
     const u32 groups = (g.tiles + 16 * kBandWaves - 1) / (16 * kBandWaves);
     void *args[] = {&job, const_cast<BandTaps *>(&taps), const_cast<BandGrid *>(&g)};
-    return hipLaunchKernel(reinterpret_cast<const void *>(&k_band_single<NB, NR, CLAMP, DIR, PAST>), dim3(groups),
+    return hipLaunchKernel(reinterpret_cast<const void *>(&k_band_single<NB, NR, CLAMP, DIR, TO>), dim3(groups),
                            dim3(64 * kBandWaves), args, 0, st);
 }
 
@@ -56,8 +57,11 @@ hipError_t launch_any(const U8Job &j, const BandTaps &taps, int off, int border,
 {
     OutputStores o;
     o.add(j);
-    return o.past_l2() ? launch_band<NB, NR, CLAMP, DIR, true>(j, taps, off, border, waves, st)
-                       : launch_band<NB, NR, CLAMP, DIR, false>(j, taps, off, border, waves, st);
+    switch (o.kind()) {
+    case OutputStores::kToCache: return launch_band<NB, NR, CLAMP, DIR, 1>(j, taps, off, border, waves, st);
+    case OutputStores::kToMemory: return launch_band<NB, NR, CLAMP, DIR, 2>(j, taps, off, border, waves, st);
+    default: return launch_band<NB, NR, CLAMP, DIR, 0>(j, taps, off, border, waves, st);
+    }
 }
 
 }  // namespace
@@ -124,7 +128,7 @@ hipError_t launch_u8_mfma_weighted(const U8Job &j, int border, const int32_t *we
                  : launch_any<4, 4, false, 0>(j, taps, off, border, waves, st);
 }
 
-hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border, bool past,
+hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *queue, int border, int kind,
                              bool dir, const U8Shape &s, int grid, hipStream_t st, uint32_t *claims)
 {
     int off = border == 1 ? 2 : 0, bm = border_mode(border);
@@ -142,21 +146,22 @@ hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total
         u32 w = (u32)waves;
         int bq = s.th / 4;
         void *args[] = {(void *)&b, const_cast<BandTaps *>(&kTaps4x5), (void *)&w, (void *)&bq, (void *)&off, (void *)&bm};
-        const void *fn = past ? reinterpret_cast<const void *>(&k_band_args<true>)
-                              : reinterpret_cast<const void *>(&k_band_args<false>);
+        const void *fn = kind == OutputStores::kToCache    ? reinterpret_cast<const void *>(&k_band_args<1>)
+                         : kind == OutputStores::kToMemory ? reinterpret_cast<const void *>(&k_band_args<2>)
+                                                           : reinterpret_cast<const void *>(&k_band_args<0>);
         return hipLaunchKernel(fn, dim3((w + kBandWaves - 1) / kBandWaves), dim3(64 * kBandWaves), args, 0, st);
     }
     void *args[] = {(void *)&jobs, (void *)&tiles, (void *)&total, (void *)&queue, (void *)&claims,
                     const_cast<BandTaps *>(&kTaps4x5), (void *)&off, (void *)&bm};
-    return hipLaunchKernel(batched_fn(s, past, dir), dim3(grid), dim3(64 * kBandWaves), args, 0, st);
+    return hipLaunchKernel(batched_fn(s, kind, dir), dim3(grid), dim3(64 * kBandWaves), args, 0, st);
 }
 
-int u8_persistent_grid(const U8Shape &s, bool past, bool dir)
+int u8_persistent_grid(const U8Shape &s, int kind, bool dir)
 {
     int dev = 0, ncu = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_fn(s, past, dir), 64 * kBandWaves, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_fn(s, kind, dir), 64 * kBandWaves, 0) != hipSuccess)
         return 0;
     if (per_cu < 1) per_cu = 1;
     return ncu * per_cu;

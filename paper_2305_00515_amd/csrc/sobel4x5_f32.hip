@@ -272,11 +272,23 @@ __device__ __forceinline__ F2 load_pair(gin row, uint32_t &oa, uint32_t &ob)
     }
 }
 
-// Stores past the L2: nothing here reads the outputs again.
+// PAST: past the caches (nontemporal).  The adjoint's outputs always go past
+// them: 32 x 1024^2 81 us against 92.5 through, and with the update that reads
+// them next 156.4 against 156.6.  Magnitudes are read next by a loss, and up to
+// 64 MiB they stay in the caches for it (over many inputs, 16 x 1024^2: 29.3 us
+// alone, 49.4 with their sum, 162 a training step; past 32.2, 57.7 and 170; only
+// a caller who keeps all outputs pays, 33.7).  More than that would push the
+// image out, which the adjoint reads again: 32 x 1024^2 past 298 us a step, kept
+// 310, although a sum of the magnitudes takes 92 and 79.
+constexpr int64_t kF32Past = (int64_t)64 << 20;
+template <bool PAST>
 __device__ __forceinline__ void store_pair(gout p, F2 v, bool keep_a, bool keep_b)
 {
     if (keep_a && keep_b) {
-        __builtin_nontemporal_store(f2v{v.a, v.b}, reinterpret_cast<GF f2v_a4 *>(p));
+        if constexpr (PAST)
+            __builtin_nontemporal_store(f2v{v.a, v.b}, reinterpret_cast<GF f2v_a4 *>(p));
+        else
+            *reinterpret_cast<GF f2v_a4 *>(p) = f2v{v.a, v.b};
     } else {
         if (keep_a) *reinterpret_cast<GF float *>(p) = v.a;
         if (keep_b) *reinterpret_cast<GF float *>(p + 4) = v.b;
@@ -289,7 +301,7 @@ __device__ __forceinline__ void store_pair(gout p, F2 v, bool keep_a, bool keep_
 // (centre columns + OFF).  Step t loads input row o0 + OFF - 2 + t and, from
 // t = 4 on, finishes output row o0 + t - 4.  BM is the border rule.
 // IN: every column the wave loads lies inside the image.
-template <int OFF, int BM, bool IN>
+template <int OFF, int BM, bool IN, bool PAST>
 __device__ __forceinline__ void fwd_sweep(const F32Args &a, int b, int s, int o0, int o1)
 {
     const int lane = threadIdx.x & 63;
@@ -341,7 +353,7 @@ __device__ __forceinline__ void fwd_sweep(const F32Args &a, int b, int s, int o0
         // every lane finishes its sums: inside the store's branch the lane
         // shifts could not be part of the additions
         asm volatile("" : "+v"(m.a), "+v"(m.b), "+v"(oa));
-        store_pair(dst + oa, m, keep_a, keep_b);
+        store_pair<PAST>(dst + oa, m, keep_a, keep_b);
         dst += a.out_pitch;
         asm volatile("" : "+s"(dst));
     };
@@ -352,7 +364,7 @@ __device__ __forceinline__ void fwd_sweep(const F32Args &a, int b, int s, int o0
     run_steps<4>(4, T, step);
 }
 
-template <int OFF, int BM>
+template <int OFF, int BM, bool PAST>
 __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_fwd(F32Args a, int nstrip, int nchunk)
 {
     const int wave = blockIdx.x * kWavesPerGroup + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -364,9 +376,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void k_f32_fwd(F32Args a, int 
     if (o1 <= o0) return;
     const int x0 = s * kOwnF - kHaloF + OFF;
     if (x0 >= 0 && x0 + 128 <= a.W && s * kOwnF + kOwnF <= a.Wo)
-        fwd_sweep<OFF, BM, true>(a, b, s, o0, o1);
+        fwd_sweep<OFF, BM, true, PAST>(a, b, s, o0, o1);
     else
-        fwd_sweep<OFF, BM, false>(a, b, s, o0, o1);
+        fwd_sweep<OFF, BM, false, PAST>(a, b, s, o0, o1);
 }
 
 // ---------------------------------------------------------------- adjoint
@@ -485,7 +497,7 @@ __device__ __forceinline__ void bwd_sweep(const F32Args &a, int b, int s, int X0
         asm volatile("" : "+v"(v.a), "+v"(v.b), "+v"(oa));   // (as in the forward)
         gout p = dst + (int64_t)row * a.out_pitch;
         asm volatile("" : "+s"(p));
-        store_pair(p + oa, v, keep_a, keep_b);
+        store_pair<true>(p + oa, v, keep_a, keep_b);
     };
 
     // Step t: the row's filters (all steps), the weighted planes of centre row
@@ -702,13 +714,19 @@ int chunks_for(const void *fn, int64_t strips, int rows, int most)
 
 }  // namespace
 
+template <bool PAST>
+static const void *fwd_fn(const F32Args &a)
+{
+    return a.off          ? reinterpret_cast<const void *>(&k_f32_fwd<2, kClamp, PAST>)
+           : a.bmode == 1 ? reinterpret_cast<const void *>(&k_f32_fwd<0, kZero, PAST>)
+           : a.bmode == 2 ? reinterpret_cast<const void *>(&k_f32_fwd<0, kRefl, PAST>)
+                          : reinterpret_cast<const void *>(&k_f32_fwd<0, kClamp, PAST>);
+}
+
 hipError_t launch_f32_fwd(const F32Args &a, hipStream_t st)
 {
     if (a.B <= 0 || a.Ho <= 0 || a.Wo <= 0) return hipSuccess;
-    const void *fn = a.off ? reinterpret_cast<const void *>(&k_f32_fwd<2, kClamp>)
-                   : a.bmode == 1 ? reinterpret_cast<const void *>(&k_f32_fwd<0, kZero>)
-                   : a.bmode == 2 ? reinterpret_cast<const void *>(&k_f32_fwd<0, kRefl>)
-                                  : reinterpret_cast<const void *>(&k_f32_fwd<0, kClamp>);
+    const void *fn = (int64_t)a.B * a.Ho * a.Wo * 4 > kF32Past ? fwd_fn<true>(a) : fwd_fn<false>(a);
     int nstrip = (a.Wo + kOwnF - 1) / kOwnF;
     int nchunk = chunks_for(fn, (int64_t)a.B * nstrip, a.Ho, 16);
     const int64_t waves = (int64_t)a.B * nstrip * nchunk;

@@ -337,29 +337,33 @@ __device__ __forceinline__ int sum_squares(const int (&G)[NR])
     return S;
 }
 
-// 4 N bytes at any address.  PAST: past the L2 (a constant: the compiler makes
-// one ordinary store of a choice between the two).
-template <bool PAST, int N>
+// 4 N bytes at any address, stored as OutputStores says (a constant: the
+// compiler makes one ordinary store of a choice).  The 4 or 8 bytes of a
+// magnitude beside planes are left to the L2, where they meet their neighbours,
+// unless everything goes past both caches.
+template <int TO, int N>
 __device__ __forceinline__ void store_words(gdst p, const u32 (&w)[N])
 {
     if constexpr (N % 4 == 0) {
 #pragma unroll
         for (int i = 0; i < N; i += 4) {
             const bv4 v{w[i], w[i + 1], w[i + 2], w[i + 3]};
-            if constexpr (PAST)
+            if constexpr (TO == OutputStores::kToMemory)
                 __builtin_nontemporal_store(v, reinterpret_cast<BAND_G bv4_u *>(p + 4 * i));
+            else if constexpr (TO == OutputStores::kToCache)
+                __builtin_amdgcn_global_store_b128(reinterpret_cast<BAND_G bv4 *>(p + 4 * i), v, "agent");
             else
                 *reinterpret_cast<BAND_G bv4_u *>(p + 4 * i) = v;
         }
     } else if constexpr (N == 2) {
         const bv2 v{w[0], w[1]};
-        if constexpr (PAST)
+        if constexpr (TO == OutputStores::kToMemory)
             __builtin_nontemporal_store(v, reinterpret_cast<BAND_G bv2_u *>(p));
         else
             *reinterpret_cast<BAND_G bv2_u *>(p) = v;
     } else {
         static_assert(N == 1, "words");
-        if constexpr (PAST)
+        if constexpr (TO == OutputStores::kToMemory)
             __builtin_nontemporal_store(w[0], reinterpret_cast<BAND_G u32_u1 *>(p));
         else
             *reinterpret_cast<BAND_G u32_u1 *>(p) = w[0];
@@ -389,7 +393,7 @@ __device__ __forceinline__ void store_left(gdst p, const u32 (&w)[N], int left)
 // job says, none included (kPlanesAny).
 constexpr int kPlanes16 = 1, kPlanes32 = 2, kPlanesAny = 3;
 
-template <int NB, int NR, int MODE, bool CLAMP, int DIR, bool PAST>
+template <int NB, int NR, int MODE, bool CLAMP, int DIR, int TO>
 __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T)
 {
     constexpr int NC = 4 * NB;
@@ -468,7 +472,7 @@ __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, in
             const bool full = MODE != kNarrow || left >= NC;
             if (!DIR || J.mag) {
                 if (full)
-                    store_words<PAST>(mag, m);
+                    store_words<TO>(mag, m);
                 else
                     store_left<1>(mag, m, left);
             }
@@ -479,12 +483,12 @@ __device__ __forceinline__ void band_sweep(const U8Job &J, const BandTile &t, in
                     gdst p = (gdst)J.dir[f * 4 / NR] + plane;
                     if ((DIR & kPlanes16) && (DIR != kPlanesAny || J.dir_type == 1)) {
                         if (full)
-                            store_words<PAST>(p, s16[f]);
+                            store_words<TO>(p, s16[f]);
                         else
                             store_left<2>(p, s16[f], left);
                     } else if ((DIR & kPlanes32) && (DIR != kPlanesAny || J.dir_type == 2)) {
                         if (full)
-                            store_words<PAST>(p, s32[f]);
+                            store_words<TO>(p, s32[f]);
                         else
                             store_left<4>(p, s32[f], left);
                     }
@@ -533,7 +537,7 @@ __device__ __forceinline__ BandTile band_tile(const U8Job &J, u32 id, int bq)
     return t;
 }
 
-template <int NB, int NR, bool CLAMP, int DIR, bool PAST>
+template <int NB, int NR, bool CLAMP, int DIR, int TO>
 __device__ __forceinline__ void band_run(const U8Job &J, const BandTile &t, int off, int bm, const BandTaps &T)
 {
     const int x = t.xo + off - 4, y = t.yo + off - 2;
@@ -542,15 +546,15 @@ __device__ __forceinline__ void band_run(const U8Job &J, const BandTile &t, int 
     const bool cols_in = all(x >= 0 && x + 4 * NB + 8 <= J.W && J.Wo >= 4 * NB);
     const bool word = all((((u32)(uintptr_t)J.src + (u32)x) & 3) == 0) && (J.src_pitch & 3) == 0;
     if (rows_in && cols_in && word)
-        band_sweep<NB, NR, kInside, CLAMP, DIR, PAST>(J, t, off, bm, T);
+        band_sweep<NB, NR, kInside, CLAMP, DIR, TO>(J, t, off, bm, T);
     else if (rows_in && cols_in)
-        band_sweep<NB, NR, kShift, CLAMP, DIR, PAST>(J, t, off, bm, T);
+        band_sweep<NB, NR, kShift, CLAMP, DIR, TO>(J, t, off, bm, T);
     else if (rows_in && J.Wo >= 4 * NB)
-        band_sweep<NB, NR, kCols, CLAMP, DIR, PAST>(J, t, off, bm, T);
+        band_sweep<NB, NR, kCols, CLAMP, DIR, TO>(J, t, off, bm, T);
     else if (J.Wo >= 4 * NB)
-        band_sweep<NB, NR, kEdge, CLAMP, DIR, PAST>(J, t, off, bm, T);
+        band_sweep<NB, NR, kEdge, CLAMP, DIR, TO>(J, t, off, bm, T);
     else
-        band_sweep<NB, NR, kNarrow, CLAMP, DIR, PAST>(J, t, off, bm, T);
+        band_sweep<NB, NR, kNarrow, CLAMP, DIR, TO>(J, t, off, bm, T);
 }
 
 struct BandGrid {
@@ -567,7 +571,7 @@ __device__ __forceinline__ u32 band_workgroup(u32 b, u32 groups)
     return b < 8 * per ? (b & 7) * per + b / 8 : b;
 }
 
-template <int NB, int NR, bool CLAMP, int DIR, bool PAST>
+template <int NB, int NR, bool CLAMP, int DIR, int TO>
 __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(DIR ? 3 : 4, 4))) void k_band_single(
     const U8Job J, const BandTaps T, const BandGrid gr)
 {
@@ -575,7 +579,7 @@ __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu
     const u32 id = min(16 * wave + (threadIdx.x & 15), gr.tiles - 1);
     const BandTile t = band_tile<NB>(J, id, gr.bq);
     if (16 * wave >= gr.tiles) return;
-    band_run<NB, NR, CLAMP, DIR, PAST>(J, t, gr.off, gr.bm, T);
+    band_run<NB, NR, CLAMP, DIR, TO>(J, t, gr.off, gr.bm, T);
 }
 
 // Batch of images: wave-tile t of the host-built table is {image, first tile,
@@ -586,7 +590,7 @@ __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu
 // (debug launches only, else nullptr): one counter per wave-tile, plus one
 // for every time a wave takes it, so a launch that leaves any counter other
 // than 1 has skipped or repeated one.
-template <int NB, int DIR, bool PAST>
+template <int NB, int DIR, int TO>
 __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(DIR ? 3 : 4, 4))) void k_band_batched(
     const U8Job *__restrict__ jobs, const int4 *__restrict__ table, int32_t total, uint32_t *queue, uint32_t *claims,
     const BandTaps T, int off, int bm)
@@ -605,7 +609,7 @@ __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu
         const U8Job J = jobs[e.x];
         if (claims != nullptr && (threadIdx.x & 63) == 0) atomicAdd(&claims[t], 1u);
         const BandTile tile = band_tile<NB>(J, min((u32)e.y + (threadIdx.x & 15), (u32)e.w - 1), e.z);
-        band_run<NB, 4, false, DIR, PAST>(J, tile, off, bm, T);
+        band_run<NB, 4, false, DIR, TO>(J, tile, off, bm, T);
         if (queue == nullptr) break;
     }
     if (queue == nullptr) return;
@@ -636,7 +640,7 @@ struct BandImages {
     u32 first[64];      // first wave of each image, ~0 beyond the last one
 };
 
-template <bool PAST>
+template <int TO>
 __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_band_args(
     const BandImages B, const BandTaps T, u32 waves, int bq, int off, int bm)
 {
@@ -657,7 +661,7 @@ __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu
     J.inv_nt = I.inv_nt;
     const BandTile t = band_tile<4>(J, min(16 * (w - B.first[i]) + (threadIdx.x & 15), I.tiles - 1), bq);
     if (w >= waves) return;
-    band_run<4, 4, false, 0, PAST>(J, t, off, bm, T);
+    band_run<4, 4, false, 0, TO>(J, t, off, bm, T);
 }
 
 }  // namespace

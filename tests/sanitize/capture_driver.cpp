@@ -14,6 +14,7 @@ namespace {
 bool capturing = false;
 struct Launch {
     bool in_arguments;            // the images travel in the kernel's arguments
+    int kind;                     // how outputs are stored
     std::vector<const uint8_t *> srcs;
 };
 std::vector<Launch> launches;
@@ -36,10 +37,10 @@ void u8_tile(U8Job &j, const U8Shape &s)
     j.nt = (uint32_t)((j.Wo + s.ppl - 1) / s.ppl);
     j.inv_nt = 0;
 }
-hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *, int, bool, bool,
+hipError_t launch_u8_batched(const U8Job *jobs, const int4 *tiles, int32_t total, uint32_t *, int, int kind, bool,
                              const U8Shape &, int, hipStream_t, uint32_t *)
 {
-    Launch l{tiles == nullptr, {}};
+    Launch l{tiles == nullptr, kind, {}};
     for (int32_t i = 0; i < total; ++i) l.srcs.push_back(jobs[tiles ? tiles[i].x : i].src);
     launches.push_back(l);
     return hipSuccess;
@@ -54,7 +55,7 @@ hipError_t launch_u8_single(const U8Job &, int, const U8Shape &, hipStream_t) { 
 bool mfma_weights_fit(const int32_t *) { return false; }
 hipError_t launch_u8_mfma_weighted(const U8Job &, int, const int32_t *, int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_u8_2dir(const U8Job &, int, int, const U8Shape &, hipStream_t) { return hipErrorNoDevice; }
-int u8_persistent_grid(const U8Shape &, bool, bool) { return 0; }
+int u8_persistent_grid(const U8Shape &, int, bool) { return 0; }
 hipError_t launch_u8_weighted(const WJob &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_copy16(const void *, void *, int64_t, hipStream_t) { return hipErrorNoDevice; }
 int64_t fingerprint_blocks(int64_t rows) { return rows; }
@@ -161,6 +162,18 @@ int main()
         launches.clear();
         CHECK(sobel4x5_batched_noalloc(imgs.data(), count, 0, st) == SOBEL4X5_OK);
         CHECK(launches.size() == 1 && !launches[0].in_arguments && allocations == 0);
+    }
+
+    // Outputs stay in the Infinity Cache up to 32 MiB.
+    {
+        std::vector<uint8_t> in((size_t)4096 * 8193), out((size_t)4096 * 8193 + 64);
+        uint8_t *line = out.data() + (64 - (uintptr_t)out.data() % 64) % 64;
+        for (int rows : {8192, 8193}) {
+            const sobel4x5_image one = {in.data(), line, 4096, rows, 4096, 4096};
+            launches.clear();
+            CHECK(sobel4x5_batched(&one, 1, 0, st) == SOBEL4X5_OK && launches.size() == 1);
+            CHECK(launches[0].kind == (rows == 8192 ? s4x5::OutputStores::kToCache : s4x5::OutputStores::kToMemory));
+        }
     }
 
     if (bad) return 1;

@@ -12,12 +12,12 @@ hipError_t launch_u8_single(const U8Job &, int, const U8Shape &, hipStream_t) { 
 bool mfma_weights_fit(const int32_t *) { return false; }
 hipError_t launch_u8_mfma_weighted(const U8Job &, int, const int32_t *, int, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_u8_2dir(const U8Job &, int, int, const U8Shape &, hipStream_t) { return hipErrorNoDevice; }
-hipError_t launch_u8_batched(const U8Job *, const int4 *, int32_t, uint32_t *, int, bool, bool, const U8Shape &, int,
+hipError_t launch_u8_batched(const U8Job *, const int4 *, int32_t, uint32_t *, int, int, bool, const U8Shape &, int,
                              hipStream_t, uint32_t *)
 {
     return hipErrorNoDevice;
 }
-int u8_persistent_grid(const U8Shape &, bool, bool) { return 0; }
+int u8_persistent_grid(const U8Shape &, int, bool) { return 0; }
 hipError_t launch_u8_weighted(const WJob &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_copy16(const void *, void *, int64_t, hipStream_t) { return hipErrorNoDevice; }
 int64_t fingerprint_blocks(int64_t rows) { return rows; }

@@ -8,6 +8,7 @@ in front of inline asm.  So no asm instruction may come closer than two wait
 states to the vector instruction that wrote its scalar operand, and none may be
 the first to read a product's result.
 """
+import functools
 import os
 import re
 import subprocess
@@ -74,15 +75,20 @@ def test_reader_finds_what_it_looks_for():
     assert not findings(head + "v_mfma_i32_16x16x64_i8 v[2:5], v[10:13], v[14:17], 0\nv_mul_i32_i24 v6, v3, v3\n" + asm)
 
 
-@pytest.mark.parametrize("source", [s for s in build.SOURCES if s.endswith(".hip")])
-def test_no_asm_before_its_operand_is_ready(tmp_path, source):
+@functools.lru_cache(None)
+def listing_of(source):
+    """The assembly of a kernel source."""
     try:
         build.hipcc()
     except RuntimeError:
         pytest.skip("no hipcc")
-    out = tmp_path / "k.s"
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
-    subprocess.run([build.hipcc()] + flags + ["-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, source)],
-                   check=True, capture_output=True)
-    bad = findings(out.read_text())
+    return subprocess.run([build.hipcc()] + flags + ["-S", "--cuda-device-only", "-o", "-",
+                                                     os.path.join(build.CSRC, source)],
+                          check=True, capture_output=True, text=True).stdout
+
+
+@pytest.mark.parametrize("source", [s for s in build.SOURCES if s.endswith(".hip")])
+def test_no_asm_before_its_operand_is_ready(source):
+    bad = findings(listing_of(source))
     assert not bad, "%d places, e.g. %s" % (len(bad), bad[:3])
