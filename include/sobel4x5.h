@@ -329,10 +329,10 @@ int sobel4x5_validate_batch_ex(const sobel4x5_image *imgs, const sobel4x5_output
  *   directly, others, and small images of odd width that leave rows over,
  *   through the staging buffers) with the given border; magnitude only.
  *   Synchronous: returns when every magnitude is in host memory.  A pipeline
- *   must not be run by two threads at once.  On an EHIP return every copy and kernel the call
- *   queued has finished (nothing writes a caller buffer afterwards), the
- *   magnitudes of this call's images are unspecified, and the pipeline is
- *   idle and reusable with any other image array.
+ *   must not be run by two threads at once.  On an EHIP return every copy and
+ *   kernel the call queued has finished (nothing writes a caller buffer
+ *   afterwards), the magnitudes of this call's images are unspecified, and the
+ *   pipeline is idle and reusable with any other image array.
  * sobel4x5_pipe_destroy -- wait for nothing, free everything.
  */
 typedef struct sobel4x5_pipe_s *sobel4x5_pipe;
@@ -393,12 +393,13 @@ int sobel4x5_debug_round_mag(const int32_t *S, uint8_t *out, int64_t n, void *st
 int sobel4x5_debug_round_mag_ex(const int32_t *S, uint8_t *out, int64_t n, int32_t method, void *stream);
 
 /*
- * Diagnostic: the four-directional magnitude's rounding from the half sums
- * and differences that its kernel multiplies out, E1 = (Gx + Gy)/2,
- * E2 = (Gx - Gy)/2, Hp = (Gd + Gdt)/2 and Hm = (Gd - Gdt)/2, for which
- * S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2) (Eq. (sobel5_2)).  q: n quadruples
- * (E1, E2, Hp, Hm) of int16 (device, 8 bytes each); out[i] (device) receives the byte of quadruple i, which
- * must equal min(255, round(sqrt(S))) for every int16 quadruple.
+ * Diagnostic: the kernels' clamp, squares and rounding on the half sums and
+ * differences E1 = (Gx + Gy)/2, E2 = (Gx - Gy)/2, Hp = (Gd + Gdt)/2 and
+ * Hm = (Gd - Gdt)/2, for which S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2)
+ * (Eq. (sobel5_2); the kernels themselves square the responses as they are).
+ * q: n quadruples (E1, E2, Hp, Hm) of int16 (device, 8 bytes each); out[i]
+ * (device) receives the byte of quadruple i, which must equal
+ * min(255, round(sqrt(S))) for every int16 quadruple.
  * EINVAL for n < 0 or NULL pointers with n > 0.
  */
 int sobel4x5_debug_round_quad(const int16_t *q, uint8_t *out, int64_t n, void *stream);

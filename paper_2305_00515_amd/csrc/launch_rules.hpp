@@ -33,16 +33,17 @@ inline int f32_ranges(int64_t slots, int64_t strips, int rows, int most)
 
 // Single uint8 image: steps (of four rows) of a wave's bands, for nt tile
 // columns, nq quads of rows and `slots` resident waves of 16 tiles.
+// (Times of calls back to back on one set of buffers.)
 // - The fewest steps with which all waves are resident at once, as a wave that
-//   waits for a slot starts with a trip to memory (4096^2 at 4 steps 10.7 us,
-//   at 2 12.1; 3840x2160 at 2 steps 6.9 us, at 1 8.5).  Above one step an
-//   even number (the steps come in pairs: 4001x2999 9.1 us at 4 steps, 10.0
-//   at 3).  At most 8 steps: larger images run several rounds, which hide
-//   each other's first loads and end more evenly (16384^2: 103.6 us at 8
-//   steps, 114.8 at 64; 8192^2: 25.8 at 8 and 25.7 at 16).
+//   waits for a slot starts with a trip to memory (4096^2 at 4 steps 8.1 us, at
+//   2 9.1, at 1 11.2; 3840x2160 at 2 steps 5.9 us, at 1 7.2).  Above one step
+//   an even number (the steps come in pairs: 4001x2999 7.0 us at 4 steps, 7.2
+//   at 3).  At most 8 steps: larger images run several rounds, which hide each
+//   other's first loads and end more evenly (4096^2 9.6 us at 16 steps and 29.7
+//   at 64; 8192^2 25.0 at 8, 24.7 at 16 and 30.7 at 64).
 // - With planes one step: the stores bound it, and many short waves store in
-//   the order of memory (4096^2 with int16 planes 24.6 us at 1 step, 27.8 at
-//   2, 31.5 at 8; int32 52.5, 53.3, 55.0).
+//   the order of memory (the four planes of 4096^2, int16, 23.1 us at 1 step,
+//   23.6 at 2, 26.1 at 8; int32 46.6, 47.8, 49.7).
 // More only where a launch would not hold the waves.
 inline int band_steps(int64_t nt, int64_t nq, int64_t slots, bool planes)
 {

@@ -568,7 +568,8 @@ void tune_store(const std::string &key, const U8Shape &s)
 //   2101^2: 36.2 and 34.6, 40 of 64..1080: 18.1 and 16.6);
 // - 4 rows with directional planes, which are bound by their stores, or 8
 //   where rows share lines (32 images of 128..4096 with int16 planes: 312 us
-//   at 8 rows, 361 at 4 and at 16).
+//   at 8 rows, 361 at 4 and at 16; int32: 4 of 2048^2 54.0 us at 4 rows, 57.5
+//   at 8; 6 of 2999x3001 260 and 196).
 // SOBEL4X5_BATCH_TH (4..256) and SOBEL4X5_BATCH_STATIC (0 or 1) override it.
 U8Shape batch_default_shape(const OutputStores &o)
 {
@@ -987,7 +988,7 @@ int sobel4x5_batched_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *outs
     hipStream_t st = static_cast<hipStream_t>(stream);
     // A few images' magnitudes: the images go into the kernel's arguments, and
     // the call keeps nothing.  (16 images of 64..640: 5 us a launch, where a
-    // a plan's look-up and launch take 9 and a new plan 100.)
+    // plan's look-up and launch take 9 and a new plan 100.)
     if (!outs && count <= kBatchArgs) {
         U8Job jobs[kBatchArgs];
         OutputStores stores;

@@ -31,14 +31,16 @@
 // the ones whose whole stencil chain lies inside its lanes (forward: 2
 // columns of halo per side, adjoint: 6).
 //
-// What bounds it (32 x 1024^2): the forward memory, 268 MB in 59 us, 4.6 TB/s;
-// a plain copy of its bytes takes 54 us.  The adjoint its arithmetic: 72
-// vector instructions a column and row step, 77 us at the full issue rate with
-// the halo columns and the 8 warm-up rows of a 73-row range, in 97 us; a copy
-// of its 403 MB takes 81.  Together 147 us, 190 before:
+// What bounds it (32 x 1024^2): the forward memory, 268 MB in 50 us on one set
+// of buffers and 60 on several in turn, 4.5 to 5.4 TB/s; a plain copy of its
+// bytes takes 54 us.  The adjoint its arithmetic: 72 vector instructions a
+// column and row step, 77 us at the full issue rate with the halo columns and
+// the 8 warm-up rows of a 73-row range, in 81 us; a copy of its 403 MB takes 81.
+// Together 146 us among other work, 190 before.  What counted (times of the
+// pair's parts among other work):
 //   - strips inside the image load and store a lane's pair in one piece, past
-//     the L2 on the way out (forward 77 -> 67 us, adjoint 118 -> 105, with the
-//     next two);
+//     the caches on the way out where that is better (store_pair; forward 77 ->
+//     67 us, adjoint 118 -> 105, with the next two);
 //   - rows are walked in scalar registers, and the loads add a 32-bit lane
 //     offset to them: no vector instruction addresses memory;
 //   - the warm-up steps compute only the stages whose rows are there;

@@ -77,7 +77,8 @@ __global__ void k_round_mag_int(const int32_t *S, uint8_t *out, int64_t n)
 }
 
 // Quadruples (E1, E2, Hp, Hm) of int16, S = 2 (E1^2 + E2^2 + Hp^2 + Hm^2): the
-// clamp, the 24-bit squares and the rounding of the kernels.  The halves
+// clamp, the 24-bit squares and the rounding of the kernels, on a form of S that
+// no kernel forms itself.  The halves
 // E1 = (Gx + Gy) / 2, ... reach sqrt(S / 2), so they are clamped at 256 like
 // a response: one that is larger saturates the magnitude alone.
 __global__ __launch_bounds__(256) void k_round_quad(const int16_t *q, uint8_t *out, int64_t n)

@@ -36,11 +36,13 @@
 // What bounds it: memory.  A four-directional magnitude takes 9.3 vector
 // instructions and one product a pixel (8192^2: 10.7 M wave instructions,
 // 1.05 M of them products; 18 us of issue), and HBM moves 1.03 times the
-// input and 1.00 times the output.  8192^2 takes 25.8 us, 5.2 TB/s, where a
-// plain copy of the same bytes takes 27.0 us; the packed int16 sweep that
-// ran here before took 20.4 instructions a pixel and 45.1 us.  What counted:
-//   - 16-byte stores past the L2 (nontemporal): 31.7 -> 25.8 us, and rows
-//     of the output that are not aligned to lines cost 2 us instead of 5;
+// input and 1.00 times the output.  8192^2 takes 30.0 us from HBM (buffers in
+// turn, 4.5 TB/s) and 25.0 us on one pair of buffers, which the Infinity Cache
+// holds in part and where torch's copy of the same bytes takes 27.0 us; the
+// packed int16 sweep that ran here before took 20.4 instructions a pixel and
+// 45.1 us.  What counted, on one pair of buffers:
+//   - 16-byte stores past the L2: 31.7 -> 25.8 us, and rows of the output
+//     that are not aligned to lines cost 2 us instead of 5;
 //   - windows loaded at multiples of 4 bytes: at odd addresses (kShift) a
 //     launch took 38 us before, 33 us with it (26.8 us with the stores above);
 //   - neighbouring workgroups on one XCD: 35.7 -> 31.7 us;
@@ -639,6 +641,10 @@ struct BandImages {
     BandImage img[kBatchArgs];
     u32 first[64];      // first wave of each image, ~0 beyond the last one
 };
+
+// (256 bytes of the 4 KB of arguments belong to the runtime)
+static_assert(kBatchArgs < 64 && sizeof(BandImages) + sizeof(BandTaps) + 4 * sizeof(u32) + 256 <= 4096,
+              "one lane an image, and a kernel's arguments");
 
 template <int TO>
 __global__ __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_band_args(
