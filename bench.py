@@ -438,7 +438,7 @@ def bench_copy(torch, api, dev, steps):
 #            products, which issue beside them ((SQ_INSTS_VALU -
 #            SQ_INSTS_MFMA) x 64 / pixels from the same profile); one of them,
 #            the square root, issues at a lower rate.
-U8_PROFILE = {"src_sha256": "74f2b287e172847d", "traffic_bytes": 136018432,
+U8_PROFILE = {"src_sha256": "9d0f2d1f6afe53c7", "traffic_bytes": 135996288,
               "valu_slots_per_px": (10749052 - 1048576) * 64 / 8192.0 ** 2}
 
 
