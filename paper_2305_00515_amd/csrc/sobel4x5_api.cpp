@@ -668,13 +668,16 @@ PlanCache &plan_cache()
     return *c;
 }
 
-// Whether `st` is being captured into a graph (the null stream cannot be).
-hipError_t is_captured(hipStream_t st, bool *captured)
+// Whether `st` is being captured into a graph (the null stream cannot be; what
+// is wrong with a stream that cannot be asked, the launch on it will say).
+bool is_captured(hipStream_t st)
 {
     hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    const hipError_t e = st ? hipStreamIsCapturing(st, &s) : hipSuccess;
-    *captured = s != hipStreamCaptureStatusNone;
-    return e;
+    if (st && hipStreamIsCapturing(st, &s) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return s != hipStreamCaptureStatusNone;
 }
 
 // Key of a one-shot batched call, from the descriptor fields one by one (not
@@ -1012,9 +1015,7 @@ int sobel4x5_batched_ex(const sobel4x5_image *imgs, const sobel4x5_outputs *outs
     // A graph would replay the launch with the cached plan's tables, which the
     // cache frees at its own time: only a plan that the caller holds may be
     // captured.
-    bool captured;
-    if (hipError_t e = is_captured(st, &captured); e != hipSuccess) return hip_fail(e, "batched launch");
-    if (captured)
+    if (is_captured(st))
         return fail(SOBEL4X5_EUNSUPPORTED, "a stream capture takes batches of up to %d magnitudes; others need a plan "
                     "(sobel4x5_plan_create) that outlives the graph", kBatchArgs);
     int dev = 0;
@@ -1088,9 +1089,8 @@ int sobel4x5_batched_noalloc(const sobel4x5_image *imgs, int32_t count, int32_t 
     // Under capture the copies below would read `stage` again at every replay,
     // and the device buffer would hold whatever call came last: the images go
     // into kernel arguments instead, which the graph keeps.
-    bool captured;
-    hipError_t e = is_captured(st, &captured);
-    if (e != hipSuccess) return hip_fail(e, "batched launch");
+    hipError_t e = hipSuccess;
+    const bool captured = is_captured(st);
     for (int32_t i = 0; captured && i < count; i += kBatchArgs) {
         e = guard(launch_u8_batched(jobs + i, nullptr, std::min(kBatchArgs, count - i), nullptr, border,
                                     stores.kind(), false, shape, 0, st));
